@@ -42,7 +42,8 @@ struct Scratch {
   DevBuf acc[2];
   DevBuf frontier[2];
   DevBuf counts;     // frontier sizes per level
-  DevBuf counters;   // 5 x (L + 1) uint64
+  DevBuf counters;   // 6 x (L + 1) uint64
+  DevBuf count_rows; // per level: the shards of its counters and contribution mass
   DevBuf colparams;  // per-column theta / unit / qid
   DevBuf partial;    // per-block partial norms
   DevBuf flags;      // error and signal flags

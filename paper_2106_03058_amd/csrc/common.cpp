@@ -55,6 +55,7 @@ void Scratch::release() {
   for (auto& b : frontier) b.release();
   counts.release();
   counters.release();
+  count_rows.release();
   colparams.release();
   partial.release();
   flags.release();

@@ -358,6 +358,29 @@ __global__ void k_arc_factors(const uint32_t* __restrict__ nd, const double* __r
     out[j] = da[nd[j]];
 }
 
+// The counter rows of level blockIdx.x added up: its counters and mass.
+__global__ __launch_bounds__(kWave) void k_fold_counts(const unsigned long long* __restrict__ rows,
+                                                       unsigned long long* __restrict__ counters,
+                                                       double* __restrict__ mass) {
+  static_assert(kCountShards == kWave, "one row per lane");
+  const int lane = lane_id();
+  const unsigned long long* row =
+      rows + (static_cast<size_t>(blockIdx.x) * kCountShards + lane) * kCountStride;
+  unsigned long long v[kNumCounters];
+#pragma unroll
+  for (int k = 0; k < kNumCounters; ++k) v[k] = row[k];
+  double m = reinterpret_cast<const double*>(row)[kCountMass];
+#pragma unroll
+  for (int k = 0; k < kNumCounters; ++k) v[k] = wave_sum_u64(v[k]);
+#pragma unroll
+  for (int off = kWave / 2; off > 0; off >>= 1) m += __shfl_down(m, off);
+  if (lane == 0) {
+#pragma unroll
+    for (int k = 0; k < kNumCounters; ++k) counters[static_cast<size_t>(blockIdx.x) * kNumCounters + k] = v[k];
+    mass[blockIdx.x] = m;
+  }
+}
+
 // ------------------------------------------------------------ driver
 constexpr int kSparseShift = 5;  // sparse levels: frontier below n C / 32
 constexpr int kBinShift = 3;     // binned levels: estimated pushes reach n C / 8
@@ -460,6 +483,7 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
       (rc = sc.frontier[1].reserve(cells * sizeof(uint64_t), false, s)) ||
       (rc = sc.counts.reserve(sizeof(unsigned long long) * (AGP_MAX_LEVELS + 2), false, s)) ||
       (rc = sc.counters.reserve(sizeof(unsigned long long) * kNumCounters * (AGP_MAX_LEVELS + 1), false, s)) ||
+      (rc = sc.count_rows.reserve(kCountLevelBytes * (L + 1), false, s)) ||
       (rc = sc.colparams.reserve(sizeof(ColParams) * C + sizeof(uint32_t) * C, false, s)) ||
       (rc = sc.partial.reserve(sizeof(double) * (size_t)std::max<int64_t>(tblocks, 1) * C, false, s)) ||
       (rc = sc.flags.reserve(sizeof(int) * 4, false, s)) ||
@@ -480,7 +504,7 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
       (reinterpret_cast<uintptr_t>(mode + AGP_MAX_LEVELS + 2) + 255) & ~static_cast<uintptr_t>(255));
   AGP_HIP(hipMemsetAsync(sc.levelinfo.ptr, 0, sc.levelinfo.bytes, s));
   AGP_HIP(hipMemsetAsync(counts, 0, sc.counts.bytes, s));
-  AGP_HIP(hipMemsetAsync(counters, 0, sc.counters.bytes, s));
+  AGP_HIP(hipMemsetAsync(sc.count_rows.ptr, 0, kCountLevelBytes * (L + 1), s));
   AGP_HIP(hipMemsetAsync(flags, 0, sc.flags.bytes, s));
   if (qids) AGP_HIP(hipMemcpyAsync(dq, qids, sizeof(uint32_t) * C, hipMemcpyHostToDevice, s));
 
@@ -631,8 +655,7 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
   A.su = C;
   A.sc = 1;
   A.xld = ldc;
-  A.counters = counters;
-  A.mass = mass;
+  A.counters = sc.count_rows.as<unsigned long long>();
   A.err = flags;
   A.positive = positive ? 1 : 0;
   A.dense_cut = std::max<unsigned long long>(1ull, static_cast<unsigned long long>(cells >> tune.sparse_shift));
@@ -791,6 +814,7 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
                                              mode + i + 1);
       if (timed) (void)hipEventRecord(ev[4 * i + 3], s);
     }
+    k_fold_counts<<<L + 1, kWave, 0, s>>>(sc.count_rows.as<unsigned long long>(), counters, mass);
   };
   if (tune.capture == 1) {
     // key: everything the captured kernels take by value
@@ -810,6 +834,7 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
     k.append(reinterpret_cast<const char*>(&samp_rows), sizeof(samp_rows));
     k.append(reinterpret_cast<const char*>(&samp_items), sizeof(samp_items));
     k.append(reinterpret_cast<const char*>(&sc.rec[1].ptr), sizeof(void*));
+    k.append(reinterpret_cast<const char*>(&sc.count_rows.ptr), sizeof(void*));
     k.append(reinterpret_cast<const char*>(&A.nodefac), sizeof(void*));
     k.append(reinterpret_cast<const char*>(&A.arcfac), sizeof(void*));
     hipGraphExec_t exec = nullptr;
@@ -1527,7 +1552,10 @@ using namespace lvl;
 // for callers that cannot allocate.  In host code `scratch` names a host-side
 // stand-in: only the address hipGetSymbolAddress returns for the current
 // device may reach a kernel or a copy.
-static __device__ __align__(256) unsigned char scratch[AGP_NOALLOC_SCRATCH_BYTES];
+// The counter rows lie after the AGP_NOALLOC_SCRATCH_BYTES that the buffers
+// of a call's cells share.
+constexpr size_t kNoAllocCountBytes = kCountLevelBytes * (AGP_MAX_LEVELS + 1);
+static __device__ __align__(256) unsigned char scratch[AGP_NOALLOC_SCRATCH_BYTES + kNoAllocCountBytes];
 
 namespace {
 constexpr int kNoAllocDevices = 64;
@@ -1601,6 +1629,9 @@ int propagate_noalloc(agp_graph* g, double a, double b, const double* w, int32_t
                                 std::to_string(cells * 2 * (sizeof(Cell) + sizeof(uint64_t))) +
                                 " bytes of scratch; the fixed array holds " +
                                 std::to_string(static_cast<size_t>(AGP_NOALLOC_SCRATCH_BYTES)));
+  v.count_rows.ptr = static_cast<char*>(g_noalloc_base[dev]) + AGP_NOALLOC_SCRATCH_BYTES;
+  v.count_rows.bytes = kNoAllocCountBytes;
+  v.count_rows.borrowed = true;
   // the residue accumulators start at zero (the array keeps the last call's contents)
   const size_t words = 2 * cells * sizeof(Cell) / sizeof(unsigned long long);
   k_zero_words<<<grid_for(static_cast<int64_t>(words > 0 ? words : 1), 256, 4096), 256, 0, s>>>(
