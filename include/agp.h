@@ -264,8 +264,9 @@ typedef struct agp_tuning {
   int32_t tile_columns; /* columns per tile; 0: the widest tile that fits       */
   int32_t big_row;      /* deterministic pushes from which an entry's row is
                            deferred to a grid-wide kernel; 0: 4096              */
-  int32_t big_items;    /* sampled work items (16 windows each) from which an
-                           entry's sampled suffix is deferred; 0: 64            */
+  int32_t big_items;    /* sampled work items (1 to 16 windows of about 64
+                           expected draws each) from which an entry's sampled
+                           suffix is deferred; 0: 64                            */
   int32_t sparse_shift; /* a level whose frontier holds fewer than n C / 2^k
                            entries appends first contributions directly; 0: 5 */
   int32_t bin_shift;    /* (aggregation 2) a level whose estimated pushes reach

@@ -323,4 +323,11 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
   return v;
 }
 
+// the sum of v over the wave, in every lane
+__device__ __forceinline__ uint32_t wave_sum_all(uint32_t v) {
+#pragma unroll
+  for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  return v;
+}
+
 }  // namespace agp

@@ -78,10 +78,12 @@ constexpr int kBuckets = 1024;
 // Rows with many deterministic pushes (a hub with a large residue) would
 // keep one wave busy while the rest of the grid idles; a batched level
 // defers rows of at least big_row (default kBigRow) deterministic pushes to a
-// list that k_det_big then spreads over the whole grid in chunks of kBigChunk
-// pushes.
+// list that k_det_big then spreads over the whole grid, and, when a batch
+// makes more than kBatchDet pushes in all (64 columns of one hub are one
+// batch), its rows of kBatchDetRow and more.
 constexpr uint32_t kBigRow = 4096;
-constexpr int kBigChunk = 4096;  // a lane walks from row to row inside its chunk
+constexpr uint32_t kBatchDet = 2048, kBatchDetRow = 128;
+constexpr unsigned long long kBigChunk = 4096;  // pushes per wave of k_det_big at most
 constexpr int kBigShift = 40;    // list counter: deferred rows << 40 | their pushes (a level's pushes < 2^40)
 
 struct BigRow {
@@ -92,18 +94,19 @@ struct BigRow {
 };
 
 // Likewise an entry whose sampled suffix makes samp_items (64 by default)
-// or more work items (a hub holding a small residue in some column): its
-// items go to a second list that k_samp_big spreads over the whole grid
-// (one item per lane).
+// or more work items (a hub holding a small residue in some column), or
+// kBatchItemRow or more in a batch of more than kBatchItems: its items go to
+// a second list that k_samp_big spreads evenly over the whole grid.
 constexpr long long kBigItems = 64;
+constexpr uint32_t kBatchItems = 512, kBatchItemRow = 8;
 
 struct BigSamp {
   unsigned long long off;  // work items of the entries deferred before this one
   int64_t rp;              // first arc of the row
   double cv;               // c = rho |r| d_u^-b
-  double p0;               // a = 0: the sampling probability of every run
-  uint32_t u, c, J, d;
-  uint32_t neg, items;
+  double p0;               // as in BatchLds
+  uint32_t u, c, J, d;     // c: with the flags of BatchLds
+  uint32_t items, pad;
 };
 
 struct ColParams {
@@ -484,14 +487,41 @@ __device__ __forceinline__ unsigned long long* count_row(const LevelArgs& A) {
 // number of sampled work items), the wave then makes the batch's
 // deterministic pushes with all lanes, one push per lane and step, and puts
 // the sampled work items in a queue that idle lanes draw from.  A sampled
-// work item is up to kWinPerItem consecutive 64-position windows of one
-// entry's suffix; a lane walks their Philox / geometric-skip chains one draw
-// per step and takes the next item from the queue in the step after its last
-// draw, so lanes stay busy across entries and batches.  All loops run in
-// lockstep per wave so that staging can use wave-wide ballots.
+// work item is a run of 1 to 16 consecutive 64-position windows of one
+// entry's suffix, as many as are expected to take about kItemDraws draws (so
+// that no lane is left with a long chain while the others idle); a lane walks
+// their Philox / geometric-skip chains one draw per step and takes the next
+// item from the queue in the step after its last draw, so lanes stay busy
+// across entries and batches.  All loops run in lockstep per wave so that
+// staging can use wave-wide ballots.
+//
+// What bounds it: VALU issue on the first level of a feature matrix (74% of
+// the cycles at 76 Gdraw/s), elsewhere VALU issue and the latency of the
+// dependent loads together (46% busy on dense transition levels), at four
+// waves per SIMD (127 VGPRs, 37 KB of LDS per block).  On levels with hubs
+// the longest lane used to be the bound: items of 16 windows are up to 1024
+// draws for one lane, and the 64 columns of a hub are one batch.  Items of
+// even draws and batch-wise deferral took a level of 64 Katz columns on a
+// 2^20-node R-MAT graph (47M draws) from 6.3 to 1.2 ms, the call from 148 to
+// 41 ms, and 64 ten-step transition columns on 2^22 nodes from 155 to 129 ms.
 constexpr int kBatch = kWave;
-constexpr int kWinPerItem = 16;
+constexpr int kMaxItemShift = 4;  // at most 16 windows per item
 constexpr int kItemMap = 128;
+// A level with at most kFewEntries entries (one batch per resident wave) is
+// bound by the longest chain of a lane, not by issue: its batches hold
+// entries / kResidentWaves entries and its items aim at a quarter of the draws.
+constexpr unsigned long long kResidentWaves = 4096;  // four blocks of four waves on each of 256 CUs
+constexpr unsigned long long kFewEntries = kResidentWaves * kWave;
+
+// log2 of the windows of an entry's work items, given an upper bound p on its
+// sampling probability: a window takes about 1 + 64 p draws, an item about
+// 64 (16 with few entries).
+__device__ __forceinline__ uint32_t item_shift(double p, bool few) {
+  const float f = 1.0f + 64.0f * static_cast<float>(p);
+  uint32_t s = f <= 4.0f ? 4u : f <= 8.0f ? 3u : f <= 16.0f ? 2u : f <= 32.0f ? 1u : 0u;
+  if (few) s = s > 2u ? s - 2u : 0u;
+  return s;
+}
 
 struct BatchLds {
   int64_t rp[kBatch];
@@ -499,18 +529,23 @@ struct BatchLds {
   double p0[kBatch];           // a = 0: sampling probability of every run of the entry;
                                // a > 0: the first arc's factor when the entry has no
                                // deterministic push (its first run starts there), else 0
-  long long doff[kBatch + 1];  // deterministic pushes before each entry (exclusive scan)
-  long long ioff[kBatch + 1];  // sampled work items before each entry
+  long long doff[kBatch];      // deterministic pushes before each entry (exclusive scan)
+  uint32_t ioff[kBatch + 2];   // sampled work items before each entry
   // the entry's column parameters that its work items need (theta, the
-  // random stream's counter word and key), so that taking an item reads LDS
+  // random stream's counter word), so that taking an item reads LDS
   double th[kBatch];
-  uint32_t ctr3[kBatch], key0[kBatch], key1[kBatch];
-  // c: column | kBatchNeg (negative residue) | kBatchAZero (a = 0)
+  uint32_t ctr3[kBatch];
+  // c: column | kBatchNeg (negative residue) | kBatchAZero (a = 0) | log2 of
+  // the windows per work item << kBatchShiftBit
   uint32_t u[kBatch], c[kBatch], d[kBatch], J[kBatch];
   uint8_t item_entry[kItemMap];  // the entry of each of the batch's first kItemMap work items
 };
-constexpr uint32_t kBatchNeg = 1u << 31, kBatchAZero = 1u << 30, kBatchCol = kBatchAZero - 1u;
-// columns of one level launch at most (the column index leaves those two bits free)
+// (the columns of a batched call share one key, held in scalar registers)
+constexpr uint32_t kBatchNeg = 1u << 31, kBatchAZero = 1u << 30;
+constexpr int kBatchShiftBit = 27;  // three bits
+constexpr uint32_t kBatchCol = (1u << kBatchShiftBit) - 1u;
+static_assert(kMaxItemShift < 8, "three bits hold the shift");
+// columns of one level launch at most (the column index leaves those bits free)
 constexpr int32_t kMaxTileColumns = static_cast<int32_t>(kBatchCol);
 
 // floor(a / C) and a mod C for a < 2^22, from rc = 1 / C rounded to binary32:
@@ -542,12 +577,208 @@ __device__ __forceinline__ void wave_sync() {
 }
 
 // largest e in [0, 64) with off[e] <= k (off non-decreasing, off[0] <= k)
-__device__ __forceinline__ int batch_find(const long long* off, long long k) {
+template <typename I>
+__device__ __forceinline__ int batch_find(const I* off, I k) {
   int e = 0;
 #pragma unroll
   for (int step = kBatch / 2; step > 0; step >>= 1)
     if (off[e + step] <= k) e += step;
   return e;
+}
+
+// Exclusive scans of the batch's work items into B.ioff, and the entry of each
+// of the first kItemMap items; returns the items of the whole batch.
+__device__ __forceinline__ uint32_t queue_items(BatchLds& B, uint32_t iwork) {
+  const int lane = lane_id();
+  uint32_t iinc = iwork;
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const uint32_t t = __shfl_up(iinc, off);
+    if (lane >= off) iinc += t;
+  }
+  B.ioff[lane] = iinc - iwork;
+  const int j1 = static_cast<int>(iinc < kItemMap ? iinc : kItemMap);
+  for (int j = static_cast<int>(iinc - iwork < kItemMap ? iinc - iwork : kItemMap); j < j1; ++j)
+    B.item_entry[j] = static_cast<uint8_t>(lane);
+  if (lane == kWave - 1) B.ioff[kBatch] = iinc;
+  return __shfl(iinc, kWave - 1);
+}
+
+// Draws the queued work items of the batches that refill sets up:
+// refill(it_next, it_total) puts the next batch in B and its queue of items
+// [it_next, it_total), or returns false when none is left; emit(pushed, v, c,
+// delta, neg) makes a sampled push of every lane that has one (all lanes
+// together); served(c, candidates, accepted, runs) gets a finished item's
+// counts (server).  w_*: wave-uniform counts (batched calls).
+template <typename T, bool kServe, typename Refill, typename Emit, typename Served>
+__device__ __forceinline__ void sample_loop(const LevelArgs& A, BatchLds& B, Refill&& refill, Emit&& emit_sampled,
+                                            Served&& served, uint32_t& w_cand, uint32_t& w_acc, uint32_t& w_runs) {
+  using P = Prec<T>;
+  using Delta = typename P::Delta;
+  const int lane = lane_id();
+  const unsigned long long lt_mask = (1ull << lane) - 1ull;
+  uint32_t it_next = 0, it_total = 0;  // wave-uniform: queue of the loaded batch
+  bool more = true;                    // wave-uniform: refill may have another batch
+
+  // lane state: the sampled work item in progress
+  bool active = false, need_run = false, neg = false, azero = true;
+  uint32_t u = 0, c = 0, s = 0, rend = 0, run_end = 0, pos = 0, t = 0, ctr3 = 0;
+  uint32_t key0 = kServe ? 0u : __builtin_amdgcn_readfirstlane(A.cp[0].key0);
+  uint32_t key1 = kServe ? 0u : __builtin_amdgcn_readfirstlane(A.cp[0].key1);
+  uint32_t it_cand = 0, it_acc = 0, it_runs = 0;
+  int64_t rpu = 0;
+  double cv = 0.0, dstart = 1.0, th = 0.0;
+  const ColParams* cpp = A.cp;
+  SkipTable tab;
+
+  for (;;) {
+    // (a) a lane whose item has no window left becomes idle
+    if (active && need_run && s >= rend) {
+      active = false;
+      if (kServe) served(c, it_cand, it_acc, it_runs);
+    }
+    // (b) the queue is empty and a lane is idle: set up the next batch
+    if (more && it_next >= it_total && __any(!active)) more = refill(it_next, it_total);
+    // (c) idle lanes take sampled work items from the queue
+    {
+      const unsigned long long idle = __ballot(!active);
+      if (!active) {
+        const uint32_t it = it_next + static_cast<uint32_t>(__popcll(idle & lt_mask));
+        if (it < it_total) {
+          const int e = it < kItemMap ? B.item_entry[it] : batch_find<uint32_t>(B.ioff, it);
+          const uint32_t il = it - B.ioff[e];
+          u = B.u[e];
+          const uint32_t cw = B.c[e];
+          c = cw & kBatchCol;
+          rpu = B.rp[e];
+          cv = B.cv[e];
+          neg = (cw & kBatchNeg) != 0;
+          const uint32_t J = B.J[e], d = B.d[e];
+          cpp = A.cp + c;
+          azero = (cw & kBatchAZero) != 0;
+          th = B.th[e];
+          ctr3 = B.ctr3[e];
+          if (kServe) {
+            key0 = cpp->key0;
+            key1 = cpp->key1;
+          }
+          const uint32_t shift = (cw >> kBatchShiftBit) & 7u;
+          const uint32_t nwin = ((d - 1) >> kSegLog2) - (J >> kSegLog2) + 1;
+          const uint32_t w0 = il << shift;
+          const uint32_t w1 = (w0 + (1u << shift)) < nwin ? w0 + (1u << shift) : nwin;
+          const uint32_t ws = ((J >> kSegLog2) + w0) << kSegLog2;
+          const uint32_t we = ((J >> kSegLog2) + w1) << kSegLog2;
+          s = ws > J ? ws : J;
+          rend = we < d ? we : d;
+          if (azero)
+            tab = make_skip_table(B.p0[e]);
+          else  // the first run's factor when the entry's setup has it (else 0)
+            dstart = il == 0 ? B.p0[e] : 0.0;
+          run_end = 0;  // (the item has no run yet)
+          active = true;
+          need_run = true;
+          it_cand = it_acc = it_runs = 0;
+        }
+      }
+      it_next += static_cast<uint32_t>(__popcll(idle));
+      if (it_next > it_total) it_next = it_total;
+    }
+    if (!__any(active)) {
+      if (!more) break;  // queue empty (no idle lane took an item), no batch left
+      continue;
+    }
+    // (d) a run: the rest of the current window, or (a > 0) of its degree
+    // group unless few candidates are expected over the rest of the window
+    if (!kServe) w_runs += static_cast<uint32_t>(__popcll(__ballot(active && need_run)));
+    if (active && need_run) {
+      if (kServe) ++it_runs;
+      const uint32_t wnext = ((s >> kSegLog2) + 1u) << kSegLog2;
+      const uint32_t wend = wnext < rend ? wnext : rend;
+      const bool first = run_end == 0;
+      run_end = wend;
+      if (!azero) {
+        // the factor of the run's first arc (for an item's first run at the
+        // row start, from the entry's setup); the group end only when the
+        // run stops there
+        if (!(first && dstart > 0.0))
+          dstart = A.arcfac != nullptr ? A.arcfac[rpu + s] : cpp->da[A.nd[rpu + s]];
+        const double num = cv * dstart;
+        const double pr = num / th;
+        if (!(pr * static_cast<double>(wend - s) <= kMergeCandidates)) {
+          const uint32_t ge = A.gend[rpu + s];
+          if (ge < wend) run_end = ge;
+        }
+        tab = make_skip_table(pr);
+      }
+      pos = s;
+      t = 0;
+      need_run = false;
+    }
+    // (e) one draw of the run's chain
+    bool emit = false, cand_hit = false;
+    uint32_t v = 0;
+    Delta delta{};
+    if (active && !need_run) {
+      const U4 o = kServe ? philox4x32_10(t, s, u, ctr3, key0, key1) : philox4x32_10_skey(t, s, u, ctr3, key0, key1);
+      const double V = unit_double(o.x, o.y);
+      const uint32_t cand = pos + static_cast<uint32_t>(geometric_skip(tab, V));
+      if (cand >= run_end) {
+        s = run_end;
+        need_run = true;
+      } else {
+        cand_hit = true;
+        if (kServe) ++it_cand;
+        const int64_t arc = rpu + cand;
+        // the neighbour is loaded beside its factor degree, before the
+        // acceptance test needs it (one round trip instead of two)
+        const uint32_t va = A.col[arc];
+        bool accept = true;  // a = 0: the ratio is 1 and every uniform is below it
+        if (!azero) {
+          const double ratio = (A.arcfac != nullptr ? A.arcfac[arc] : cpp->da[A.nd[arc]]) / dstart;
+          accept = unit_double(o.z, o.w) < ratio;
+        }
+        if (accept) {
+          if (kServe) ++it_acc;
+          v = va;
+          emit = true;
+          delta = P::theta_units(*cpp, neg);
+        }
+        pos = cand + 1;
+        ++t;
+      }
+    }
+    if (!kServe) {
+      w_cand += static_cast<uint32_t>(__popcll(__ballot(cand_hit)));
+      w_acc += static_cast<uint32_t>(__popcll(__ballot(emit)));
+    }
+    emit_sampled(emit, v, c, delta, neg);
+  }
+}
+
+// Reserves list slots for the lanes that defer (wave-uniform call): the list
+// counter takes one atomic for all of them, which returns the slot and the
+// work before it; false where the list is full (or the lane does not defer).
+// The counter is read first, so that it never wraps.
+__device__ __forceinline__ bool defer_slots(unsigned long long* ctr, unsigned long long cap, bool want,
+                                            unsigned long long work, unsigned long long* slot,
+                                            unsigned long long* off) {
+  const unsigned long long mask = __ballot(want);
+  if (mask == 0ull) return false;
+  if ((__hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> kBigShift) >= cap) return false;
+  const int lane = lane_id();
+  unsigned long long inc = want ? work : 0ull;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const unsigned long long t = __shfl_up(inc, o);
+    if (lane >= o) inc += t;
+  }
+  const unsigned long long total = __shfl(inc, kWave - 1);
+  unsigned long long old = 0;
+  if (lane == 0) old = atomic_add_ret(ctr, (static_cast<unsigned long long>(__popcll(mask)) << kBigShift) | total);
+  old = __shfl(old, 0);
+  *slot = (old >> kBigShift) + static_cast<unsigned long long>(__popcll(mask & ((1ull << lane) - 1ull)));
+  *off = (old & ((1ull << kBigShift) - 1ull)) + inc - work;
+  return want && *slot < cap;
 }
 
 // kFirst: the residues are the signal x (level 0 of a batched call).
@@ -588,7 +819,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
   }
   const int lane = lane_id();
   const int wave = threadIdx.x / kWave;
-  const unsigned long long lt_mask = (1ull << lane) - 1ull;
   BatchLds& B = s_batch[wave];
   uint64_t* stage = s_stage[wave];
   int staged = 0;  // wave-uniform
@@ -644,14 +874,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
   };
 
   // up to 64 entries per batch; fewer when the level has fewer entries than
-  // 64 per wave, so that small frontiers still spread over the whole grid
+  // 64 per resident wave, so that small frontiers spread over the whole chip
+  // (but no wider: spread over four generations of waves, a level of 10^5
+  // entries paid four times for the setup's chain of loads with a third of
+  // the lanes busy; nine queries on a 30011-node graph: 4.07 -> 1.95 ms)
   const unsigned long long nwaves = static_cast<unsigned long long>(gridDim.x) * kWaves;
-  const unsigned long long eb_raw = count / nwaves;
-  const unsigned long long eb = eb_raw < 1ull ? 1ull : (eb_raw > (unsigned long long)kBatch ? kBatch : eb_raw);
+  const unsigned long long want = (count + kResidentWaves - 1) / kResidentWaves;
+  const unsigned long long eb = want < 1ull ? 1ull : (want > (unsigned long long)kBatch ? kBatch : want);
+  const bool few = count <= kFewEntries;
   const unsigned long long nbatch = (count + eb - 1) / eb;
-  const unsigned long long bstride = static_cast<unsigned long long>(gridDim.x) * kWaves;
   unsigned long long bnext = static_cast<unsigned long long>(blockIdx.x) * kWaves + wave;
-  long long it_next = 0, it_total = 0;  // wave-uniform: queue of the loaded batch
   // the frontier items of this wave's next batch, loaded one batch ahead so
   // that a batch's setup starts from its items
   auto load_items = [&](unsigned long long b) -> uint64_t {
@@ -671,381 +903,245 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
   };
   uint64_t next_items = load_items(bnext);
 
-  // lane state: the sampled work item in progress
-  bool active = false, need_run = false, neg = false, azero = true;
-  uint32_t u = 0, c = 0, s = 0, rend = 0, run_end = 0, pos = 0, t = 0, ctr3 = 0, key0 = 0, key1 = 0;
-  uint32_t it_cand = 0, it_acc = 0, it_runs = 0;
-  int64_t rpu = 0;
-  double cv = 0.0, dstart = 1.0, th = 0.0;
-  const ColParams* cpp = A.cp;
-  SkipTable tab;
-
-  for (;;) {
-    // (a) a lane whose item has no window left becomes idle
-    if (active && need_run && s >= rend) {
-      active = false;
-      if (kServe) {
-        if (it_cand) {
-          serve_count(A, s_scnt, c, 3, static_cast<unsigned long long>(it_cand));
-          if (it_acc) serve_count(A, s_scnt, c, 4, static_cast<unsigned long long>(it_acc));
+  auto refill = [&](uint32_t& it_next, uint32_t& it_total) -> bool {
+    if (bnext >= nbatch) return false;
+    wave_sync();  // every lane has read the previous batch
+    const unsigned long long e0 = bnext * eb;
+    bnext += nwaves;
+    const int ne = static_cast<int>((count - e0) < eb ? (count - e0) : eb);
+    const uint64_t batch_item = next_items;
+    next_items = load_items(bnext);
+    long long dwork = 0;
+    uint32_t iwork = 0;
+    uint32_t eu = 0, ec = 0, ed = 0, eJ = 0, ecw = 0;
+    int64_t erp = 0;
+    double ecv = 0.0, ep0 = 0.0;
+    bool eneg = false;
+    bool front_live = false;
+    if (lane < ne) {
+      const uint64_t item = batch_item;
+      eu = static_cast<uint32_t>(item >> 32);
+      ec = static_cast<uint32_t>(item);
+      size_t cell = static_cast<size_t>(eu) * A.su + static_cast<size_t>(ec) * A.sc;
+      if constexpr (kServe) {  // (table position, query): the node is the key (or the offset); free it
+        cell = eu;
+        if (A.tab_mask[ec] == kDirectPlain) {
+          eu = static_cast<uint32_t>(cell) - A.tab_cur[ec];
+        } else {
+          eu = A.keys_cur[cell] - 1u;
+          A.keys_cur[cell] = 0u;
         }
-        if (it_runs) serve_count(A, s_scnt, c, 5, static_cast<unsigned long long>(it_runs));
       }
-    }
-    // (b) the queue is empty and a lane is idle: set up the next batch
-    if (it_next >= it_total && bnext < nbatch && __any(!active)) {
-      wave_sync();  // every lane has read the previous batch
-      const unsigned long long e0 = bnext * eb;
-      bnext += bstride;
-      const int ne = static_cast<int>((count - e0) < eb ? (count - e0) : eb);
-      const uint64_t batch_item = next_items;
-      next_items = load_items(bnext);
-      long long dwork = 0, iwork = 0;
-      uint32_t eu = 0, ec = 0, ed = 0, eJ = 0, ecw = 0;
-      int64_t erp = 0;
-      double ecv = 0.0, ep0 = 0.0;
-      bool eneg = false;
-      bool front_live = false;
-      if (lane < ne) {
-        const uint64_t item = batch_item;
-        eu = static_cast<uint32_t>(item >> 32);
-        ec = static_cast<uint32_t>(item);
-        size_t cell = static_cast<size_t>(eu) * A.su + static_cast<size_t>(ec) * A.sc;
-        if constexpr (kServe) {  // (table position, query): the node is the key (or the offset); free it
-          cell = eu;
-          if (A.tab_mask[ec] == kDirectPlain) {
-            eu = static_cast<uint32_t>(cell) - A.tab_cur[ec];
-          } else {
-            eu = A.keys_cur[cell] - 1u;
-            A.keys_cur[cell] = 0u;
-          }
-        }
-        // The loads that need only the entry go out together (a batched
-        // entry always names a node of the graph and a live column: its row
-        // bounds and factor degree beside its residue and column parameters),
-        // then the ones that need their results (the reserve's old value, the
-        // first neighbour's factor degree, d_u^-b).
-        uint32_t deg_u = 0;
-        int32_t fdeg_u = 0;
-        int64_t rp_u = 0;
-        const bool pre = !kServe && A.nodefac != nullptr;  // the node's two factors in one load
-        const bool pre_arc = !kServe && A.arcfac != nullptr;  // each arc's neighbour factor in one load
-        double2 nf = make_double2(0.0, 0.0);
-        if (!kServe) {
-          deg_u = static_cast<uint32_t>(A.deg[eu]);
-          if (pre)
-            nf = reinterpret_cast<const double2*>(A.nodefac)[eu];
-          else
-            fdeg_u = A.fdeg[eu];
-          rp_u = A.rp[eu];
-        }
-        const ColParams& cp = A.cp[ec];
-        T r;
-        if (kFirst)
-          r = x[static_cast<size_t>(eu) * static_cast<size_t>(A.xld) + ec];
+      // The loads that need only the entry go out together (a batched
+      // entry always names a node of the graph and a live column: its row
+      // bounds and factor degree beside its residue and column parameters),
+      // then the ones that need their results (the reserve's old value, the
+      // first neighbour's factor degree, d_u^-b).
+      uint32_t deg_u = 0;
+      int32_t fdeg_u = 0;
+      int64_t rp_u = 0;
+      const bool pre = !kServe && A.nodefac != nullptr;  // the node's two factors in one load
+      const bool pre_arc = !kServe && A.arcfac != nullptr;  // each arc's neighbour factor in one load
+      double2 nf = make_double2(0.0, 0.0);
+      if (!kServe) {
+        deg_u = static_cast<uint32_t>(A.deg[eu]);
+        if (pre)
+          nf = reinterpret_cast<const double2*>(A.nodefac)[eu];
         else
-          r = P::take(acc_cur, cell, cp);
-        // (a served query's table also holds nodes whose sum cancelled to zero,
-        // and level 0 over every cell holds the zero cells of x: they are not
-        // in the frontier)
-        const bool live = !(cp.flags & kDrop) && !((kServe || (kFirst && A.fin == nullptr)) && r == T(0));
-        if (kServe && live) {
-          deg_u = static_cast<uint32_t>(A.deg[eu]);
           fdeg_u = A.fdeg[eu];
-          rp_u = A.rp[eu];
+        rp_u = A.rp[eu];
+      }
+      const ColParams& cp = A.cp[ec];
+      T r;
+      if (kFirst)
+        r = x[static_cast<size_t>(eu) * static_cast<size_t>(A.xld) + ec];
+      else
+        r = P::take(acc_cur, cell, cp);
+      // (a served query's table also holds nodes whose sum cancelled to zero,
+      // and level 0 over every cell holds the zero cells of x: they are not
+      // in the frontier)
+      const bool live = !(cp.flags & kDrop) && !((kServe || (kFirst && A.fin == nullptr)) && r == T(0));
+      if (kServe && live) {
+        deg_u = static_cast<uint32_t>(A.deg[eu]);
+        fdeg_u = A.fdeg[eu];
+        rp_u = A.rp[eu];
+      }
+      T* const o = static_cast<T*>(cp.out) + static_cast<size_t>(eu) * static_cast<size_t>(cp.out_stride);
+      const T o_old = (live && cp.kappa != 0.0) ? *o : T(0);
+      // (a = 0: every factor d^-a is 1, no degree is read)
+      const uint32_t nd_first = (!pre && live && deg_u > 0 && !(cp.flags & kAZero)) ? A.nd[rp_u] : 0u;
+      const double db_u = live ? (pre ? nf.x : cp.db[fdeg_u]) : 0.0;
+      eneg = r < T(0);
+      ecw = ec | (eneg ? kBatchNeg : 0u) | ((cp.flags & kAZero) ? kBatchAZero : 0u);
+      // (the previous batch is no longer read: these slots are free; the
+      // entries past ne get no work items)
+      B.th[lane] = cp.theta;
+      B.ctr3[lane] = (cp.qid << 8) | static_cast<uint32_t>(cp.level);
+          if (live) {
+        if (kServe) {
+          serve_count(A, s_scnt, ec, 0, 1ull);
+        } else {
+          front_live = true;
+          n_hash += splitmix64(eu);
         }
-        T* const o = static_cast<T*>(cp.out) + static_cast<size_t>(eu) * static_cast<size_t>(cp.out_stride);
-        const T o_old = (live && cp.kappa != 0.0) ? *o : T(0);
-        // (a = 0: every factor d^-a is 1, no degree is read)
-        const uint32_t nd_first = (!pre && live && deg_u > 0 && !(cp.flags & kAZero)) ? A.nd[rp_u] : 0u;
-        const double db_u = live ? (pre ? nf.x : cp.db[fdeg_u]) : 0.0;
-        eneg = r < T(0);
-        ecw = ec | (eneg ? kBatchNeg : 0u) | ((cp.flags & kAZero) ? kBatchAZero : 0u);
-        // (the previous batch is no longer read: these slots are free; the
-        // entries past ne get no work items)
-        B.th[lane] = cp.theta;
-        B.ctr3[lane] = (cp.qid << 8) | static_cast<uint32_t>(cp.level);
-        B.key0[lane] = cp.key0;
-        B.key1[lane] = cp.key1;
-        if (live) {
-          if (kServe) {
-            serve_count(A, s_scnt, ec, 0, 1ull);
-          } else {
-            front_live = true;
-            n_hash += splitmix64(eu);
-          }
-          // reserve: pi(u) += (S w_i / Y_i) r(u), rounded to the working precision
-          if (cp.kappa != 0.0) {
-            const T q = to_w(cp.kappa * static_cast<double>(r), T());
-            *o = o_old + q;
-          }
-          if (!(cp.flags & kLastLevel) && cp.rho != 0.0) {
-            ed = deg_u;
-            if (ed > 0) {
-              const double absr = fabs(static_cast<double>(r));
-              const double t0 = cp.rho * absr;
-              ecv = t0 * db_u;
-              const double eth = cp.theta;
-              erp = rp_u;
-              double inc0 = ecv;
-              if (cp.flags & kAZero) {
-                eJ = (ecv >= eth) ? ed : 0u;
-                const double num = ecv * 1.0;  // every neighbour's factor d^-0 is 1
-                ep0 = num / eth;
-              } else {  // increments fall along the degree-sorted row: binary search
-                const double da0 = pre ? nf.y : cp.da[nd_first];
-                inc0 = ecv * da0;
-                uint32_t lo = 0, hi = ed;
-                if (!(inc0 >= eth))
-                  hi = 0;  // no deterministic push
-                else if (ecv * (pre_arc ? A.arcfac[erp + ed - 1] : cp.da[A.nd[erp + ed - 1]]) >= eth)
-                  lo = ed;  // every push is deterministic
-                while (lo < hi) {
-                  const uint32_t mid = (lo + hi) >> 1;
-                  const double inc = ecv * (pre_arc ? A.arcfac[erp + mid] : cp.da[A.nd[erp + mid]]);
-                  if (inc >= eth)
-                    lo = mid + 1;
-                  else
-                    hi = mid;
-                }
-                eJ = lo;
-                // without deterministic pushes the first sampled run starts at
-                // the row's first arc: its factor goes with the entry
-                ep0 = eJ == 0 ? da0 : 0.0;
-              }
-              const long long windows =
-                  (eJ < ed) ? static_cast<long long>(((ed - 1) >> kSegLog2) - (eJ >> kSegLog2) + 1) : 0;
-              dwork = eJ;
-              iwork = (windows + kWinPerItem - 1) / kWinPerItem;
-              // a long deterministic prefix goes to the deferred list (the
-              // counter is read first so that it never wraps)
-              if (!kServe && A.big_ctr != nullptr && eJ >= A.big_row &&
-                  (__hip_atomic_load(A.big_ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> kBigShift) <
-                      A.big_cap) {
-                const unsigned long long old =
-                    atomic_add_ret(A.big_ctr, (1ull << kBigShift) | static_cast<unsigned long long>(eJ));
-                const unsigned long long slot = old >> kBigShift;
-                if (slot < A.big_cap) {
-                  BigRow br;
-                  br.off = old & ((1ull << kBigShift) - 1ull);
-                  br.rp = erp;
-                  br.cv = ecv;
-                  br.c = ec;
-                  br.J = eJ;
-                  br.neg = eneg ? 1u : 0u;
-                  br.pad = 0;
-                  A.big[slot] = br;
-                  dwork = 0;
-                }
-              }
-              if (!kServe && A.samp_ctr != nullptr && iwork >= A.samp_items &&
-                  (__hip_atomic_load(A.samp_ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> kBigShift) <
-                      A.big_cap) {
-                const unsigned long long old =
-                    atomic_add_ret(A.samp_ctr, (1ull << kBigShift) | static_cast<unsigned long long>(iwork));
-                const unsigned long long slot = old >> kBigShift;
-                if (slot < A.big_cap) {
-                  BigSamp bs;
-                  bs.off = old & ((1ull << kBigShift) - 1ull);
-                  bs.rp = erp;
-                  bs.cv = ecv;
-                  bs.p0 = ep0;
-                  bs.u = eu;
-                  bs.c = ec;
-                  bs.J = eJ;
-                  bs.d = ed;
-                  bs.neg = eneg ? 1u : 0u;
-                  bs.items = static_cast<uint32_t>(iwork);
-                  A.samp[slot] = bs;
-                  iwork = 0;
-                }
-              }
-              // bound on the magnitude this entry can add (every contribution
-              // is at most max(inc_0, theta)), for the overflow check
-              const T big = to_w(inc0 > eth ? inc0 : eth, T());
-              const double m = static_cast<double>(ed) * P::mag_units(big, cp);
-              if (kServe) {
-                serve_count(A, s_scnt, ec, 2, static_cast<unsigned long long>(eJ));
-                if (ec < kServeLdsSlots)
-                  atomicAdd(&s_smass[ec], m);
+        // reserve: pi(u) += (S w_i / Y_i) r(u), rounded to the working precision
+        if (cp.kappa != 0.0) {
+          const T q = to_w(cp.kappa * static_cast<double>(r), T());
+          *o = o_old + q;
+        }
+        if (!(cp.flags & kLastLevel) && cp.rho != 0.0) {
+          ed = deg_u;
+          if (ed > 0) {
+            const double absr = fabs(static_cast<double>(r));
+            const double t0 = cp.rho * absr;
+            ecv = t0 * db_u;
+            const double eth = cp.theta;
+            erp = rp_u;
+            double inc0 = ecv;
+            if (cp.flags & kAZero) {
+              eJ = (ecv >= eth) ? ed : 0u;
+              const double num = ecv * 1.0;  // every neighbour's factor d^-0 is 1
+              ep0 = num / eth;
+            } else {  // increments fall along the degree-sorted row: binary search
+              const double da0 = pre ? nf.y : cp.da[nd_first];
+              inc0 = ecv * da0;
+              uint32_t lo = 0, hi = ed;
+              if (!(inc0 >= eth))
+                hi = 0;  // no deterministic push
+              else if (ecv * (pre_arc ? A.arcfac[erp + ed - 1] : cp.da[A.nd[erp + ed - 1]]) >= eth)
+                lo = ed;  // every push is deterministic
+              while (lo < hi) {
+                const uint32_t mid = (lo + hi) >> 1;
+                const double inc = ecv * (pre_arc ? A.arcfac[erp + mid] : cp.da[A.nd[erp + mid]]);
+                if (inc >= eth)
+                  lo = mid + 1;
                 else
-                  atomicAdd(A.mass + ec, m);
-              } else {
-                n_det += eJ;
-                mass += m;
+                  hi = mid;
               }
+              eJ = lo;
+              // without deterministic pushes the first sampled run starts at
+              // the row's first arc: its factor goes with the entry
+              ep0 = eJ == 0 ? da0 : 0.0;
+            }
+            const long long windows =
+                (eJ < ed) ? static_cast<long long>(((ed - 1) >> kSegLog2) - (eJ >> kSegLog2) + 1) : 0;
+            dwork = eJ;
+            // (past a deterministic prefix the probability starts below 1)
+            const uint32_t shift = item_shift(eJ == 0 ? inc0 / eth : 1.0, few);
+            ecw |= shift << kBatchShiftBit;
+            iwork = static_cast<uint32_t>((windows + (1ll << shift) - 1) >> shift);
+            // bound on the magnitude this entry can add (every contribution
+            // is at most max(inc_0, theta)), for the overflow check
+            const T big = to_w(inc0 > eth ? inc0 : eth, T());
+            const double m = static_cast<double>(ed) * P::mag_units(big, cp);
+            if (kServe) {
+              serve_count(A, s_scnt, ec, 2, static_cast<unsigned long long>(eJ));
+              if (ec < kServeLdsSlots)
+                atomicAdd(&s_smass[ec], m);
+              else
+                atomicAdd(A.mass + ec, m);
+            } else {
+              n_det += eJ;
+              mass += m;
             }
           }
         }
       }
-      if (!kServe) w_front += static_cast<uint32_t>(__popcll(__ballot(front_live)));
-      long long dinc = dwork, iinc = iwork;
+    }
+    if (!kServe) w_front += static_cast<uint32_t>(__popcll(__ballot(front_live)));
+    // long deterministic prefixes and entries with many work items leave for
+    // the deferred lists
+    if (!kServe && A.big_ctr != nullptr && __any(eJ >= kBatchDetRow || eJ >= A.big_row)) {
+      const bool full = wave_sum_all(eJ < (1u << 20) ? eJ : (1u << 20)) > kBatchDet;
+      unsigned long long slot = 0, off = 0;
+      if (defer_slots(A.big_ctr, A.big_cap, eJ >= A.big_row || (full && eJ >= kBatchDetRow), eJ, &slot, &off)) {
+        BigRow br;
+        br.off = off;
+        br.rp = erp;
+        br.cv = ecv;
+        br.c = ec;
+        br.J = eJ;
+        br.neg = eneg ? 1u : 0u;
+        br.pad = 0;
+        A.big[slot] = br;
+        dwork = 0;
+      }
+    }
+    const uint32_t big_items = static_cast<uint32_t>(A.samp_items);
+    if (!kServe && A.samp_ctr != nullptr && __any(iwork >= kBatchItemRow || iwork >= big_items)) {
+      const bool full = wave_sum_all(iwork < (1u << 20) ? iwork : (1u << 20)) > kBatchItems;
+      unsigned long long slot = 0, off = 0;
+      if (defer_slots(A.samp_ctr, A.big_cap, iwork >= big_items || (full && iwork >= kBatchItemRow), iwork, &slot,
+                      &off)) {
+        BigSamp bs;
+        bs.off = off;
+        bs.rp = erp;
+        bs.cv = ecv;
+        bs.p0 = ep0;
+        bs.u = eu;
+        bs.c = ecw;
+        bs.J = eJ;
+        bs.d = ed;
+        bs.items = iwork;
+        bs.pad = 0;
+        A.samp[slot] = bs;
+        iwork = 0;
+      }
+    }
+    long long dtot = 0;  // deterministic pushes of the batch
+    if (__any(dwork != 0)) {
+      long long dinc = dwork;
 #pragma unroll
       for (int off = 1; off < kWave; off <<= 1) {
         const long long td = __shfl_up(dinc, off);
-        const long long ti = __shfl_up(iinc, off);
-        if (lane >= off) {
-          dinc += td;
-          iinc += ti;
-        }
+        if (lane >= off) dinc += td;
       }
-      B.rp[lane] = erp;
-      B.cv[lane] = ecv;
-      B.p0[lane] = ep0;
       B.doff[lane] = dinc - dwork;
-      B.ioff[lane] = iinc - iwork;
-      {
-        const int j1 = static_cast<int>(iinc < kItemMap ? iinc : kItemMap);
-        for (int j = static_cast<int>(iinc - iwork < kItemMap ? iinc - iwork : kItemMap); j < j1; ++j)
-          B.item_entry[j] = static_cast<uint8_t>(lane);
-      }
-      if (lane == kWave - 1) {
-        B.doff[kBatch] = dinc;
-        B.ioff[kBatch] = iinc;
-      }
-      B.u[lane] = eu;
-      B.c[lane] = ecw;
-      B.d[lane] = ed;
-      B.J[lane] = eJ;
-      wave_sync();
-      // deterministic pushes of the batch: the increment reaches theta
-      const long long dtot = B.doff[kBatch];
-      for (long long kb = 0; kb < dtot; kb += kWave) {
-        const long long k = kb + lane;
-        bool emit = false;
-        uint32_t v = 0, vc = 0;
-        Delta delta{};
-        if (k < dtot) {
-          const int e = batch_find(B.doff, k);
-          const int64_t arc = B.rp[e] + (k - B.doff[e]);
-          const uint32_t cw = B.c[e];
-          vc = cw & kBatchCol;
-          const ColParams* cpd = A.cp + vc;
-          v = A.col[arc];
-          double inc = B.cv[e];
-          if (!(cpd->flags & kAZero)) inc = inc * (A.arcfac != nullptr ? A.arcfac[arc] : cpd->da[A.nd[arc]]);
-          T val = to_w(inc, T());
-          if (cw & kBatchNeg) val = -val;
-          emit = P::to_units(val, *cpd, &delta);
-          if (!emit) atomicOr(A.err + (kServe ? vc : 0u), 1);
-          if (binned && A.det_bins != nullptr) mark_det_bin<kG>(A, A.det_bins, v, vc);
-        }
-        emit_atomic(emit, v, vc, delta);
-      }
-      it_next = 0;
-      it_total = B.ioff[kBatch];
+      dtot = __shfl(dinc, kWave - 1);
     }
-    // (c) idle lanes take sampled work items from the queue
-    {
-      const unsigned long long idle = __ballot(!active);
-      if (!active) {
-        const long long it = it_next + __popcll(idle & lt_mask);
-        if (it < it_total) {
-          const int e = it < kItemMap ? B.item_entry[it] : batch_find(B.ioff, it);
-          const uint32_t il = static_cast<uint32_t>(it - B.ioff[e]);
-          u = B.u[e];
-          const uint32_t cw = B.c[e];
-          c = cw & kBatchCol;
-          rpu = B.rp[e];
-          cv = B.cv[e];
-          neg = (cw & kBatchNeg) != 0;
-          const uint32_t J = B.J[e], d = B.d[e];
-          cpp = A.cp + c;
-          azero = (cw & kBatchAZero) != 0;
-          th = B.th[e];
-          ctr3 = B.ctr3[e];
-          key0 = B.key0[e];
-          key1 = B.key1[e];
-          const uint32_t nwin = ((d - 1) >> kSegLog2) - (J >> kSegLog2) + 1;
-          const uint32_t w0 = il * kWinPerItem;
-          const uint32_t w1 = (w0 + kWinPerItem) < nwin ? w0 + kWinPerItem : nwin;
-          const uint32_t ws = ((J >> kSegLog2) + w0) << kSegLog2;
-          const uint32_t we = ((J >> kSegLog2) + w1) << kSegLog2;
-          s = ws > J ? ws : J;
-          rend = we < d ? we : d;
-          if (azero)
-            tab = make_skip_table(B.p0[e]);
-          else  // the first run's factor when the entry's setup has it (else 0)
-            dstart = il == 0 ? B.p0[e] : 0.0;
-          run_end = 0;  // (the item has no run yet)
-          active = true;
-          need_run = true;
-          it_cand = it_acc = it_runs = 0;
-        }
+    B.rp[lane] = erp;
+    B.cv[lane] = ecv;
+    B.p0[lane] = ep0;
+    B.u[lane] = eu;
+    B.c[lane] = ecw;
+    B.d[lane] = ed;
+    B.J[lane] = eJ;
+    it_next = 0;
+    it_total = queue_items(B, iwork);
+    wave_sync();
+    // deterministic pushes of the batch: the increment reaches theta
+    for (long long kb = 0; kb < dtot; kb += kWave) {
+      const long long k = kb + lane;
+      bool emit = false;
+      uint32_t v = 0, vc = 0;
+      Delta delta{};
+      if (k < dtot) {
+        const int e = batch_find<long long>(B.doff, k);
+        const int64_t arc = B.rp[e] + (k - B.doff[e]);
+        const uint32_t cw = B.c[e];
+        vc = cw & kBatchCol;
+        const ColParams* cpd = A.cp + vc;
+        v = A.col[arc];
+        double inc = B.cv[e];
+        if (!(cpd->flags & kAZero)) inc = inc * (A.arcfac != nullptr ? A.arcfac[arc] : cpd->da[A.nd[arc]]);
+        T val = to_w(inc, T());
+        if (cw & kBatchNeg) val = -val;
+        emit = P::to_units(val, *cpd, &delta);
+        if (!emit) atomicOr(A.err + (kServe ? vc : 0u), 1);
+        if (binned && A.det_bins != nullptr) mark_det_bin<kG>(A, A.det_bins, v, vc);
       }
-      it_next += __popcll(idle);
-      if (it_next > it_total) it_next = it_total;
+      emit_atomic(emit, v, vc, delta);
     }
-    if (!__any(active)) {
-      if (bnext >= nbatch) break;  // queue empty (no idle lane took an item), no batch left
-      continue;
+    return true;
+  };
+  auto served = [&](uint32_t c, uint32_t cand, uint32_t acc, uint32_t runs) {
+    if (cand) {
+      serve_count(A, s_scnt, c, 3, static_cast<unsigned long long>(cand));
+      if (acc) serve_count(A, s_scnt, c, 4, static_cast<unsigned long long>(acc));
     }
-    // (d) a run: the rest of the current window, or (a > 0) of its degree
-    // group unless few candidates are expected over the rest of the window
-    if (!kServe) w_runs += static_cast<uint32_t>(__popcll(__ballot(active && need_run)));
-    if (active && need_run) {
-      if (kServe) ++it_runs;
-      const uint32_t wnext = ((s >> kSegLog2) + 1u) << kSegLog2;
-      const uint32_t wend = wnext < rend ? wnext : rend;
-      const bool first = run_end == 0;
-      run_end = wend;
-      if (!azero) {
-        // the factor of the run's first arc (for an item's first run at the
-        // row start, from the entry's setup); the group end only when the
-        // run stops there
-        if (!(first && dstart > 0.0))
-          dstart = A.arcfac != nullptr ? A.arcfac[rpu + s] : cpp->da[A.nd[rpu + s]];
-        const double num = cv * dstart;
-        const double pr = num / th;
-        if (!(pr * static_cast<double>(wend - s) <= kMergeCandidates)) {
-          const uint32_t ge = A.gend[rpu + s];
-          if (ge < wend) run_end = ge;
-        }
-        tab = make_skip_table(pr);
-      }
-      pos = s;
-      t = 0;
-      need_run = false;
-    }
-    // (e) one draw of the run's chain
-    bool emit = false, cand_hit = false;
-    uint32_t v = 0;
-    Delta delta{};
-    if (active && !need_run) {
-      const U4 o = philox4x32_10(t, s, u, ctr3, key0, key1);
-      const double V = unit_double(o.x, o.y);
-      const uint32_t cand = pos + static_cast<uint32_t>(geometric_skip(tab, V));
-      if (cand >= run_end) {
-        s = run_end;
-        need_run = true;
-      } else {
-        cand_hit = true;
-        if (kServe) ++it_cand;
-        const int64_t arc = rpu + cand;
-        // the neighbour is loaded beside its factor degree, before the
-        // acceptance test needs it (one round trip instead of two)
-        const uint32_t va = A.col[arc];
-        bool accept = true;  // a = 0: the ratio is 1 and every uniform is below it
-        if (!azero) {
-          const double ratio = (A.arcfac != nullptr ? A.arcfac[arc] : cpp->da[A.nd[arc]]) / dstart;
-          accept = unit_double(o.z, o.w) < ratio;
-        }
-        if (accept) {
-          if (kServe) ++it_acc;
-          v = va;
-          emit = true;
-          delta = P::theta_units(*cpp, neg);
-        }
-        pos = cand + 1;
-        ++t;
-      }
-    }
-    if (!kServe) {
-      w_cand += static_cast<uint32_t>(__popcll(__ballot(cand_hit)));
-      w_acc += static_cast<uint32_t>(__popcll(__ballot(emit)));
-    }
-    emit_sampled(emit, v, c, delta, neg);
-  }
+    if (runs) serve_count(A, s_scnt, c, 5, static_cast<unsigned long long>(runs));
+  };
+  sample_loop<T, kServe>(A, B, refill, emit_sampled, served, w_cand, w_acc, w_runs);
   if (sparse) stage_flush(stage, staged, A.fout, A.cnt_out);
   if (binned) finish_records<kG>(A, s_hist, reinterpret_cast<uint32_t*>(stage), staged, acc_next);
   if (kServe) {  // flush the block's per-column sums
@@ -1094,7 +1190,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
 
 // ------------------------------------------------- deferred rows
 // The deterministic pushes of the rows a level deferred, after its k_level
-// launch: a wave takes kBigChunk consecutive pushes of the concatenated rows
+// launch: a wave takes a chunk of consecutive pushes of the concatenated rows
 // (lane l pushes l, l + 64, ...), finds its row once by binary search over
 // the rows' offsets and moves to the next row when it crosses its end.  The
 // pushes are computed and accumulated as in k_level (first contributions of
@@ -1117,10 +1213,14 @@ __global__ __launch_bounds__(kThreads) void k_det_big(LevelArgs A, typename Prec
   const int wave = threadIdx.x / kWave;
   uint64_t* stage = s_stage[wave];
   int staged = 0;  // wave-uniform
-  const unsigned long long nchunks = (total + kBigChunk - 1) / kBigChunk;
-  for (unsigned long long ch = static_cast<unsigned long long>(blockIdx.x) * kWaves + wave; ch < nchunks;
-       ch += static_cast<unsigned long long>(gridDim.x) * kWaves) {
-    unsigned long long k = ch * kBigChunk + lane;
+  // a chunk of pushes per wave: as many as give every wave one, in whole
+  // steps of 64, at most kBigChunk
+  const unsigned long long nw = static_cast<unsigned long long>(gridDim.x) * kWaves;
+  unsigned long long chunk = ((total + nw - 1) / nw + kWave - 1) & ~static_cast<unsigned long long>(kWave - 1);
+  if (chunk > kBigChunk) chunk = kBigChunk;
+  const unsigned long long nchunks = (total + chunk - 1) / chunk;
+  for (unsigned long long ch = static_cast<unsigned long long>(blockIdx.x) * kWaves + wave; ch < nchunks; ch += nw) {
+    unsigned long long k = ch * chunk + lane;
     unsigned long long e = 0, hi = nb;  // last row with off <= k
     while (hi - e > 1) {
       const unsigned long long mid = (e + hi) >> 1;
@@ -1130,7 +1230,7 @@ __global__ __launch_bounds__(kThreads) void k_det_big(LevelArgs A, typename Prec
         hi = mid;
     }
     unsigned long long off = R[e].off, next = e + 1 < nb ? R[e + 1].off : total;
-    for (int j = 0; j < kBigChunk / kWave; ++j, k += kWave) {
+    for (unsigned long long j = 0; j < chunk; j += kWave, k += kWave) {
       bool emit = false;
       uint32_t v = 0, vc = 0;
       Delta delta{};
@@ -1168,18 +1268,21 @@ __global__ __launch_bounds__(kThreads) void k_det_big(LevelArgs A, typename Prec
 }
 
 // The sampled work items of the entries a level deferred, after its k_level
-// launch: lane g takes items g, g + G, ... of the concatenated entries (G
-// lanes in the grid), finds an item's entry by binary search over the
-// entries' item offsets and walks its windows exactly as k_level does (the
-// same runs, draws and acceptance tests, so the same pushes); the pushes
-// are emitted as in k_level's mode for the level (records, first-touch
-// appends or plain atomics), and the level's candidate and acceptance
-// counters get this kernel's counts.
+// launch: every wave takes the same number of consecutive items (an item is
+// about the same number of draws whatever its entry), finds its first entry
+// by binary search over the entries' item offsets, loads up to 64 entries at
+// a time into its batch and draws their items exactly as k_level does (the
+// same runs, draws and acceptance tests, so the same pushes); the pushes are
+// emitted as in k_level's mode for the level (records, first-touch appends or
+// plain atomics), and the level's candidate and acceptance counters get this
+// kernel's counts.
 template <typename T, int kG = 1>
-__global__ __launch_bounds__(kThreads) void k_samp_big(LevelArgs A, typename Prec<T>::Cell* __restrict__ acc_next) {
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_samp_big(
+    LevelArgs A, typename Prec<T>::Cell* __restrict__ acc_next) {
   using P = Prec<T>;
   using Delta = typename P::Delta;
   constexpr int kWaves = kThreads / kWave;
+  __shared__ BatchLds s_batch[kWaves];
   __shared__ uint64_t s_stage[kWaves][kStage];
   __shared__ unsigned int s_hist[kBuckets];
   const unsigned long long ctr = *A.samp_ctr;
@@ -1195,128 +1298,79 @@ __global__ __launch_bounds__(kThreads) void k_samp_big(LevelArgs A, typename Pre
     for (int i = threadIdx.x; i < kBuckets; i += blockDim.x) s_hist[i] = 0;
     __syncthreads();
   }
+  const int lane = lane_id();
   const int wave = threadIdx.x / kWave;
+  BatchLds& B = s_batch[wave];
   uint64_t* stage = s_stage[wave];
   int staged = 0;  // wave-uniform
-  unsigned long long n_cand = 0, n_acc = 0, n_runs = 0;
-  const unsigned long long G = static_cast<unsigned long long>(gridDim.x) * blockDim.x;
-  unsigned long long next = static_cast<unsigned long long>(blockIdx.x) * blockDim.x + threadIdx.x;
+  uint32_t w_cand = 0, w_acc = 0, w_runs = 0;
 
-  bool active = false, need_run = false, neg = false, azero = true;
-  uint32_t u = 0, c = 0, s = 0, rend = 0, run_end = 0, pos = 0, t = 0, ctr3 = 0, key0 = 0, key1 = 0;
-  int64_t rpu = 0;
-  double cv = 0.0, dstart = 1.0, th = 0.0;
-  const ColParams* cpp = A.cp;
-  SkipTable tab;
-  for (;;) {
-    if (active && need_run && s >= rend) active = false;
-    if (!active && next < total) {  // the lane's next item
-      unsigned long long e = 0, hi = nb;  // last entry with off <= next
-      while (hi - e > 1) {
-        const unsigned long long mid = (e + hi) >> 1;
-        if (R[mid].off <= next)
-          e = mid;
-        else
-          hi = mid;
-      }
-      const BigSamp& bs = R[e];
-      const uint32_t il = static_cast<uint32_t>(next - bs.off);
-      next += G;
-      u = bs.u;
-      c = bs.c;
-      rpu = bs.rp;
-      cv = bs.cv;
-      neg = bs.neg != 0;
-      const uint32_t J = bs.J, d = bs.d;
-      cpp = A.cp + c;
-      azero = (cpp->flags & kAZero) != 0;
-      th = cpp->theta;
-      ctr3 = (cpp->qid << 8) | static_cast<uint32_t>(cpp->level);
-      key0 = cpp->key0;
-      key1 = cpp->key1;
-      const uint32_t nwin = ((d - 1) >> kSegLog2) - (J >> kSegLog2) + 1;
-      const uint32_t w0 = il * kWinPerItem;
-      const uint32_t w1 = (w0 + kWinPerItem) < nwin ? w0 + kWinPerItem : nwin;
-      const uint32_t ws = ((J >> kSegLog2) + w0) << kSegLog2;
-      const uint32_t we = ((J >> kSegLog2) + w1) << kSegLog2;
-      s = ws > J ? ws : J;
-      rend = we < d ? we : d;
-      if (azero) tab = make_skip_table(bs.p0);
-      active = true;
-      need_run = true;
-    }
-    if (!__any(active)) break;
-    if (active && need_run) {  // a run, as in k_level
-      ++n_runs;
-      const uint32_t wnext = ((s >> kSegLog2) + 1u) << kSegLog2;
-      const uint32_t wend = wnext < rend ? wnext : rend;
-      run_end = wend;
-      if (!azero) {
-        // the group end is loaded beside the factor degree (one round trip)
-        const uint32_t ge = A.gend[rpu + s];
-        dstart = A.arcfac != nullptr ? A.arcfac[rpu + s] : cpp->da[A.nd[rpu + s]];
-        const double num = cv * dstart;
-        const double pr = num / th;
-        if (!(pr * static_cast<double>(wend - s) <= kMergeCandidates) && ge < wend) run_end = ge;
-        tab = make_skip_table(pr);
-      }
-      pos = s;
-      t = 0;
-      need_run = false;
-    }
-    bool emit = false;
-    uint32_t v = 0;
-    Delta delta{};
-    if (active && !need_run) {  // one draw, as in k_level
-      const U4 o = philox4x32_10(t, s, u, ctr3, key0, key1);
-      const double V = unit_double(o.x, o.y);
-      const uint32_t cand = pos + static_cast<uint32_t>(geometric_skip(tab, V));
-      if (cand >= run_end) {
-        s = run_end;
-        need_run = true;
-      } else {
-        ++n_cand;
-        const int64_t arc = rpu + cand;
-        const uint32_t va = A.col[arc];  // beside the factor degree, as in k_level
-        bool accept = true;
-        if (!azero) {
-          const double ratio = (A.arcfac != nullptr ? A.arcfac[arc] : cpp->da[A.nd[arc]]) / dstart;
-          accept = unit_double(o.z, o.w) < ratio;
-        }
-        if (accept) {
-          ++n_acc;
-          v = va;
-          emit = true;
-          delta = P::theta_units(*cpp, neg);
-        }
-        pos = cand + 1;
-        ++t;
-      }
-    }
-    if (binned) {
-      emit_record<kG>(A, s_hist, reinterpret_cast<uint32_t*>(stage), staged, emit, v, c, neg, acc_next);
-    } else {
-      const size_t vcell = static_cast<size_t>(v) * A.su + static_cast<size_t>(c) * A.sc;
-      bool first = false;
-      if (emit) {
-        if (sparse)
-          first = P::add_ret(acc_next, vcell, delta);
-        else
-          P::add(acc_next, vcell, delta);
-      }
-      if (sparse) stage_push(stage, staged, (static_cast<uint64_t>(v) << 32) | c, first, A.fout, A.cnt_out);
+  // items [i0, i1) of this wave, from entry e on
+  const unsigned long long nw = static_cast<unsigned long long>(gridDim.x) * kWaves;
+  const unsigned long long per = (total + nw - 1) / nw;
+  unsigned long long i0 = (static_cast<unsigned long long>(blockIdx.x) * kWaves + wave) * per;
+  const unsigned long long i1 = i0 + per < total ? i0 + per : total;
+  unsigned long long e = 0;
+  if (i0 < i1) {
+    unsigned long long hi = nb;  // last entry with off <= i0
+    while (hi - e > 1) {
+      const unsigned long long mid = (e + hi) >> 1;
+      if (R[mid].off <= i0)
+        e = mid;
+      else
+        hi = mid;
     }
   }
+  auto refill = [&](uint32_t& it_next, uint32_t& it_total) -> bool {
+    if (i0 >= i1) return false;
+    wave_sync();  // every lane has read the previous batch
+    const int k = static_cast<int>(nb - e < (unsigned long long)kBatch ? nb - e : kBatch);
+    BigSamp bs{};
+    if (lane < k) bs = R[e + lane];
+    const ColParams& cp = A.cp[bs.c & kBatchCol];
+    B.rp[lane] = bs.rp;
+    B.cv[lane] = bs.cv;
+    B.p0[lane] = bs.p0;
+    B.th[lane] = cp.theta;
+    B.ctr3[lane] = (cp.qid << 8) | static_cast<uint32_t>(cp.level);
+    B.u[lane] = bs.u;
+    B.c[lane] = bs.c;
+    B.d[lane] = bs.d;
+    B.J[lane] = bs.J;
+    const uint32_t items = queue_items(B, bs.items);
+    wave_sync();
+    const unsigned long long first = R[e].off;  // the offsets of consecutive entries are contiguous
+    const unsigned long long end = first + items;
+    it_next = static_cast<uint32_t>(i0 - first);
+    it_total = static_cast<uint32_t>((end < i1 ? end : i1) - first);
+    i0 = end < i1 ? end : i1;
+    e += static_cast<unsigned long long>(k);
+    return true;
+  };
+  auto emit_sampled = [&](bool emit, uint32_t v, uint32_t c, const Delta& delta, bool neg) {
+    if (binned) {
+      emit_record<kG>(A, s_hist, reinterpret_cast<uint32_t*>(stage), staged, emit, v, c, neg, acc_next);
+      return;
+    }
+    const size_t vcell = static_cast<size_t>(v) * A.su + static_cast<size_t>(c) * A.sc;
+    bool first = false;
+    if (emit) {
+      if (sparse)
+        first = P::add_ret(acc_next, vcell, delta);
+      else
+        P::add(acc_next, vcell, delta);
+    }
+    if (sparse) stage_push(stage, staged, (static_cast<uint64_t>(v) << 32) | c, first, A.fout, A.cnt_out);
+  };
+  auto served = [](uint32_t, uint32_t, uint32_t, uint32_t) {};
+  sample_loop<T, false>(A, B, refill, emit_sampled, served, w_cand, w_acc, w_runs);
   if (sparse) stage_flush(stage, staged, A.fout, A.cnt_out);
   if (binned) finish_records<kG>(A, s_hist, reinterpret_cast<uint32_t*>(stage), staged, acc_next);
-  unsigned long long* cnt = count_row(A);
-  const unsigned long long v3 = wave_sum_u64(n_cand);
-  const unsigned long long v4 = wave_sum_u64(n_acc);
-  const unsigned long long v5 = wave_sum_u64(n_runs);
-  if (lane_id() == 0) {
-    if (v3) atomicAdd(cnt + 3, v3);
-    if (v4) atomicAdd(cnt + 4, v4);
-    if (v5) atomicAdd(cnt + 5, v5);
+  if (lane == 0) {
+    unsigned long long* cnt = count_row(A);
+    if (w_cand) atomicAdd(cnt + 3, static_cast<unsigned long long>(w_cand));
+    if (w_acc) atomicAdd(cnt + 4, static_cast<unsigned long long>(w_acc));
+    if (w_runs) atomicAdd(cnt + 5, static_cast<unsigned long long>(w_runs));
   }
 }
 

@@ -618,7 +618,7 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
   const unsigned cgrid = grid_for(static_cast<int64_t>((cells + cseg - 1) / cseg), kThreads / kWave, 1280);
 
   // rows with long deterministic prefixes, deferred per level to k_det_big
-  constexpr unsigned long long kBigCap = 1ull << 16;
+  constexpr unsigned long long kBigCap = 1ull << 18;
   unsigned long long big_cap = kBigCap;
   if (const char* e = std::getenv("AGP_BIG_ROWS")) {  // shorter lists (tests); 0: no deferral
     const unsigned long long v = std::strtoull(e, nullptr, 10);
