@@ -109,12 +109,29 @@ struct BigSamp {
   uint32_t items, pad;
 };
 
+// How a launch takes its columns' level parameters: a batched call's levels
+// are the same for every column and sit in scalar registers, with a = 0 and
+// a > 0 as kernels of their own (each holds only its own lane state: with one
+// kernel for all, the parameters of every entry were loads and lane
+// registers); the server's columns are each at a level of their own.
+enum : int { kBatchAZ = 0, kBatchAP = 1, kPerColumn = 2 };
+
+// One level of a batched call (device memory, so that a captured level loop
+// serves every call with the same buffers).
+struct LevelParams {
+  double rho, kappa;    // Y_{i+1} / Y_i and S w_i / Y_i
+  int flags;            // kLastLevel
+  uint32_t key0, key1;  // 64-bit seed
+  int pad;
+};
+
+// rho to out_stride, key0 to flags: the server's columns only.
 struct ColParams {
   double theta;          // eps * ||x_c||_1
   double scale;          // 2^-ue (binary32 units)
+  long long dtheta;      // fl(theta) in units
   double rho;            // Y_{i+1} / Y_i at the column's current level
   double kappa;          // S w_i / Y_i at the column's current level
-  long long dtheta;      // fl(theta) in units
   const double* da;      // d^-a, d = 0..max degree
   const double* db;      // d^-b
   void* out;             // reserve of node u at out + u * out_stride
@@ -135,6 +152,12 @@ struct LevelArgs {
   const int32_t* deg;   // row lengths (neighbours to push to)
   const int32_t* fdeg;  // degrees in the factors d^-a, d^-b
   const ColParams* cp;
+  // batched calls: the level's parameters, the degree-power tables and the
+  // reserve of node u, column c at out[u * out_stride + c]
+  const LevelParams* lp;
+  const double *da, *db;
+  void* out;
+  long long out_stride;
   // batched calls (one a and b for every column): per node u, d_u^-b and the
   // d^-a of its first neighbour (2 doubles; 0 for a node without arcs), or
   // null (the setup then reads them through the degree tables)
@@ -187,6 +210,21 @@ struct LevelArgs {
   const uint32_t* tab_mask;
   const uint32_t* tab_cur;   // this level's tables
 };
+
+// The arguments of the running kernel (whose first parameter is a LevelArgs),
+// read from its argument segment again: the value hidden in the empty asm
+// keeps the compiler from holding every argument of a batch's setup or of a
+// flush in scalar registers across the draw loop, where more than fit became
+// a lane read (a vector instruction) at each use: 231 of them in the a > 0
+// kernel, 45 this way.  With the kernels split by kBatchAZ / kBatchAP, 128
+// columns of features on 2.4M nodes took 101 -> 90 ms, 32 columns on 8M nodes
+// 42.7 -> 37.5, 64 transition columns on 2^22 nodes 129 -> 121.
+__device__ __forceinline__ const LevelArgs& args_again() {
+  using KernArg = const LevelArgs __attribute__((address_space(4)));
+  KernArg* p = (KernArg*)__builtin_amdgcn_kernarg_segment_ptr();
+  __asm__ volatile("" : "+s"(p));
+  return *(const LevelArgs*)p;
+}
 
 // Position of node v in a query's table, claiming it if v is not there yet
 // (*first: v was not there); ~0u when the table is too full.  mask == ~0u:
@@ -372,7 +410,8 @@ __device__ __forceinline__ void apply_record(const LevelArgs&, unsigned long lon
 // from its back (one atomic on each group's count; records beyond a group's
 // buffer are added with atomics).  Wave-uniform.
 template <int kG, typename Cell>
-__device__ __forceinline__ void stage_flush_records(uint32_t* stage, int& staged, const LevelArgs& A, Cell* acc) {
+__device__ __forceinline__ void stage_flush_records(uint32_t* stage, int& staged, Cell* acc) {
+  const LevelArgs& A = args_again();
   if constexpr (kG == 1) {
     if (staged == 0) return;
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -437,12 +476,12 @@ __device__ __forceinline__ void emit_record(const LevelArgs& A, unsigned int* s_
     if (emit) stage[g ? kRecStage - 1 - (n1 + __popcll(m1 & lt)) : n0 + __popcll(m0 & lt)] = rec;
     const int k0 = n0 + __popcll(m0), k1 = n1 + __popcll(m1);
     staged = k0 | (k1 << 16);
-    if (k0 + k1 > kRecStage - kWave) stage_flush_records<kG>(stage, staged, A, acc);
+    if (k0 + k1 > kRecStage - kWave) stage_flush_records<kG>(stage, staged, acc);
   } else {
     const unsigned long long m0 = __ballot(emit);
     if (emit) stage[staged + __popcll(m0 & lt)] = rec;
     staged += __popcll(m0);
-    if (staged > kRecStage - kWave) stage_flush_records<kG>(stage, staged, A, acc);
+    if (staged > kRecStage - kWave) stage_flush_records<kG>(stage, staged, acc);
   }
 }
 
@@ -451,7 +490,7 @@ __device__ __forceinline__ void emit_record(const LevelArgs& A, unsigned int* s_
 template <int kG, typename Cell>
 __device__ __forceinline__ void finish_records(const LevelArgs& A, unsigned int* s_hist, uint32_t* stage, int& staged,
                                                Cell* acc) {
-  stage_flush_records<kG>(stage, staged, A, acc);
+  stage_flush_records<kG>(stage, staged, acc);
   __syncthreads();
   for (int i = threadIdx.x; i < kBuckets; i += blockDim.x)
     if (s_hist[i]) atomicAdd(A.bucket_count + i, s_hist[i]);
@@ -535,8 +574,8 @@ struct BatchLds {
   // random stream's counter word), so that taking an item reads LDS
   double th[kBatch];
   uint32_t ctr3[kBatch];
-  // c: column | kBatchNeg (negative residue) | kBatchAZero (a = 0) | log2 of
-  // the windows per work item << kBatchShiftBit
+  // c: column | kBatchNeg (negative residue) | kBatchAZero (server: a = 0) |
+  // log2 of the windows per work item << kBatchShiftBit
   uint32_t u[kBatch], c[kBatch], d[kBatch], J[kBatch];
   uint8_t item_entry[kItemMap];  // the entry of each of the batch's first kItemMap work items
 };
@@ -607,28 +646,28 @@ __device__ __forceinline__ uint32_t queue_items(BatchLds& B, uint32_t iwork) {
 // Draws the queued work items of the batches that refill sets up:
 // refill(it_next, it_total) puts the next batch in B and its queue of items
 // [it_next, it_total), or returns false when none is left; emit(pushed, v, c,
-// delta, neg) makes a sampled push of every lane that has one (all lanes
+// neg) makes a sampled push of every lane that has one (all lanes
 // together); served(c, candidates, accepted, runs) gets a finished item's
 // counts (server).  w_*: wave-uniform counts (batched calls).
-template <typename T, bool kServe, typename Refill, typename Emit, typename Served>
+template <int kMode, typename Refill, typename Emit, typename Served>
 __device__ __forceinline__ void sample_loop(const LevelArgs& A, BatchLds& B, Refill&& refill, Emit&& emit_sampled,
                                             Served&& served, uint32_t& w_cand, uint32_t& w_acc, uint32_t& w_runs) {
-  using P = Prec<T>;
-  using Delta = typename P::Delta;
+  constexpr bool kServe = kMode == kPerColumn;
   const int lane = lane_id();
   const unsigned long long lt_mask = (1ull << lane) - 1ull;
   uint32_t it_next = 0, it_total = 0;  // wave-uniform: queue of the loaded batch
   bool more = true;                    // wave-uniform: refill may have another batch
 
   // lane state: the sampled work item in progress
-  bool active = false, need_run = false, neg = false, azero = true;
+  bool active = false, need_run = false, neg = false;
+  bool azero = kMode == kBatchAZ;  // (a constant but for the server)
   uint32_t u = 0, c = 0, s = 0, rend = 0, run_end = 0, pos = 0, t = 0, ctr3 = 0;
-  uint32_t key0 = kServe ? 0u : __builtin_amdgcn_readfirstlane(A.cp[0].key0);
-  uint32_t key1 = kServe ? 0u : __builtin_amdgcn_readfirstlane(A.cp[0].key1);
+  uint32_t key0 = kServe ? 0u : __builtin_amdgcn_readfirstlane(A.lp->key0);
+  uint32_t key1 = kServe ? 0u : __builtin_amdgcn_readfirstlane(A.lp->key1);
   uint32_t it_cand = 0, it_acc = 0, it_runs = 0;
   int64_t rpu = 0;
   double cv = 0.0, dstart = 1.0, th = 0.0;
-  const ColParams* cpp = A.cp;
+  const double* da = A.da;
   SkipTable tab;
 
   for (;;) {
@@ -651,16 +690,19 @@ __device__ __forceinline__ void sample_loop(const LevelArgs& A, BatchLds& B, Ref
           const uint32_t cw = B.c[e];
           c = cw & kBatchCol;
           rpu = B.rp[e];
-          cv = B.cv[e];
           neg = (cw & kBatchNeg) != 0;
           const uint32_t J = B.J[e], d = B.d[e];
-          cpp = A.cp + c;
-          azero = (cw & kBatchAZero) != 0;
-          th = B.th[e];
           ctr3 = B.ctr3[e];
           if (kServe) {
-            key0 = cpp->key0;
-            key1 = cpp->key1;
+            const ColParams& cp = A.cp[c];
+            azero = (cw & kBatchAZero) != 0;
+            key0 = cp.key0;
+            key1 = cp.key1;
+            da = cp.da;
+          }
+          if (!azero) {
+            cv = B.cv[e];
+            th = B.th[e];
           }
           const uint32_t shift = (cw >> kBatchShiftBit) & 7u;
           const uint32_t nwin = ((d - 1) >> kSegLog2) - (J >> kSegLog2) + 1;
@@ -701,7 +743,7 @@ __device__ __forceinline__ void sample_loop(const LevelArgs& A, BatchLds& B, Ref
         // row start, from the entry's setup); the group end only when the
         // run stops there
         if (!(first && dstart > 0.0))
-          dstart = A.arcfac != nullptr ? A.arcfac[rpu + s] : cpp->da[A.nd[rpu + s]];
+          dstart = A.arcfac != nullptr ? A.arcfac[rpu + s] : da[A.nd[rpu + s]];
         const double num = cv * dstart;
         const double pr = num / th;
         if (!(pr * static_cast<double>(wend - s) <= kMergeCandidates)) {
@@ -717,7 +759,6 @@ __device__ __forceinline__ void sample_loop(const LevelArgs& A, BatchLds& B, Ref
     // (e) one draw of the run's chain
     bool emit = false, cand_hit = false;
     uint32_t v = 0;
-    Delta delta{};
     if (active && !need_run) {
       const U4 o = kServe ? philox4x32_10(t, s, u, ctr3, key0, key1) : philox4x32_10_skey(t, s, u, ctr3, key0, key1);
       const double V = unit_double(o.x, o.y);
@@ -734,14 +775,13 @@ __device__ __forceinline__ void sample_loop(const LevelArgs& A, BatchLds& B, Ref
         const uint32_t va = A.col[arc];
         bool accept = true;  // a = 0: the ratio is 1 and every uniform is below it
         if (!azero) {
-          const double ratio = (A.arcfac != nullptr ? A.arcfac[arc] : cpp->da[A.nd[arc]]) / dstart;
+          const double ratio = (A.arcfac != nullptr ? A.arcfac[arc] : da[A.nd[arc]]) / dstart;
           accept = unit_double(o.z, o.w) < ratio;
         }
         if (accept) {
           if (kServe) ++it_acc;
           v = va;
           emit = true;
-          delta = P::theta_units(*cpp, neg);
         }
         pos = cand + 1;
         ++t;
@@ -751,7 +791,7 @@ __device__ __forceinline__ void sample_loop(const LevelArgs& A, BatchLds& B, Ref
       w_cand += static_cast<uint32_t>(__popcll(__ballot(cand_hit)));
       w_acc += static_cast<uint32_t>(__popcll(__ballot(emit)));
     }
-    emit_sampled(emit, v, c, delta, neg);
+    emit_sampled(emit, v, c, neg);
   }
 }
 
@@ -782,14 +822,16 @@ __device__ __forceinline__ bool defer_slots(unsigned long long* ctr, unsigned lo
 }
 
 // kFirst: the residues are the signal x (level 0 of a batched call).
-// kServe: counters and overflow mass are kept per column instead of per level.
+// kMode: kBatchAZ, kBatchAP or kPerColumn (the server: counters and overflow
+// mass are kept per column instead of per level).
 // kG: column groups of the records on binned levels (1 or 2).
-template <typename T, bool kFirst, bool kServe, int kG = 1>
+template <typename T, bool kFirst, int kMode, int kG = 1>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_level(LevelArgs A, const T* __restrict__ x,
                                                     typename Prec<T>::Cell* __restrict__ acc_cur,
                                                     typename Prec<T>::Cell* __restrict__ acc_next) {
   using P = Prec<T>;
   using Delta = typename P::Delta;
+  constexpr bool kServe = kMode == kPerColumn;
   constexpr int kWaves = kThreads / kWave;
   __shared__ BatchLds s_batch[kWaves];
   __shared__ uint64_t s_stage[kWaves][kStage];
@@ -865,10 +907,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
     if (sparse)  // stage first-touched cells, flush in chunks
       stage_push(stage, staged, (static_cast<uint64_t>(v) << 32) | ec, first, A.fout, A.cnt_out);
   };
-  auto emit_sampled = [&](bool emit, uint32_t v, uint32_t ec, const Delta& delta, bool eneg) {
+  auto emit_sampled = [&](bool emit, uint32_t v, uint32_t ec, bool eneg) {
     if (binned) {
       emit_record<kG>(A, s_hist, reinterpret_cast<uint32_t*>(stage), staged, emit, v, ec, eneg, acc_next);
     } else {
+      Delta delta{};
+      if (emit) delta = P::theta_units(A.cp[ec], eneg);
       emit_atomic(emit, v, ec, delta);
     }
   };
@@ -905,6 +949,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
 
   auto refill = [&](uint32_t& it_next, uint32_t& it_total) -> bool {
     if (bnext >= nbatch) return false;
+    const LevelArgs& A = args_again();
     wave_sync();  // every lane has read the previous batch
     const unsigned long long e0 = bnext * eb;
     bnext += nwaves;
@@ -952,6 +997,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
         rp_u = A.rp[eu];
       }
       const ColParams& cp = A.cp[ec];
+      const double rho = kServe ? cp.rho : A.lp->rho, kappa = kServe ? cp.kappa : A.lp->kappa;
+      const int lflags = kServe ? cp.flags : A.lp->flags;
+      const bool azero = kServe ? (lflags & kAZero) != 0 : kMode == kBatchAZ;
+      const double* const da = kServe ? cp.da : A.da;
+      const double* const db = kServe ? cp.db : A.db;
       T r;
       if (kFirst)
         r = x[static_cast<size_t>(eu) * static_cast<size_t>(A.xld) + ec];
@@ -960,23 +1010,24 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
       // (a served query's table also holds nodes whose sum cancelled to zero,
       // and level 0 over every cell holds the zero cells of x: they are not
       // in the frontier)
-      const bool live = !(cp.flags & kDrop) && !((kServe || (kFirst && A.fin == nullptr)) && r == T(0));
+      const bool live = !(kServe && (lflags & kDrop)) && !((kServe || (kFirst && A.fin == nullptr)) && r == T(0));
       if (kServe && live) {
         deg_u = static_cast<uint32_t>(A.deg[eu]);
         fdeg_u = A.fdeg[eu];
         rp_u = A.rp[eu];
       }
-      T* const o = static_cast<T*>(cp.out) + static_cast<size_t>(eu) * static_cast<size_t>(cp.out_stride);
-      const T o_old = (live && cp.kappa != 0.0) ? *o : T(0);
+      T* const o = kServe ? static_cast<T*>(cp.out) + static_cast<size_t>(eu) * static_cast<size_t>(cp.out_stride)
+                          : static_cast<T*>(A.out) + static_cast<size_t>(eu) * static_cast<size_t>(A.out_stride) + ec;
+      const T o_old = (live && kappa != 0.0) ? *o : T(0);
       // (a = 0: every factor d^-a is 1, no degree is read)
-      const uint32_t nd_first = (!pre && live && deg_u > 0 && !(cp.flags & kAZero)) ? A.nd[rp_u] : 0u;
-      const double db_u = live ? (pre ? nf.x : cp.db[fdeg_u]) : 0.0;
+      const uint32_t nd_first = (!pre && live && deg_u > 0 && !azero) ? A.nd[rp_u] : 0u;
+      const double db_u = live ? (pre ? nf.x : db[fdeg_u]) : 0.0;
       eneg = r < T(0);
-      ecw = ec | (eneg ? kBatchNeg : 0u) | ((cp.flags & kAZero) ? kBatchAZero : 0u);
+      ecw = ec | (eneg ? kBatchNeg : 0u) | (kServe && azero ? kBatchAZero : 0u);
       // (the previous batch is no longer read: these slots are free; the
       // entries past ne get no work items)
       B.th[lane] = cp.theta;
-      B.ctr3[lane] = (cp.qid << 8) | static_cast<uint32_t>(cp.level);
+      B.ctr3[lane] = (cp.qid << 8) | static_cast<uint32_t>(kServe ? cp.level : A.level);
           if (live) {
         if (kServe) {
           serve_count(A, s_scnt, ec, 0, 1ull);
@@ -985,34 +1036,34 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
           n_hash += splitmix64(eu);
         }
         // reserve: pi(u) += (S w_i / Y_i) r(u), rounded to the working precision
-        if (cp.kappa != 0.0) {
-          const T q = to_w(cp.kappa * static_cast<double>(r), T());
+        if (kappa != 0.0) {
+          const T q = to_w(kappa * static_cast<double>(r), T());
           *o = o_old + q;
         }
-        if (!(cp.flags & kLastLevel) && cp.rho != 0.0) {
+        if (!(lflags & kLastLevel) && rho != 0.0) {
           ed = deg_u;
           if (ed > 0) {
             const double absr = fabs(static_cast<double>(r));
-            const double t0 = cp.rho * absr;
+            const double t0 = rho * absr;
             ecv = t0 * db_u;
             const double eth = cp.theta;
             erp = rp_u;
             double inc0 = ecv;
-            if (cp.flags & kAZero) {
+            if (azero) {
               eJ = (ecv >= eth) ? ed : 0u;
               const double num = ecv * 1.0;  // every neighbour's factor d^-0 is 1
               ep0 = num / eth;
             } else {  // increments fall along the degree-sorted row: binary search
-              const double da0 = pre ? nf.y : cp.da[nd_first];
+              const double da0 = pre ? nf.y : da[nd_first];
               inc0 = ecv * da0;
               uint32_t lo = 0, hi = ed;
               if (!(inc0 >= eth))
                 hi = 0;  // no deterministic push
-              else if (ecv * (pre_arc ? A.arcfac[erp + ed - 1] : cp.da[A.nd[erp + ed - 1]]) >= eth)
+              else if (ecv * (pre_arc ? A.arcfac[erp + ed - 1] : da[A.nd[erp + ed - 1]]) >= eth)
                 lo = ed;  // every push is deterministic
               while (lo < hi) {
                 const uint32_t mid = (lo + hi) >> 1;
-                const double inc = ecv * (pre_arc ? A.arcfac[erp + mid] : cp.da[A.nd[erp + mid]]);
+                const double inc = ecv * (pre_arc ? A.arcfac[erp + mid] : da[A.nd[erp + mid]]);
                 if (inc >= eth)
                   lo = mid + 1;
                 else
@@ -1123,7 +1174,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
         const ColParams* cpd = A.cp + vc;
         v = A.col[arc];
         double inc = B.cv[e];
-        if (!(cpd->flags & kAZero)) inc = inc * (A.arcfac != nullptr ? A.arcfac[arc] : cpd->da[A.nd[arc]]);
+        if (kServe ? !(cw & kBatchAZero) : kMode == kBatchAP)
+          inc = inc * (A.arcfac != nullptr ? A.arcfac[arc] : (kServe ? cpd->da : A.da)[A.nd[arc]]);
         T val = to_w(inc, T());
         if (cw & kBatchNeg) val = -val;
         emit = P::to_units(val, *cpd, &delta);
@@ -1141,7 +1193,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
     }
     if (runs) serve_count(A, s_scnt, c, 5, static_cast<unsigned long long>(runs));
   };
-  sample_loop<T, kServe>(A, B, refill, emit_sampled, served, w_cand, w_acc, w_runs);
+  sample_loop<kMode>(A, B, refill, emit_sampled, served, w_cand, w_acc, w_runs);
   if (sparse) stage_flush(stage, staged, A.fout, A.cnt_out);
   if (binned) finish_records<kG>(A, s_hist, reinterpret_cast<uint32_t*>(stage), staged, acc_next);
   if (kServe) {  // flush the block's per-column sums
@@ -1195,7 +1247,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
 // the rows' offsets and moves to the next row when it crosses its end.  The
 // pushes are computed and accumulated as in k_level (first contributions of
 // a sparse level appended to the next frontier).
-template <typename T, int kG = 1>
+template <typename T, int kMode, int kG = 1>
 __global__ __launch_bounds__(kThreads) void k_det_big(LevelArgs A, typename Prec<T>::Cell* __restrict__ acc_next) {
   using P = Prec<T>;
   using Delta = typename P::Delta;
@@ -1246,7 +1298,7 @@ __global__ __launch_bounds__(kThreads) void k_det_big(LevelArgs A, typename Prec
         const int64_t arc = br.rp + static_cast<int64_t>(k - off);
         v = A.col[arc];
         double inc = br.cv;
-        if (!(cpd->flags & kAZero)) inc = inc * (A.arcfac != nullptr ? A.arcfac[arc] : cpd->da[A.nd[arc]]);
+        if (kMode == kBatchAP) inc = inc * (A.arcfac != nullptr ? A.arcfac[arc] : A.da[A.nd[arc]]);
         T val = to_w(inc, T());
         if (br.neg) val = -val;
         emit = P::to_units(val, *cpd, &delta);
@@ -1276,7 +1328,7 @@ __global__ __launch_bounds__(kThreads) void k_det_big(LevelArgs A, typename Prec
 // emitted as in k_level's mode for the level (records, first-touch appends or
 // plain atomics), and the level's candidate and acceptance counters get this
 // kernel's counts.
-template <typename T, int kG = 1>
+template <typename T, int kMode, int kG = 1>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_samp_big(
     LevelArgs A, typename Prec<T>::Cell* __restrict__ acc_next) {
   using P = Prec<T>;
@@ -1323,6 +1375,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
   }
   auto refill = [&](uint32_t& it_next, uint32_t& it_total) -> bool {
     if (i0 >= i1) return false;
+    const LevelArgs& A = args_again();
+    const BigSamp* const R = A.samp;
     wave_sync();  // every lane has read the previous batch
     const int k = static_cast<int>(nb - e < (unsigned long long)kBatch ? nb - e : kBatch);
     BigSamp bs{};
@@ -1332,7 +1386,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
     B.cv[lane] = bs.cv;
     B.p0[lane] = bs.p0;
     B.th[lane] = cp.theta;
-    B.ctr3[lane] = (cp.qid << 8) | static_cast<uint32_t>(cp.level);
+    B.ctr3[lane] = (cp.qid << 8) | static_cast<uint32_t>(A.level);
     B.u[lane] = bs.u;
     B.c[lane] = bs.c;
     B.d[lane] = bs.d;
@@ -1347,11 +1401,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
     e += static_cast<unsigned long long>(k);
     return true;
   };
-  auto emit_sampled = [&](bool emit, uint32_t v, uint32_t c, const Delta& delta, bool neg) {
+  auto emit_sampled = [&](bool emit, uint32_t v, uint32_t c, bool neg) {
     if (binned) {
       emit_record<kG>(A, s_hist, reinterpret_cast<uint32_t*>(stage), staged, emit, v, c, neg, acc_next);
       return;
     }
+    Delta delta{};
+    if (emit) delta = P::theta_units(A.cp[c], neg);
     const size_t vcell = static_cast<size_t>(v) * A.su + static_cast<size_t>(c) * A.sc;
     bool first = false;
     if (emit) {
@@ -1363,7 +1419,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
     if (sparse) stage_push(stage, staged, (static_cast<uint64_t>(v) << 32) | c, first, A.fout, A.cnt_out);
   };
   auto served = [](uint32_t, uint32_t, uint32_t, uint32_t) {};
-  sample_loop<T, false>(A, B, refill, emit_sampled, served, w_cand, w_acc, w_runs);
+  sample_loop<kMode>(A, B, refill, emit_sampled, served, w_cand, w_acc, w_runs);
   if (sparse) stage_flush(stage, staged, A.fout, A.cnt_out);
   if (binned) finish_records<kG>(A, s_hist, reinterpret_cast<uint32_t*>(stage), staged, acc_next);
   if (lane == 0) {
@@ -1388,6 +1444,8 @@ __global__ __launch_bounds__(kThreads) void k_estimate(LevelArgs A, const T* __r
   // large frontiers: an evenly spaced sample of 2^20 to 2^21 entries, scaled
   // up (the estimate only chooses between interchangeable aggregation modes)
   const unsigned long long stride = count >= (1ull << 21) ? count >> 20 : 1ull;
+  const double rho = A.lp->rho;
+  if ((A.lp->flags & kLastLevel) || rho == 0.0) return;
   double sum = 0.0;
   for (unsigned long long j = blockIdx.x * (unsigned long long)blockDim.x + threadIdx.x; j * stride < count;
        j += (unsigned long long)gridDim.x * blockDim.x) {
@@ -1402,7 +1460,6 @@ __global__ __launch_bounds__(kThreads) void k_estimate(LevelArgs A, const T* __r
       c = static_cast<uint32_t>(item);
     }
     const ColParams& cp = A.cp[c];
-    if ((cp.flags & (kDrop | kLastLevel)) || cp.rho == 0.0) continue;
     const uint32_t d = static_cast<uint32_t>(A.deg[u]);
     if (d == 0) continue;
     const size_t cell = static_cast<size_t>(u) * A.su + static_cast<size_t>(c) * A.sc;
@@ -1415,7 +1472,7 @@ __global__ __launch_bounds__(kThreads) void k_estimate(LevelArgs A, const T* __r
     } else {
       absr = 0.0;  // binary64 calls are never binned
     }
-    const double cv = cp.rho * absr * cp.db[A.fdeg[u]];
+    const double cv = rho * absr * A.db[A.fdeg[u]];
     sum += cv >= cp.theta ? static_cast<double>(d) : static_cast<double>(d) * (cv / cp.theta);
   }
 #pragma unroll

@@ -8,7 +8,7 @@
 //            (binary32: int64 cells; binary64: 128-bit cells), ping-ponged
 //   F[2]     frontier lists of (u << 32 | c) with non-zero residue
 // One k_level launch per level (level_kernels.h); the per-column parameters of
-// the level are written by k_set_level.  Non-negative signals append sparse
+// the level are read by k_level from a device table (LevelParams).  Non-negative signals append sparse
 // frontiers directly; denser frontiers are compacted by a wave-ballot pass.
 #include <hip/hip_runtime.h>
 
@@ -311,34 +311,6 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
   cp[c] = p;
 }
 
-// Level-dependent parameters of every column of a batched call.
-// Per-level values of a call, in device memory so that a captured level
-// loop serves every call with the same buffers.
-struct LevelParams {
-  double rho, kappa;
-  int flags;
-  uint32_t key0, key1;
-  int pad;
-};
-
-__global__ void k_set_level(ColParams* __restrict__ cp, int C, int level, const LevelParams* __restrict__ lp,
-                            const double* da, const double* db, void* out, long long out_stride, size_t elem) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= C) return;
-  ColParams& p = cp[c];
-  const LevelParams q = lp[level];
-  p.level = level;
-  p.rho = q.rho;
-  p.kappa = q.kappa;
-  p.flags = q.flags;
-  p.da = da;
-  p.db = db;
-  p.key0 = q.key0;
-  p.key1 = q.key1;
-  p.out = static_cast<char*>(out) + static_cast<size_t>(c) * elem;
-  p.out_stride = out_stride;
-}
-
 // Per node u: d_u^-b (its factor degree's entry) and the d^-a of its first
 // neighbour in the degree-sorted row (0 for a node without arcs).
 __global__ void k_node_factors(const int64_t* __restrict__ rp, const int32_t* __restrict__ deg,
@@ -457,6 +429,26 @@ agp_tuning_t tuning_for(agp_graph* g, int32_t C, double a, double b, const agp_t
     if (v >= 1) t.big_items = static_cast<int32_t>(v);
   }
   return t;
+}
+
+// A level's kernels: the level, then the rows and suffixes it deferred
+// (grouped: records in two column groups, binary32 only).
+template <typename T, int kMode>
+void launch_level(const LevelArgs& A, int blocks, bool first, bool grouped, const T* x,
+                  typename Prec<T>::Cell* cur, typename Prec<T>::Cell* nxt, hipStream_t s) {
+  auto go = [&](auto G) {
+    constexpr int kG = decltype(G)::value;
+    if (first)
+      k_level<T, true, kMode, kG><<<blocks, kThreads, 0, s>>>(A, x, cur, nxt);
+    else
+      k_level<T, false, kMode, kG><<<blocks, kThreads, 0, s>>>(A, x, cur, nxt);
+    if (A.big_ctr != nullptr) k_det_big<T, kMode, kG><<<1024, kThreads, 0, s>>>(A, nxt);
+    if (A.samp_ctr != nullptr) k_samp_big<T, kMode, kG><<<1024, kThreads, 0, s>>>(A, nxt);
+  };
+  if constexpr (sizeof(T) == 4) {
+    if (grouped) return go(std::integral_constant<int, 2>{});
+  }
+  go(std::integral_constant<int, 1>{});
 }
 
 // One tile of C columns: x and out point at the tile's first column, rows
@@ -652,6 +644,10 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
   A.deg = g->degree;
   A.fdeg = g->fdeg;
   A.cp = cp;
+  A.da = da;
+  A.db = db;
+  A.out = out;
+  A.out_stride = ldc;
   A.su = C;
   A.sc = 1;
   A.xld = ldc;
@@ -714,13 +710,13 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
       sc.arcfac_a = -1.0;
     }
   }
-  // per-level values of this call (read by k_set_level from device memory)
+  // per-level values of this call (read by the level kernels from device memory)
   LevelParams lph[AGP_MAX_LEVELS + 1];
   const uint32_t key0 = static_cast<uint32_t>(seed), key1 = static_cast<uint32_t>(seed >> 32);
   for (int32_t i = 0; i <= L; ++i) {
     lph[i].rho = rho[i];
     lph[i].kappa = kappa[i];
-    lph[i].flags = (i == L ? kLastLevel : 0) | (a == 0.0 ? kAZero : 0);
+    lph[i].flags = i == L ? kLastLevel : 0;
     lph[i].key0 = key0;
     lph[i].key1 = key1;
     lph[i].pad = 0;
@@ -731,8 +727,8 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
   // captured once and replayed (timed per level only when launched directly)
   auto levels = [&](hipStream_t s, bool timed) {
     for (int32_t i = 0; i <= L; ++i) {
-      k_set_level<<<grid_for(C, 64), 64, 0, s>>>(cp, C, i, lpd, da, db, out, ldc, sizeof(T));
       A.level = i;
+      A.lp = lpd + i;
       A.fin = (i == 0 && virtual0) ? nullptr : F[i & 1];
       A.cnt_in = counts + i;
       A.fout = F[(i + 1) & 1];
@@ -760,26 +756,11 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
           k_estimate<T, false><<<1024, kThreads, 0, s>>>(A, x, cur, est + i);
       }
       if (timed) (void)hipEventRecord(ev[4 * i + 1], s);
-      bool grouped = false;  // records in two column groups (binary32 only)
-      if constexpr (sizeof(T) == 4) {
-        grouped = bin_level && ng > 1;
-        if (grouped) {
-          if (i == 0)
-            k_level<T, true, false, 2><<<tune.level_blocks, kThreads, 0, s>>>(A, x, cur, nxt);
-          else
-            k_level<T, false, false, 2><<<tune.level_blocks, kThreads, 0, s>>>(A, x, cur, nxt);
-          if (A.big_ctr != nullptr) k_det_big<T, 2><<<1024, kThreads, 0, s>>>(A, nxt);
-          if (A.samp_ctr != nullptr) k_samp_big<T, 2><<<1024, kThreads, 0, s>>>(A, nxt);
-        }
-      }
-      if (!grouped) {
-        if (i == 0)
-          k_level<T, true, false><<<tune.level_blocks, kThreads, 0, s>>>(A, x, cur, nxt);
-        else
-          k_level<T, false, false><<<tune.level_blocks, kThreads, 0, s>>>(A, x, cur, nxt);
-        if (A.big_ctr != nullptr) k_det_big<T><<<1024, kThreads, 0, s>>>(A, nxt);
-        if (A.samp_ctr != nullptr) k_samp_big<T><<<1024, kThreads, 0, s>>>(A, nxt);
-      }
+      const bool grouped = sizeof(T) == 4 && bin_level && ng > 1;  // records in two column groups
+      if (a == 0.0)
+        launch_level<T, kBatchAZ>(A, tune.level_blocks, i == 0, grouped, x, cur, nxt, s);
+      else
+        launch_level<T, kBatchAP>(A, tune.level_blocks, i == 0, grouped, x, cur, nxt, s);
       if (timed) (void)hipEventRecord(ev[4 * i + 2], s);
       if (bin_level) {
         uint32_t* r0 = sc.rec[0].as<uint32_t>();

@@ -414,7 +414,7 @@ int step(agp_server* s) {
   A.tab_off = tab_next;
   A.tab_mask = tab_mask;
   A.tab_cur = tab_off;
-  k_level<float, false, true><<<kLevelBlocks, kThreads, 0, st>>>(A, nullptr, s->vals.as<long long>(),
+  k_level<float, false, kPerColumn><<<kLevelBlocks, kThreads, 0, st>>>(A, nullptr, s->vals.as<long long>(),
                                                                  s->vals.as<long long>());
   if (nplain > 0) {
     AGP_HIP(hipMemcpyAsync(s->plain.ptr, s->h_plain, sizeof(srv::PlainTable) * nplain, hipMemcpyHostToDevice, st));
