@@ -37,55 +37,12 @@ using namespace lvl;
 
 // ---------------------------------------------------------- thresholds
 // ||x_c||_1 in binary64: sequential over blocks of 4096 rows, then over the
-// block sums.  flags: 1 = non-finite entry, 2 = negative entry.  The same
-// pass forms the level-0 frontier (the non-zero cells of x, in any order).
-// One wave per (row block, 64 columns); loads are issued 32 rows at a time
-// and summed in row order; the frontier goes out in chunks of up to kCap
-// entries (one atomic on the shared list counter each).
-constexpr int kThetaBatch = 32;
-constexpr int kThetaCap = 4096;  // 32 KiB of LDS per wave
+// block sums.  flags: 1 = non-finite entry, 2 = negative entry.
+constexpr int kThetaBatch = 32;   // rows of loads in flight (k_theta_scan)
+constexpr int kThetaWaves = 16;   // waves of a row block (k_theta_partial)
+constexpr int kThetaLoads = 16;   // loads in flight per lane
 
 __global__ void k_set_u64(unsigned long long* p, unsigned long long v) { *p = v; }
-
-// kList: append the non-zero cells to F (the level-0 frontier); else only
-// count them in *cnt (a mostly non-zero signal needs no list).
-template <typename T, int kCap, bool kList>
-__global__ __launch_bounds__(kWave) void k_theta_partial(const T* __restrict__ x, long long ldx, int64_t n, int C,
-                                                         double* __restrict__ partial, int* __restrict__ flags,
-                                                         uint64_t* __restrict__ F, unsigned long long* __restrict__ cnt) {
-  __shared__ uint64_t s_stage[kList ? kCap : 1];
-  const int c = blockIdx.y * blockDim.x + threadIdx.x;
-  const bool live = c < C;
-  const int64_t lo = (int64_t)blockIdx.x * kThetaRows;
-  const int64_t hi = (lo + kThetaRows) < n ? lo + kThetaRows : n;
-  double sum = 0.0;
-  int f = 0;
-  int staged = 0;  // wave-uniform
-  for (int64_t i0 = lo; i0 < hi; i0 += kThetaBatch) {
-    T v[kThetaBatch];
-#pragma unroll
-    for (int k = 0; k < kThetaBatch; ++k)
-      v[k] = (live && i0 + k < hi) ? x[static_cast<size_t>(i0 + k) * static_cast<size_t>(ldx) + c] : T(0);
-#pragma unroll
-    for (int k = 0; k < kThetaBatch; ++k) {
-      if (i0 + k >= hi) continue;  // wave-uniform
-      if (!isfinite(static_cast<double>(v[k]))) f |= 1;
-      if (v[k] < T(0)) f |= 2;
-      sum = sum + fabs(static_cast<double>(v[k]));
-      if constexpr (kList)
-        stage_push<kCap>(s_stage, staged, (static_cast<uint64_t>(i0 + k) << 32) | static_cast<uint32_t>(c),
-                         v[k] != T(0), F, cnt);
-      else
-        staged += __popcll(__ballot(v[k] != T(0)));
-    }
-  }
-  if constexpr (kList)
-    stage_flush(s_stage, staged, F, cnt);
-  else if (staged > 0 && lane_id() == 0)
-    atomicAdd(cnt, static_cast<unsigned long long>(staged));
-  if (live) partial[(size_t)blockIdx.x * C + c] = sum;
-  if (f) atomicOr(flags, f);
-}
 
 // Adds the 64 lanes' values of v to sum in lane order (wave-uniform sum).
 __device__ __forceinline__ double add_lanes_in_order(double sum, double v) {
@@ -136,60 +93,147 @@ __device__ __forceinline__ bool wave_exact_sum(double s, int m, double& total) {
   return total < ldexp(1.0, m + 53);
 }
 
-// k_theta_partial for one column (C = 1): the lanes load all 4096 rows of the
-// block at once (row lo + 64 k + lane in v[k]); the block's sum is the exact
-// one when wave_exact_sum proves it, else the wave adds the rows one by one in
-// row order.  Either way it is the sequential sum of k_theta_partial; the
-// frontier entries are the same (u << 32).
-template <typename T, bool kList>
-__global__ __launch_bounds__(kWave) void k_theta_partial_c1(const T* __restrict__ x, long long ldx, int64_t n,
-                                                            double* __restrict__ partial, int* __restrict__ flags,
-                                                            uint64_t* __restrict__ F,
-                                                            unsigned long long* __restrict__ cnt) {
-  __shared__ uint64_t s_stage[kList ? kThetaCap : 1];
-  constexpr int kLoads = kThetaRows / kWave;
-  const int lane = lane_id();
-  const int64_t lo = (int64_t)blockIdx.x * kThetaRows;
-  const int64_t hi = (lo + kThetaRows) < n ? lo + kThetaRows : n;
-  T v[kLoads];
+// The block sums of ||x_c||_1 for up to 64 columns, the signal checks and the
+// count of non-zero cells.  One workgroup per (row block, 64 columns): each of
+// its 16 waves takes 256 of the 4096 rows, its lanes as many rows at a time as
+// there are whole rows of 2^lw columns (the smallest power of two that holds
+// them) in 64 lanes, so narrow signals load full lines too.  The partial sums
+// of the lanes and waves are added in any order where that is provably the
+// sequential sum (see wave_exact_sum; every one-hot or uniform signal, and 99
+// of 100 normal columns per block); a block with a column without proof is
+// staged through LDS in row order and added by a lane per column.  Bound: HBM
+// for large signals (128 normal columns of 2.4M nodes 0.71 ms, where one wave
+// per block and 64 columns took 0.48; 22 half-zero columns of 200003 nodes
+// 0.11, 0.38 so); for small ones the
+// chain of loads, which one wave per block with 32 rows in flight made 0.36 ms
+// long, and the listing pass after it 0.52 (nine one-hot columns of 30011
+// nodes, now 0.014 and 0.007).
+template <typename T>
+__global__ __launch_bounds__(kThetaWaves* kWave) void k_theta_partial(const T* __restrict__ x, long long ldx,
+                                                                      int64_t n, int C, int lw,
+                                                                      double* __restrict__ partial,
+                                                                      int* __restrict__ flags,
+                                                                      unsigned long long* __restrict__ cnt) {
+  __shared__ double s_sum[kThetaWaves][kWave];
+  __shared__ int s_low[kThetaWaves][kWave];
+  __shared__ unsigned int s_nnz[kThetaWaves];
+  __shared__ int s_flags[kThetaWaves];
+  __shared__ int s_redo;
+  constexpr int kThetaStage = 65536 / sizeof(T);  // values of a staged chunk
+  __shared__ T s_x[kThetaStage];
+  constexpr int kRows = kThetaRows / kThetaWaves;  // rows of a wave
+  const int lane = lane_id(), wave = threadIdx.x / kWave;
+  const int width = 1 << lw;                       // lanes per row
+  const int c = static_cast<int>(blockIdx.y) * kWave + (lane & (width - 1));
+  const int rstep = kWave >> lw;                   // rows per load
+  const bool live = c < C;
+  const int64_t lo = static_cast<int64_t>(blockIdx.x) * kThetaRows;
+  const int64_t hi = lo + kThetaRows < n ? lo + kThetaRows : n;
+  const int64_t r0 = lo + static_cast<int64_t>(wave) * kRows;
+  double sum = 0.0;
+  int low = INT_MAX, f = 0;
+  unsigned int nnz = 0;
+  for (int k0 = 0; k0 < kRows; k0 += kThetaLoads * rstep) {
+    T v[kThetaLoads];
 #pragma unroll
-  for (int k = 0; k < kLoads; ++k) {
-    const int64_t i = lo + k * kWave + lane;
-    v[k] = i < hi ? x[static_cast<size_t>(i) * static_cast<size_t>(ldx)] : T(0);  // +0 past the end
-  }
-  double s = 0.0;
-  int m = INT_MAX;
-  int f = 0;
-  int staged = 0;  // wave-uniform
-#pragma unroll
-  for (int k = 0; k < kLoads; ++k) {
-    if (!isfinite(static_cast<double>(v[k]))) f |= 1;
-    if (v[k] < T(0)) f |= 2;
-    const double a = fabs(static_cast<double>(v[k]));
-    s = s + a;
-    if (a != 0.0) {
-      const int e = low_exp(a);
-      m = e < m ? e : m;
+    for (int k = 0; k < kThetaLoads; ++k) {
+      const int kr = k0 + k * rstep + (lane >> lw);
+      const int64_t r = r0 + kr;
+      v[k] = (live && kr < kRows && r < hi) ? x[static_cast<size_t>(r) * static_cast<size_t>(ldx) + c] : T(0);
     }
-    if constexpr (kList)
-      stage_push<kThetaCap>(s_stage, staged, static_cast<uint64_t>(lo + k * kWave + lane) << 32, v[k] != T(0), F,
-                            cnt);
-    else
-      staged += __popcll(__ballot(v[k] != T(0)));
-  }
-  double sum;
-  if (!wave_exact_sum(s, m, sum)) {
-    sum = 0.0;
 #pragma unroll
-    for (int k = 0; k < kLoads; ++k) sum = add_lanes_in_order(sum, fabs(static_cast<double>(v[k])));
+    for (int k = 0; k < kThetaLoads; ++k) {
+      if (!isfinite(static_cast<double>(v[k]))) f |= 1;
+      if (v[k] < T(0)) f |= 2;
+      const double a = fabs(static_cast<double>(v[k]));
+      sum = sum + a;
+      if (a != 0.0) {
+        const int e = low_exp(a);
+        low = e < low ? e : low;
+        ++nnz;
+      }
+    }
   }
-  if constexpr (kList)
-    stage_flush(s_stage, staged, F, cnt);
-  else if (staged > 0 && lane == 0)
-    atomicAdd(cnt, static_cast<unsigned long long>(staged));
-  if (lane == 0) partial[blockIdx.x] = sum;
-  if (f) atomicOr(flags, f);
+  for (int off = width; off < kWave; off <<= 1) {  // the lanes of one column
+    sum = sum + __shfl_xor(sum, off);
+    const int o = __shfl_xor(low, off);
+    low = o < low ? o : low;
+  }
+  nnz = wave_sum_all(nnz);
+  f = (__any(f & 1) ? 1 : 0) | (__any(f & 2) ? 2 : 0);
+  s_sum[wave][lane] = sum;
+  s_low[wave][lane] = low;
+  if (lane == 0) {
+    s_nnz[wave] = nnz;
+    s_flags[wave] = f;
+  }
+  __syncthreads();
+  const bool own = live && wave == 0 && lane < width;  // one lane per column
+  double total = 0.0;
+  if (wave == 0) {
+    int m = INT_MAX;
+    for (int w = 0; w < kThetaWaves; ++w) {
+      total = total + s_sum[w][lane];
+      m = s_low[w][lane] < m ? s_low[w][lane] : m;
+    }
+    const bool exact = m == INT_MAX ? total == 0.0 : total < ldexp(1.0, m + 53);
+    const bool redo = __any(own && !exact);
+    if (redo) total = 0.0;
+    if (lane == 0) s_redo = redo ? 1 : 0;
+  }
+  __syncthreads();
+  if (s_redo) {  // in row order: the workgroup stages rows in LDS, a lane adds its column
+    constexpr int kPer = kThetaStage / (kThetaWaves * kWave);  // values per thread and chunk
+    const int rows = kThetaStage >> lw;                        // rows per chunk (at least 64, at most 4096)
+    const int tr = static_cast<int>(threadIdx.x) >> lw, trstep = (kThetaWaves * kWave) >> lw;
+    const int tc = static_cast<int>(blockIdx.y) * kWave + (threadIdx.x & (width - 1));
+    auto load = [&](int64_t r1, T* v) {
+#pragma unroll
+      for (int k = 0; k < kPer; ++k) {
+        const int64_t r = r1 + tr + k * trstep;
+        v[k] = (tc < C && r < hi) ? x[static_cast<size_t>(r) * static_cast<size_t>(ldx) + tc] : T(0);
+      }
+    };
+    T v[kPer];
+    load(lo, v);
+    for (int64_t r1 = lo; r1 < hi; r1 += rows) {
+#pragma unroll
+      for (int k = 0; k < kPer; ++k) s_x[k * kThetaWaves * kWave + threadIdx.x] = v[k];
+      __syncthreads();
+      if (r1 + rows < hi) load(r1 + rows, v);  // the next chunk's loads overlap this one's sum
+      if (own) {
+        const int nr = static_cast<int>(hi - r1 < rows ? hi - r1 : rows);
+#pragma unroll 16
+        for (int r = 0; r < nr; ++r) total = total + fabs(static_cast<double>(s_x[(r << lw) + lane]));
+      }
+      __syncthreads();
+    }
+  }
+  if (own) partial[static_cast<size_t>(blockIdx.x) * C + c] = total;
+  if (threadIdx.x == 0) {
+    unsigned int all = 0;
+    int fl = 0;
+    for (int w = 0; w < kThetaWaves; ++w) {
+      all += s_nnz[w];
+      fl |= s_flags[w];
+    }
+    if (all) atomicAdd(cnt, static_cast<unsigned long long>(all));
+    if (fl & ~__hip_atomic_load(flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicOr(flags, fl);
+  }
 }
+
+// A non-zero cell of the signal (rows ldx apart; cell = u * C + c).
+template <typename T>
+struct NonZeroX {
+  const T* x;
+  long long ldx;
+  int C;
+  __device__ bool operator()(int64_t, int64_t, size_t cell) const {
+    if (ldx == C) return x[cell] != T(0);
+    const size_t u = cell / static_cast<size_t>(C);
+    return x[u * static_cast<size_t>(ldx) + (cell - u * static_cast<size_t>(C))] != T(0);
+  }
+};
 
 // The same sums as k_theta_partial without forming a frontier; counts the
 // non-zero entries of x instead (their share decides the dense path).
@@ -356,6 +400,12 @@ __global__ __launch_bounds__(kWave) void k_fold_counts(const unsigned long long*
 // ------------------------------------------------------------ driver
 constexpr int kSparseShift = 5;  // sparse levels: frontier below n C / 32
 constexpr int kBinShift = 3;     // binned levels: estimated pushes reach n C / 8
+// and at least 2^23: the record passes are eight launches, about 0.1 ms however
+// few the records, while plain atomics add 1.8e10 pushes a second (levels of 60
+// to 300 thousand nodes x 22 to 64 columns: 16.7M pushes 1.13 ms with atomics and
+// 1.01 with records, 9M pushes 0.87 and 0.86 to 1.06, 4.4M pushes 0.67 and
+// 0.81, 1M pushes 0.46 and 0.55)
+constexpr double kMinBinPushes = 8388608.0;
 
 agp_tuning_t default_tuning() {
   agp_tuning_t t{};
@@ -504,13 +554,12 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
   // non-zero cells of x; when at least half of the cells are non-zero,
   // level 0 visits every cell in order (skipping the zeros), else a second
   // pass lists the non-zero cells
-  const dim3 tgrid((unsigned)std::max<int64_t>(tblocks, 1), (unsigned)((C + 63) / 64));
-  if (tblocks > 0 && C == 1)
-    k_theta_partial_c1<T, false><<<tgrid, kWave, 0, s>>>(x, ldc, n, sc.partial.as<double>(), flags + 1, nullptr,
-                                                         counts);
-  else if (tblocks > 0)
-    k_theta_partial<T, kThetaCap, false><<<tgrid, kWave, 0, s>>>(x, ldc, n, C, sc.partial.as<double>(), flags + 1,
-                                                                 nullptr, counts);
+  if (tblocks > 0) {
+    int lw = 0;
+    while ((1 << lw) < std::min(C, kWave)) ++lw;
+    k_theta_partial<T><<<dim3((unsigned)tblocks, (unsigned)((C + kWave - 1) / kWave)), kThetaWaves * kWave, 0, s>>>(
+        x, ldc, n, C, lw, sc.partial.as<double>(), flags + 1, counts);
+  }
   // flags[2..3]: the count of non-zero cells of x
   k_theta_final<T><<<grid_for(C, 64), 64, 0, s>>>(sc.partial.as<double>(), tblocks, C, eps,
                                                   qids ? dq : nullptr, qid_base, cp, counts,
@@ -522,18 +571,19 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
   unsigned long long nnz_x = 0;
   std::memcpy(&nnz_x, hflags + 2, sizeof(nnz_x));
   if (hflags[1] & 1) return fail(AGP_EINVAL, std::string(fn) + ": x holds a non-finite value");
+  // compaction: 32 KiB of LDS per block (five per CU); segments of 2^10 to
+  // 2^16 cells per wave, as large as leaves about 4096 of them
+  long long cseg = kCompactUnroll * kWave;
+  while (cseg < kCompactSeg && cseg * 4096 < static_cast<long long>(cells)) cseg <<= 1;
+  const unsigned cgrid = grid_for(static_cast<int64_t>((cells + cseg - 1) / cseg), kThreads / kWave, 1280);
   const bool virtual0 = nnz_x > 0 && 2 * nnz_x >= static_cast<unsigned long long>(cells) &&
                         static_cast<long long>(C) <= kVirtualMaxC;
   if (virtual0) {
     k_set_u64<<<1, 1, 0, s>>>(counts, static_cast<unsigned long long>(cells));  // the level-0 entries
   } else if (tblocks > 0) {
-    AGP_HIP(hipMemsetAsync(counts, 0, sizeof(unsigned long long), s));
-    if (C == 1)
-      k_theta_partial_c1<T, true><<<tgrid, kWave, 0, s>>>(x, ldc, n, sc.partial.as<double>(), flags + 1,
-                                                          sc.frontier[0].as<uint64_t>(), counts);
-    else
-      k_theta_partial<T, kThetaCap, true><<<tgrid, kWave, 0, s>>>(x, ldc, n, C, sc.partial.as<double>(), flags + 1,
-                                                                  sc.frontier[0].as<uint64_t>(), counts);
+    k_set_u64<<<1, 1, 0, s>>>(counts, 0ull);
+    k_compact<<<cgrid, kThreads, 0, s>>>(NonZeroX<T>{x, ldc, C}, n, C, cseg, sc.frontier[0].as<uint64_t>(), counts,
+                                         nullptr);
     AGP_HIP(hipGetLastError());
   }
   const bool positive = sizeof(T) == 4 && !(hflags[1] & 2);
@@ -555,6 +605,13 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
   while (shift < 32 && (gcells > 0 ? gcells - 1ull : 0ull) >> shift >= nbk) ++shift;
   const long long nbins = static_cast<long long>(((gcells > 0 ? gcells : 1) - 1) >> kBinLog2) + 1;  // per group
   unsigned long long rec_cap = 0;  // per group
+  // auto: no level can reach the record passes' cut when the call's pushes per
+  // level stay below it, at most one per arc and column, and for the
+  // column-stochastic a = 0, b = 1 about 1 / eps per column (||r||_1 <=
+  // ||x||_1 = theta / eps): then neither the estimate nor the passes run
+  const double level_pushes = static_cast<double>(C) *
+      std::min(static_cast<double>(g->nnz), a == 0.0 && b == 1.0 ? 1.0 / eps : HUGE_VAL);
+  if (tune.aggregation == 2 && level_pushes < kMinBinPushes) binned = false;
   if (binned) {
     // room for 4 records per cell (1 when the call runs in several tiles,
     // whose width left room for that), within 80% of the free memory (two
@@ -603,11 +660,6 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
   if (stats && (rc = sc.ensure_events())) return rc;
   uint64_t* F[2] = {sc.frontier[0].as<uint64_t>(), sc.frontier[1].as<uint64_t>()};
   Cell* acc[2] = {sc.acc[0].as<Cell>(), sc.acc[1].as<Cell>()};
-  // compaction: 32 KiB of LDS per block (five per CU); segments of 2^10 to
-  // 2^16 cells per wave, as large as leaves about 4096 of them
-  long long cseg = kCompactUnroll * kWave;
-  while (cseg < kCompactSeg && cseg * 4096 < static_cast<long long>(cells)) cseg <<= 1;
-  const unsigned cgrid = grid_for(static_cast<int64_t>((cells + cseg - 1) / cseg), kThreads / kWave, 1280);
 
   // rows with long deterministic prefixes, deferred per level to k_det_big
   constexpr unsigned long long kBigCap = 1ull << 18;
@@ -635,6 +687,15 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
   } else {
     (void)hipGetLastError();  // no room for the list: every row stays with its wave
   }
+  // no list (and no launch for it) where no entry of this call can reach it:
+  // a batch holds at most cells / kResidentWaves entries
+  const unsigned long long max_eb = std::min<unsigned long long>(kBatch, (cells + kResidentWaves - 1) / kResidentWaves);
+  const unsigned long long dmax = static_cast<unsigned long long>(g->max_degree);
+  const unsigned long long wmax = (dmax + kSeg - 1) / kSeg + 1;  // windows, and so items, of one suffix
+  if (dmax < static_cast<unsigned long long>(tune.big_row) && (dmax < kBatchDetRow || max_eb * dmax <= kBatchDet))
+    big_ctr = nullptr;
+  if (wmax < static_cast<unsigned long long>(tune.big_items) && (wmax < kBatchItemRow || max_eb * wmax <= kBatchItems))
+    samp_ctr = nullptr;
 
   LevelArgs A{};
   A.rp = g->row_ptr;
@@ -668,7 +729,8 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
   // auto: bin levels with n C / 2^k estimated pushes; with two column groups
   // from twice that (on 32-column tiles of a 111M-node graph the record
   // passes cost more than the atomics they replace below about n C / 4)
-  A.bin_pushes = std::ldexp(static_cast<double>(cells), -(ng > 1 ? std::max(tune.bin_shift - 1, 1) : tune.bin_shift));
+  A.bin_pushes = std::max(kMinBinPushes, std::ldexp(static_cast<double>(cells),
+                                                    -(ng > 1 ? std::max(tune.bin_shift - 1, 1) : tune.bin_shift)));
   // per node: d_u^-b and the first neighbour's d^-a, so that a batch setup
   // loads both with the row bounds (kept for later calls with the same a, b)
   A.nodefac = nullptr;
@@ -723,6 +785,15 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
   }
   AGP_HIP(hipMemcpyAsync(lpd, lph, sizeof(LevelParams) * (L + 1), hipMemcpyHostToDevice, s));
 
+  // workgroups of the level kernel: as many as its batches at the most
+  // (batches of 64 entries, on calls of at most kFewEntries cells
+  // kResidentWaves of them)
+  const unsigned long long max_batches =
+      cells > kFewEntries ? (cells + kBatch - 1) / kBatch : std::min<unsigned long long>(cells, kResidentWaves);
+  constexpr unsigned long long kWavesPerBlock = kThreads / kWave;
+  const int level_blocks = static_cast<int>(std::max<unsigned long long>(
+      1, std::min<unsigned long long>(tune.level_blocks, (max_batches + kWavesPerBlock - 1) / kWavesPerBlock)));
+
   // the level loop: every decision stays on the device, so it can be
   // captured once and replayed (timed per level only when launched directly)
   auto levels = [&](hipStream_t s, bool timed) {
@@ -758,9 +829,9 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
       if (timed) (void)hipEventRecord(ev[4 * i + 1], s);
       const bool grouped = sizeof(T) == 4 && bin_level && ng > 1;  // records in two column groups
       if (a == 0.0)
-        launch_level<T, kBatchAZ>(A, tune.level_blocks, i == 0, grouped, x, cur, nxt, s);
+        launch_level<T, kBatchAZ>(A, level_blocks, i == 0, grouped, x, cur, nxt, s);
       else
-        launch_level<T, kBatchAP>(A, tune.level_blocks, i == 0, grouped, x, cur, nxt, s);
+        launch_level<T, kBatchAP>(A, level_blocks, i == 0, grouped, x, cur, nxt, s);
       if (timed) (void)hipEventRecord(ev[4 * i + 2], s);
       if (bin_level) {
         uint32_t* r0 = sc.rec[0].as<uint32_t>();
@@ -807,8 +878,8 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
         static_cast<void*>(F[0]), static_cast<void*>(F[1]), static_cast<void*>(counts), static_cast<void*>(counters),
         static_cast<void*>(sc.levelinfo.ptr), static_cast<void*>(flags), static_cast<const void*>(da),
         static_cast<const void*>(db), static_cast<void*>(sc.rec[0].ptr), static_cast<void*>(sc.bins.ptr),
-        positive ? 1 : 0, binned ? ng : 0, rec_cap, shift, big_cap, big_ctr != nullptr ? 1 : 0, tune.aggregation,
-        tune.level_blocks, tune.big_row, tune.big_items, (tune.sparse_shift << 8) | tune.bin_shift);
+        positive ? 1 : 0, binned ? ng : 0, rec_cap, shift, big_cap,
+        (big_ctr != nullptr ? 1 : 0) | (samp_ctr != nullptr ? 2 : 0), tune.aggregation, level_blocks, tune.big_row, tune.big_items, (tune.sparse_shift << 8) | tune.bin_shift);
     std::string k(key, kn > 0 ? static_cast<size_t>(kn) : 0);
     k.push_back(virtual0 ? 'v' : 'l');  // level 0 over every cell or over the listed ones
     k.append(reinterpret_cast<const char*>(&big_rows), sizeof(big_rows));
