@@ -52,6 +52,10 @@ constexpr int kNumCounters = 6;   // frontier, hash, det, cand, acc, runs
 constexpr int kCountShards = 64;
 constexpr int kCountStride = 8;   // words of a row
 constexpr int kCountMass = 6;     // the mass (binary64) after the counters
+// The server keeps the same rows per slot (counters accumulate over a
+// query's levels; word 7 stays free for its error flags): kServeShards sets
+// of one row per slot, block b adding to set b mod kServeShards.
+constexpr int kServeShards = 16;
 constexpr size_t kCountLevelBytes = sizeof(unsigned long long) * kCountShards * kCountStride;
 constexpr int kThetaRows = 4096;  // rows per partial sum of ||x||_1
 constexpr int kServeLdsSlots = 128;  // server columns whose counters a block sums in LDS
@@ -171,8 +175,8 @@ struct LevelArgs {
   const unsigned long long* cnt_in;
   uint64_t* fout;
   unsigned long long* cnt_out;
-  unsigned long long* counters;  // batched: per level and shard (kCountShards rows); server: per column
-  double* mass;                  // server: per column (batched: in the counter rows)
+  unsigned long long* counters;  // batched: per level and shard (kCountShards rows); server: per shard and slot
+  int slots;                     // server: rows per shard
   int* err;                      // batched: one flag; server: one per column
   int positive;                  // non-negative signals: sparse levels allowed
   unsigned long long dense_cut;  // frontier size from which a level is dense
@@ -503,14 +507,42 @@ __device__ __forceinline__ void mark_det_bin(const LevelArgs& A, uint8_t* det_bi
   det_bins[rc.g * A.det_bins_g + (rc.cell >> kBinLog2)] = 1;
 }
 
-// Server counters: LDS sums for the first kServeLdsSlots columns, global
-// atomics beyond.
-__device__ __forceinline__ void serve_count(const LevelArgs& A, unsigned long long (*lds)[kNumCounters],
-                                            uint32_t c, int k, unsigned long long v) {
-  if (c < kServeLdsSlots)
-    atomicAdd(&lds[c][k], v);
-  else
-    atomicAdd(A.counters + static_cast<size_t>(c) * kNumCounters + k, v);
+// Server counters: LDS sums for the first kServeLdsSlots columns (one block's
+// share of a step), atomics on the block's row of the column beyond.
+struct ServeSums {
+  uint32_t front, cand, acc, runs;
+  unsigned long long det;
+  double mass;
+};
+__device__ __forceinline__ unsigned long long* serve_row(const LevelArgs& A, uint32_t c) {
+  return A.counters + (static_cast<size_t>(blockIdx.x & (kServeShards - 1)) * A.slots + c) * kCountStride;
+}
+__device__ __forceinline__ void serve_flush(unsigned long long* row, const ServeSums& v) {
+  if (v.front) atomic_add_relaxed(row + 0, v.front);
+  if (v.det) atomic_add_relaxed(row + 2, v.det);
+  if (v.cand) atomic_add_relaxed(row + 3, v.cand);
+  if (v.acc) atomic_add_relaxed(row + 4, v.acc);
+  if (v.runs) atomic_add_relaxed(row + 5, v.runs);
+  if (v.mass != 0.0) atomicAdd(reinterpret_cast<double*>(row + kCountMass), v.mass);
+}
+__device__ __forceinline__ void serve_entry(const LevelArgs& A, ServeSums* lds, uint32_t c, uint32_t det, double mass) {
+  if (c < kServeLdsSlots) {
+    atomicAdd(&lds[c].front, 1u);
+    if (det) atomicAdd(&lds[c].det, static_cast<unsigned long long>(det));
+    if (mass != 0.0) atomicAdd(&lds[c].mass, mass);
+  } else {
+    serve_flush(serve_row(A, c), ServeSums{1u, 0u, 0u, 0u, det, mass});
+  }
+}
+__device__ __forceinline__ void serve_item(const LevelArgs& A, ServeSums* lds, uint32_t c, uint32_t cand, uint32_t acc,
+                                           uint32_t runs) {
+  if (c < kServeLdsSlots) {
+    if (cand) atomicAdd(&lds[c].cand, cand);
+    if (acc) atomicAdd(&lds[c].acc, acc);
+    if (runs) atomicAdd(&lds[c].runs, runs);
+  } else {
+    serve_flush(serve_row(A, c), ServeSums{0u, cand, acc, runs, 0ull, 0.0});
+  }
 }
 
 // The block's counter row of the level (batched calls).
@@ -835,10 +867,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
   constexpr int kWaves = kThreads / kWave;
   __shared__ BatchLds s_batch[kWaves];
   __shared__ uint64_t s_stage[kWaves][kStage];
-  __shared__ unsigned int s_hist[kBuckets];
+  __shared__ unsigned int s_hist[kServe ? 1 : kBuckets];
   // server: per-column counters summed in LDS, flushed once per block
-  __shared__ unsigned long long s_scnt[kServe ? kServeLdsSlots : 1][kNumCounters];
-  __shared__ double s_smass[kServe ? kServeLdsSlots : 1];
+  __shared__ ServeSums s_serve[kServe ? kServeLdsSlots : 1];
 
   const unsigned long long count = *A.cnt_in;
   // Binned levels write (cell, value) records that later kernels group by
@@ -850,13 +881,23 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
   const bool sparse = kServe || (!binned && A.positive && count < A.dense_cut);
   if (blockIdx.x == 0 && threadIdx.x == 0)
     *A.mode_out = binned ? kModeBinned : (sparse ? kModeSparse : kModeCompact);
+  // up to 64 entries per batch; fewer when the level has fewer entries than
+  // 64 per resident wave, so that small frontiers spread over the whole chip
+  // (but no wider: spread over four generations of waves, a level of 10^5
+  // entries paid four times for the setup's chain of loads with a third of
+  // the lanes busy; nine queries on a 30011-node graph: 4.07 -> 1.95 ms)
+  const unsigned long long nwaves = static_cast<unsigned long long>(gridDim.x) * kWaves;
+  const unsigned long long want = (count + kResidentWaves - 1) / kResidentWaves;
+  const unsigned long long eb = want < 1ull ? 1ull : (want > (unsigned long long)kBatch ? kBatch : want);
+  const bool few = count <= kFewEntries;
+  const unsigned long long nbatch = (count + eb - 1) / eb;
+  if (static_cast<unsigned long long>(blockIdx.x) * kWaves >= nbatch) return;  // the whole block: no batch
   if (binned) {
     for (int i = threadIdx.x; i < kBuckets; i += blockDim.x) s_hist[i] = 0;
     __syncthreads();
   }
   if (kServe) {
-    for (int i = threadIdx.x; i < kServeLdsSlots * kNumCounters; i += blockDim.x) (&s_scnt[0][0])[i] = 0;
-    for (int i = threadIdx.x; i < kServeLdsSlots; i += blockDim.x) s_smass[i] = 0.0;
+    for (int i = threadIdx.x; i < kServeLdsSlots; i += blockDim.x) s_serve[i] = ServeSums{};
     __syncthreads();
   }
   const int lane = lane_id();
@@ -917,16 +958,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
     }
   };
 
-  // up to 64 entries per batch; fewer when the level has fewer entries than
-  // 64 per resident wave, so that small frontiers spread over the whole chip
-  // (but no wider: spread over four generations of waves, a level of 10^5
-  // entries paid four times for the setup's chain of loads with a third of
-  // the lanes busy; nine queries on a 30011-node graph: 4.07 -> 1.95 ms)
-  const unsigned long long nwaves = static_cast<unsigned long long>(gridDim.x) * kWaves;
-  const unsigned long long want = (count + kResidentWaves - 1) / kResidentWaves;
-  const unsigned long long eb = want < 1ull ? 1ull : (want > (unsigned long long)kBatch ? kBatch : want);
-  const bool few = count <= kFewEntries;
-  const unsigned long long nbatch = (count + eb - 1) / eb;
   unsigned long long bnext = static_cast<unsigned long long>(blockIdx.x) * kWaves + wave;
   // the frontier items of this wave's next batch, loaded one batch ahead so
   // that a batch's setup starts from its items
@@ -962,7 +993,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
     int64_t erp = 0;
     double ecv = 0.0, ep0 = 0.0;
     bool eneg = false;
-    bool front_live = false;
+    bool front_live = false, serve_live = false;
+    double emass = 0.0;  // server: the entry's share of its column's mass
     if (lane < ne) {
       const uint64_t item = batch_item;
       eu = static_cast<uint32_t>(item >> 32);
@@ -1030,7 +1062,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
       B.ctr3[lane] = (cp.qid << 8) | static_cast<uint32_t>(kServe ? cp.level : A.level);
           if (live) {
         if (kServe) {
-          serve_count(A, s_scnt, ec, 0, 1ull);
+          serve_live = true;
         } else {
           front_live = true;
           n_hash += splitmix64(eu);
@@ -1086,11 +1118,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
             const T big = to_w(inc0 > eth ? inc0 : eth, T());
             const double m = static_cast<double>(ed) * P::mag_units(big, cp);
             if (kServe) {
-              serve_count(A, s_scnt, ec, 2, static_cast<unsigned long long>(eJ));
-              if (ec < kServeLdsSlots)
-                atomicAdd(&s_smass[ec], m);
-              else
-                atomicAdd(A.mass + ec, m);
+              emass = m;
             } else {
               n_det += eJ;
               mass += m;
@@ -1100,6 +1128,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
       }
     }
     if (!kServe) w_front += static_cast<uint32_t>(__popcll(__ballot(front_live)));
+    if (kServe && serve_live) serve_entry(A, s_serve, ec, eJ, emass);
     // long deterministic prefixes and entries with many work items leave for
     // the deferred lists
     if (!kServe && A.big_ctr != nullptr && __any(eJ >= kBatchDetRow || eJ >= A.big_row)) {
@@ -1187,23 +1216,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
     return true;
   };
   auto served = [&](uint32_t c, uint32_t cand, uint32_t acc, uint32_t runs) {
-    if (cand) {
-      serve_count(A, s_scnt, c, 3, static_cast<unsigned long long>(cand));
-      if (acc) serve_count(A, s_scnt, c, 4, static_cast<unsigned long long>(acc));
-    }
-    if (runs) serve_count(A, s_scnt, c, 5, static_cast<unsigned long long>(runs));
+    if (kServe) serve_item(A, s_serve, c, cand, acc, runs);
   };
   sample_loop<kMode>(A, B, refill, emit_sampled, served, w_cand, w_acc, w_runs);
   if (sparse) stage_flush(stage, staged, A.fout, A.cnt_out);
   if (binned) finish_records<kG>(A, s_hist, reinterpret_cast<uint32_t*>(stage), staged, acc_next);
   if (kServe) {  // flush the block's per-column sums
     __syncthreads();
-    for (int i = threadIdx.x; i < kServeLdsSlots * kNumCounters; i += blockDim.x) {
-      const unsigned long long cv2 = (&s_scnt[0][0])[i];
-      if (cv2) atomicAdd(A.counters + i, cv2);
-    }
-    for (int i = threadIdx.x; i < kServeLdsSlots; i += blockDim.x)
-      if (s_smass[i] != 0.0) atomicAdd(A.mass + i, s_smass[i]);
+    for (int i = threadIdx.x; i < kServeLdsSlots && i < A.slots; i += blockDim.x) serve_flush(serve_row(A, i), s_serve[i]);
   }
   if (!kServe) {  // per-level counters: the block's sums, one row of atomics
     const unsigned long long v1 = wave_sum_u64(n_hash);

@@ -56,13 +56,14 @@ using srv::AdmitItem;
 __global__ void k_admit(const AdmitItem* __restrict__ items, int k, uint32_t* __restrict__ keys,
                         long long* __restrict__ vals, const uint32_t* __restrict__ tab_off,
                         const uint32_t* __restrict__ tab_mask, uint64_t* __restrict__ F,
-                        unsigned long long* __restrict__ cnt, unsigned long long* __restrict__ counters,
-                        double* __restrict__ mass, int* __restrict__ err) {
+                        unsigned long long* __restrict__ cnt, unsigned long long* __restrict__ counters, int slots,
+                        int* __restrict__ err) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= k) return;
   const AdmitItem it = items[i];
-  for (int j = 0; j < kNumCounters; ++j) counters[static_cast<size_t>(it.slot) * kNumCounters + j] = 0;
-  mass[it.slot] = 0.0;
+  for (int sh = 0; sh < kServeShards; ++sh)  // (a mass of +0.0 is all zero bits)
+    for (int j = 0; j < kCountStride; ++j)
+      counters[(static_cast<size_t>(sh) * slots + it.slot) * kCountStride + j] = 0;
   bool first = false;
   const uint32_t mask = tab_mask[it.slot];
   const uint32_t pos = mask == kDirectPlain ? tab_off[it.slot] + it.node
@@ -80,29 +81,73 @@ __global__ void k_zero_count(unsigned long long* c) { *c = 0; }
 
 // The next frontier of the queries with plain direct tables: the non-zero
 // positions of their next tables (row y of the grid scans table t[y]; the
-// other queries append first touches in the level kernel).
+// other queries append first touches in the level kernel).  A block takes
+// kScanCells positions, 32 loads per lane, and appends its non-zero ones with
+// one atomic: every append is a round trip to one address that serialises at
+// about 10 ns, and with one per wave and 512 entries a scan of 32 tables of
+// 2^18 nodes took 0.25 ms, now XXX (its 67 MB at the rate of a copy: 0.013).
+constexpr int kScanLoads = 32;
+constexpr int kScanCells = kThreads * kScanLoads;
 __global__ __launch_bounds__(kThreads) void k_scan_plain(const srv::PlainTable* __restrict__ t, int64_t n,
                                                          const long long* __restrict__ vals, uint64_t* __restrict__ F,
                                                          unsigned long long* __restrict__ cnt) {
-  __shared__ uint64_t s_stage[kThreads / kWave][kStage];
-  uint64_t* stage = s_stage[threadIdx.x / kWave];
-  int staged = 0;
+  constexpr int kWaves = kThreads / kWave;
+  __shared__ unsigned int s_count[kWaves];
+  __shared__ unsigned long long s_base;
+  const int lane = lane_id(), wave = threadIdx.x / kWave;
+  const unsigned long long lt_mask = (1ull << lane) - 1ull;
   const srv::PlainTable pt = t[blockIdx.y];
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-  const int64_t first = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  const int64_t iters = (n + stride - 1) / stride;  // the same for every wave (wave-wide staging)
-  for (int64_t it = 0; it < iters; ++it) {
-    const int64_t v = first + it * stride;
-    bool p = false;
-    uint64_t item = 0;
-    if (v < n) {
-      const uint32_t pos = pt.off + static_cast<uint32_t>(v);
-      p = vals[pos] != 0;
-      item = (static_cast<uint64_t>(pos) << 32) | pt.slot;
-    }
-    stage_push(stage, staged, item, p, F, cnt);
+  const int64_t v0 = static_cast<int64_t>(blockIdx.x) * kScanCells + wave * (kScanLoads * kWave) + lane;
+  uint32_t hits = 0;  // bit k: position v0 + 64 k is non-zero
+  unsigned int mine = 0;
+#pragma unroll
+  for (int k = 0; k < kScanLoads; ++k) {
+    const int64_t v = v0 + k * kWave;
+    // the index is clamped instead of guarded, so that the loads go out together
+    const bool p = vals[pt.off + static_cast<uint32_t>(v < n ? v : n - 1)] != 0 && v < n;
+    hits |= (p ? 1u : 0u) << k;
+    mine += static_cast<unsigned int>(__popcll(__ballot(p)));
   }
-  stage_flush(stage, staged, F, cnt);
+  if (lane == 0) s_count[wave] = mine;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    unsigned int all = 0;
+    for (int w = 0; w < kWaves; ++w) all += s_count[w];
+    s_base = all ? atomicAdd(cnt, static_cast<unsigned long long>(all)) : 0ull;
+  }
+  __syncthreads();
+  unsigned long long at = s_base;
+  for (int w = 0; w < wave; ++w) at += s_count[w];
+  for (int k = 0; k < kScanLoads; ++k) {
+    const bool p = (hits >> k) & 1u;
+    const unsigned long long m = __ballot(p);
+    if (p)
+      F[at + __popcll(m & lt_mask)] =
+          (static_cast<uint64_t>(pt.off + static_cast<uint32_t>(v0 + k * kWave)) << 32) | pt.slot;
+    at += __popcll(m);
+  }
+}
+
+// Per slot the sums of its counter rows, and its error flags in word 7.
+__global__ void k_fold_slots(const unsigned long long* __restrict__ rows, const int* __restrict__ err, int slots,
+                             unsigned long long* __restrict__ out) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= slots * kCountStride) return;
+  const int k = i % kCountStride, c = i / kCountStride;
+  if (k == kCountMass) {
+    double m = 0.0;
+    for (int sh = 0; sh < kServeShards; ++sh)
+      m += reinterpret_cast<const double*>(rows)[static_cast<size_t>(sh) * slots * kCountStride + i];
+    out[i] = static_cast<unsigned long long>(__double_as_longlong(m));
+    return;
+  }
+  if (k == kCountStride - 1) {
+    out[i] = static_cast<unsigned long long>(static_cast<unsigned int>(err[c]));
+    return;
+  }
+  unsigned long long v = 0;
+  for (int sh = 0; sh < kServeShards; ++sh) v += rows[static_cast<size_t>(sh) * slots * kCountStride + i];
+  out[i] = v;
 }
 
 __global__ void k_clear_err(const AdmitItem* __restrict__ items, int k, int* __restrict__ err) {
@@ -149,7 +194,7 @@ struct agp_server {
   std::chrono::steady_clock::time_point t0;
   // device state: the table pool (keys and values of this step's and the
   // next step's tables, frontier lists of pool positions) and per-slot data
-  agp::DevBuf keys, vals, F[2], counts, counters, mass, err, cp, admit, mode, tabs;
+  agp::DevBuf keys, vals, F[2], counts, counters, sums, err, cp, admit, mode, tabs;
   int cur = 0;
   uint64_t pool_entries = 0;
   agp::srv::RangePool pool;  // guarded by mu
@@ -170,9 +215,7 @@ struct agp_server {
   agp::srv::PlainTable* h_plain = nullptr;  // this step's plain direct tables (pinned, S)
   agp::DevBuf plain;
   std::vector<agp::srv::AdmitItem> h_admit;  // the step's admissions (kept until the step syncs)
-  unsigned long long* h_counters = nullptr;
-  double* h_mass = nullptr;
-  int* h_err = nullptr;
+  unsigned long long* h_sums = nullptr;  // per slot: counters, mass, error flags (kCountStride words)
   int worker_error = AGP_OK;
 };
 
@@ -382,8 +425,8 @@ int step(agp_server* s) {
     k_clear_err<<<grid_for(nadmit, 64), 64, 0, st>>>(s->admit.as<srv::AdmitItem>(), nadmit, s->err.as<int>());
     k_admit<<<grid_for(nadmit, 64), 64, 0, st>>>(s->admit.as<srv::AdmitItem>(), nadmit, s->keys.as<uint32_t>(),
                                                   s->vals.as<long long>(), tab_off, tab_mask, F[cur],
-                                                  counts + cur, s->counters.as<unsigned long long>(),
-                                                  s->mass.as<double>(), s->err.as<int>());
+                                                  counts + cur, s->counters.as<unsigned long long>(), s->S,
+                                                  s->err.as<int>());
   }
   k_zero_count<<<1, 1, 0, st>>>(counts + nxt);
   LevelArgs A{};
@@ -402,7 +445,7 @@ int step(agp_server* s) {
   A.fout = F[nxt];
   A.cnt_out = counts + nxt;
   A.counters = s->counters.as<unsigned long long>();
-  A.mass = s->mass.as<double>();
+  A.slots = s->S;
   A.err = s->err.as<int>();
   A.positive = 0;
   A.dense_cut = ~0ull;
@@ -418,15 +461,15 @@ int step(agp_server* s) {
                                                                  s->vals.as<long long>());
   if (nplain > 0) {
     AGP_HIP(hipMemcpyAsync(s->plain.ptr, s->h_plain, sizeof(srv::PlainTable) * nplain, hipMemcpyHostToDevice, st));
-    const unsigned gx = std::max(1u, std::min(grid_for(s->n, kThreads, 65536), 8192u / static_cast<unsigned>(nplain)));
-    k_scan_plain<<<dim3(gx, static_cast<unsigned>(nplain)), kThreads, 0, st>>>(
+    k_scan_plain<<<dim3(static_cast<unsigned>((s->n + kScanCells - 1) / kScanCells), static_cast<unsigned>(nplain)),
+                   kThreads, 0, st>>>(
         s->plain.as<srv::PlainTable>(), s->n, s->vals.as<long long>(), F[nxt], counts + nxt);
   }
+  k_fold_slots<<<grid_for(static_cast<int64_t>(s->S) * kCountStride, 256), 256, 0, st>>>(
+      s->counters.as<unsigned long long>(), s->err.as<int>(), s->S, s->sums.as<unsigned long long>());
   AGP_HIP(hipGetLastError());
-  AGP_HIP(hipMemcpyAsync(s->h_counters, s->counters.ptr, sizeof(unsigned long long) * kNumCounters * s->S,
+  AGP_HIP(hipMemcpyAsync(s->h_sums, s->sums.ptr, sizeof(unsigned long long) * kCountStride * s->S,
                          hipMemcpyDeviceToHost, st));
-  AGP_HIP(hipMemcpyAsync(s->h_mass, s->mass.ptr, sizeof(double) * s->S, hipMemcpyDeviceToHost, st));
-  AGP_HIP(hipMemcpyAsync(s->h_err, s->err.ptr, sizeof(int) * s->S, hipMemcpyDeviceToHost, st));
   AGP_HIP(hipStreamSynchronize(st));
   s->cur = nxt;
   // retire
@@ -437,8 +480,12 @@ int step(agp_server* s) {
     const uint64_t t = s->slot_ticket[c];
     if (!t) continue;
     QueryRec& r = s->recs[t];
-    const bool full = (s->h_err[c] & kErrTableFull) != 0;
-    const bool overflow = (s->h_err[c] & ~kErrTableFull) != 0 || !(s->h_mass[c] < 0x1p61);
+    const unsigned long long* k = s->h_sums + static_cast<size_t>(c) * kCountStride;
+    const int err = static_cast<int>(k[kCountStride - 1]);
+    double mass;
+    std::memcpy(&mass, &k[kCountMass], sizeof(mass));
+    const bool full = (err & kErrTableFull) != 0;
+    const bool overflow = (err & ~kErrTableFull) != 0 || !(mass < 0x1p61);
     bool finish = false, requeue = false;
     if (r.restart) {
       requeue = true;  // its residues were dropped in this step: run it again with larger tables
@@ -467,7 +514,6 @@ int step(agp_server* s) {
       again.push_back(t);
     }
     if (finish) {
-      const unsigned long long* k = s->h_counters + static_cast<size_t>(c) * kNumCounters;
       r.res.status = r.failed ? AGP_ERANGE : AGP_OK;
       r.res.levels = r.q.L;
       r.res.frontier = k[0];
@@ -564,8 +610,9 @@ int agp_server_create(const agp_graph_t* g, const agp_server_config_t* cfg, agp_
         (rc = s->F[0].reserve(P / 2 * sizeof(uint64_t), false, s->stream)) ||
         (rc = s->F[1].reserve(P / 2 * sizeof(uint64_t), false, s->stream)) ||
         (rc = s->counts.reserve(2 * sizeof(unsigned long long), true, s->stream)) ||
-        (rc = s->counters.reserve(sizeof(unsigned long long) * lvl::kNumCounters * s->S, true, s->stream)) ||
-        (rc = s->mass.reserve(sizeof(double) * s->S, true, s->stream)) ||
+        (rc = s->counters.reserve(sizeof(unsigned long long) * lvl::kCountStride * lvl::kServeShards * s->S, true,
+                                  s->stream)) ||
+        (rc = s->sums.reserve(sizeof(unsigned long long) * lvl::kCountStride * s->S, true, s->stream)) ||
         (rc = s->err.reserve(sizeof(int) * s->S, true, s->stream)) ||
         (rc = s->cp.reserve(sizeof(ColParams) * s->S, false, s->stream)) ||
         (rc = s->admit.reserve(sizeof(srv::AdmitItem) * s->S, false, s->stream)) ||
@@ -578,10 +625,8 @@ int agp_server_create(const agp_graph_t* g, const agp_server_config_t* cfg, agp_
     if (hipHostMalloc(reinterpret_cast<void**>(&s->h_cp), sizeof(ColParams) * s->S) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void**>(&s->h_tabs), sizeof(uint32_t) * 3 * s->S) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void**>(&s->h_plain), sizeof(srv::PlainTable) * s->S) != hipSuccess ||
-        hipHostMalloc(reinterpret_cast<void**>(&s->h_counters),
-                      sizeof(unsigned long long) * lvl::kNumCounters * s->S) != hipSuccess ||
-        hipHostMalloc(reinterpret_cast<void**>(&s->h_mass), sizeof(double) * s->S) != hipSuccess ||
-        hipHostMalloc(reinterpret_cast<void**>(&s->h_err), sizeof(int) * s->S) != hipSuccess)
+        hipHostMalloc(reinterpret_cast<void**>(&s->h_sums),
+                      sizeof(unsigned long long) * lvl::kCountStride * s->S) != hipSuccess)
       rc = fail(AGP_ENOMEM, "agp_server_create: pinned host allocation failed");
   }
   if (!rc) {
@@ -687,15 +732,13 @@ int agp_server_destroy(agp_server_t* s) {
   }
   if (s->worker.joinable()) s->worker.join();
   if (s->stream) (void)hipStreamSynchronize(s->stream);
-  for (auto* b : {&s->keys, &s->vals, &s->F[0], &s->F[1], &s->counts, &s->counters, &s->mass, &s->err, &s->cp,
+  for (auto* b : {&s->keys, &s->vals, &s->F[0], &s->F[1], &s->counts, &s->counters, &s->sums, &s->err, &s->cp,
                   &s->admit, &s->mode, &s->tabs, &s->plain})
     b->release();
   if (s->h_cp) (void)hipHostFree(s->h_cp);
   if (s->h_tabs) (void)hipHostFree(s->h_tabs);
   if (s->h_plain) (void)hipHostFree(s->h_plain);
-  if (s->h_counters) (void)hipHostFree(s->h_counters);
-  if (s->h_mass) (void)hipHostFree(s->h_mass);
-  if (s->h_err) (void)hipHostFree(s->h_err);
+  if (s->h_sums) (void)hipHostFree(s->h_sums);
   if (s->stream) (void)hipStreamDestroy(s->stream);
   delete s;
   return AGP_OK;
