@@ -54,8 +54,10 @@ constexpr int kCountStride = 8;   // words of a row
 constexpr int kCountMass = 6;     // the mass (binary64) after the counters
 // The server keeps the same rows per slot (counters accumulate over a
 // query's levels; word 7 stays free for its error flags): kServeShards sets
-// of one row per slot, block b adding to set b mod kServeShards.
+// of one row per slot (one set from kServeShardSlots slots on, whose rows are
+// shared by fewer blocks), block b adding to set b mod kServeShards.
 constexpr int kServeShards = 16;
+constexpr int kServeShardSlots = 8192;
 constexpr size_t kCountLevelBytes = sizeof(unsigned long long) * kCountShards * kCountStride;
 constexpr int kThetaRows = 4096;  // rows per partial sum of ||x||_1
 constexpr int kServeLdsSlots = 128;  // server columns whose counters a block sums in LDS
@@ -80,7 +82,7 @@ constexpr int kMaxBinsPerBucket = 1024;
 constexpr int kBuckets = 1024;
 
 // Rows with many deterministic pushes (a hub with a large residue) would
-// keep one wave busy while the rest of the grid idles; a batched level
+// keep one wave busy while the rest of the grid idles; a level
 // defers rows of at least big_row (default kBigRow) deterministic pushes to a
 // list that k_det_big then spreads over the whole grid, and, when a batch
 // makes more than kBatchDet pushes in all (64 columns of one hub are one
@@ -94,7 +96,7 @@ struct BigRow {
   unsigned long long off;  // deterministic pushes of the rows deferred before this one
   int64_t rp;              // first arc of the row
   double cv;               // c = rho |r| d_u^-b
-  uint32_t c, J, neg, pad;
+  uint32_t c, J;           // c: with the flags of BatchLds
 };
 
 // Likewise an entry whose sampled suffix makes samp_items (64 by default)
@@ -177,6 +179,7 @@ struct LevelArgs {
   unsigned long long* cnt_out;
   unsigned long long* counters;  // batched: per level and shard (kCountShards rows); server: per shard and slot
   int slots;                     // server: rows per shard
+  int shard_mask;                // server: shards - 1 (a power of two of them)
   int* err;                      // batched: one flag; server: one per column
   int positive;                  // non-negative signals: sparse levels allowed
   unsigned long long dense_cut;  // frontier size from which a level is dense
@@ -193,7 +196,7 @@ struct LevelArgs {
   int bucket_shift;              // cells per bucket = 2^bucket_shift
   const double* bin_est;         // non-null: bin only if *bin_est >= bin_pushes (estimated pushes)
   double bin_pushes;
-  // deferred rows (batched calls; nullptr: every row is pushed by its wave)
+  // deferred rows (nullptr: every row is pushed by its wave)
   uint32_t big_row;              // deterministic pushes from which an entry's row is deferred
   unsigned long long* big_ctr;   // this level's list counter, zero at the start
   BigRow* big;
@@ -515,7 +518,7 @@ struct ServeSums {
   double mass;
 };
 __device__ __forceinline__ unsigned long long* serve_row(const LevelArgs& A, uint32_t c) {
-  return A.counters + (static_cast<size_t>(blockIdx.x & (kServeShards - 1)) * A.slots + c) * kCountStride;
+  return A.counters + (static_cast<size_t>(blockIdx.x & A.shard_mask) * A.slots + c) * kCountStride;
 }
 __device__ __forceinline__ void serve_flush(unsigned long long* row, const ServeSums& v) {
   if (v.front) atomic_add_relaxed(row + 0, v.front);
@@ -655,6 +658,45 @@ __device__ __forceinline__ int batch_find(const I* off, I k) {
   for (int step = kBatch / 2; step > 0; step >>= 1)
     if (off[e + step] <= k) e += step;
   return e;
+}
+
+// One push of every lane that emits (all lanes together), added to the
+// accumulators with atomics: on sparse levels the first contribution to a
+// cell appends it to the next frontier; a served query's push goes to its
+// table, first touches to the next frontier.
+template <typename T, int kMode>
+__device__ __forceinline__ void push_atomic(const LevelArgs& A, uint64_t* stage, int& staged, bool sparse, bool emit,
+                                            uint32_t v, uint32_t c, const typename Prec<T>::Delta& delta,
+                                            typename Prec<T>::Cell* acc_next) {
+  using P = Prec<T>;
+  bool first = false;
+  if constexpr (kMode == kPerColumn) {
+    uint32_t pos = 0;
+    if (emit) {
+      const uint32_t mask = A.tab_mask[c];
+      if (mask == kDirectPlain) {  // the next frontier comes from a scan of the table
+        pos = A.tab_off[c] + v;
+        P::add(acc_next, pos, delta);
+      } else {
+        pos = table_find_or_insert(A.keys_nxt, A.tab_off[c], mask, v, &first);
+        if (pos == ~0u)
+          atomicOr(A.err + c, kErrTableFull);
+        else
+          P::add(acc_next, pos, delta);
+      }
+    }
+    stage_push(stage, staged, (static_cast<uint64_t>(pos) << 32) | c, first, A.fout, A.cnt_out);
+  } else {
+    const size_t vcell = static_cast<size_t>(v) * A.su + static_cast<size_t>(c) * A.sc;
+    if (emit) {
+      if (sparse)
+        first = P::add_ret(acc_next, vcell, delta);
+      else
+        P::add(acc_next, vcell, delta);
+    }
+    if (sparse)  // stage first-touched cells, flush in chunks
+      stage_push(stage, staged, (static_cast<uint64_t>(v) << 32) | c, first, A.fout, A.cnt_out);
+  }
 }
 
 // Exclusive scans of the batch's work items into B.ioff, and the entry of each
@@ -919,34 +961,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
   // on every level); emit_sampled: a sampled push of -/+ fl(theta) (a
   // 4-byte record on binned levels).
   auto emit_atomic = [&](bool emit, uint32_t v, uint32_t ec, const Delta& delta) {
-    bool first = false;
-    if constexpr (kServe) {  // the query's table: first touches go to the next frontier
-      uint32_t pos = 0;
-      if (emit) {
-        const uint32_t mask = A.tab_mask[ec];
-        if (mask == kDirectPlain) {  // the next frontier comes from a scan of the table
-          pos = A.tab_off[ec] + v;
-          P::add(acc_next, pos, delta);
-        } else {
-          pos = table_find_or_insert(A.keys_nxt, A.tab_off[ec], mask, v, &first);
-          if (pos == ~0u)
-            atomicOr(A.err + ec, kErrTableFull);
-          else
-            P::add(acc_next, pos, delta);
-        }
-      }
-      stage_push(stage, staged, (static_cast<uint64_t>(pos) << 32) | ec, first, A.fout, A.cnt_out);
-      return;
-    }
-    const size_t vcell = static_cast<size_t>(v) * A.su + static_cast<size_t>(ec) * A.sc;
-    if (emit) {
-      if (sparse)
-        first = P::add_ret(acc_next, vcell, delta);
-      else
-        P::add(acc_next, vcell, delta);
-    }
-    if (sparse)  // stage first-touched cells, flush in chunks
-      stage_push(stage, staged, (static_cast<uint64_t>(v) << 32) | ec, first, A.fout, A.cnt_out);
+    push_atomic<T, kMode>(A, stage, staged, sparse, emit, v, ec, delta, acc_next);
   };
   auto emit_sampled = [&](bool emit, uint32_t v, uint32_t ec, bool eneg) {
     if (binned) {
@@ -1131,7 +1146,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
     if (kServe && serve_live) serve_entry(A, s_serve, ec, eJ, emass);
     // long deterministic prefixes and entries with many work items leave for
     // the deferred lists
-    if (!kServe && A.big_ctr != nullptr && __any(eJ >= kBatchDetRow || eJ >= A.big_row)) {
+    if (A.big_ctr != nullptr && __any(eJ >= kBatchDetRow || eJ >= A.big_row)) {
       const bool full = wave_sum_all(eJ < (1u << 20) ? eJ : (1u << 20)) > kBatchDet;
       unsigned long long slot = 0, off = 0;
       if (defer_slots(A.big_ctr, A.big_cap, eJ >= A.big_row || (full && eJ >= kBatchDetRow), eJ, &slot, &off)) {
@@ -1139,16 +1154,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
         br.off = off;
         br.rp = erp;
         br.cv = ecv;
-        br.c = ec;
+        br.c = ecw;
         br.J = eJ;
-        br.neg = eneg ? 1u : 0u;
-        br.pad = 0;
         A.big[slot] = br;
         dwork = 0;
       }
     }
     const uint32_t big_items = static_cast<uint32_t>(A.samp_items);
-    if (!kServe && A.samp_ctr != nullptr && __any(iwork >= kBatchItemRow || iwork >= big_items)) {
+    if (A.samp_ctr != nullptr && __any(iwork >= kBatchItemRow || iwork >= big_items)) {
       const bool full = wave_sum_all(iwork < (1u << 20) ? iwork : (1u << 20)) > kBatchItems;
       unsigned long long slot = 0, off = 0;
       if (defer_slots(A.samp_ctr, A.big_cap, iwork >= big_items || (full && iwork >= kBatchItemRow), iwork, &slot,
@@ -1271,6 +1284,7 @@ template <typename T, int kMode, int kG = 1>
 __global__ __launch_bounds__(kThreads) void k_det_big(LevelArgs A, typename Prec<T>::Cell* __restrict__ acc_next) {
   using P = Prec<T>;
   using Delta = typename P::Delta;
+  constexpr bool kServe = kMode == kPerColumn;
   constexpr int kWaves = kThreads / kWave;
   __shared__ uint64_t s_stage[kWaves][kStage];
   const unsigned long long ctr = *A.big_ctr;
@@ -1313,27 +1327,20 @@ __global__ __launch_bounds__(kThreads) void k_det_big(LevelArgs A, typename Prec
           next = e + 1 < nb ? R[e + 1].off : total;
         }
         const BigRow& br = R[e];
-        vc = br.c;
+        vc = br.c & kBatchCol;
         const ColParams* cpd = A.cp + vc;
         const int64_t arc = br.rp + static_cast<int64_t>(k - off);
         v = A.col[arc];
         double inc = br.cv;
-        if (kMode == kBatchAP) inc = inc * (A.arcfac != nullptr ? A.arcfac[arc] : A.da[A.nd[arc]]);
+        if (kServe ? !(br.c & kBatchAZero) : kMode == kBatchAP)
+          inc = inc * (A.arcfac != nullptr ? A.arcfac[arc] : (kServe ? cpd->da : A.da)[A.nd[arc]]);
         T val = to_w(inc, T());
-        if (br.neg) val = -val;
+        if (br.c & kBatchNeg) val = -val;
         emit = P::to_units(val, *cpd, &delta);
-        if (!emit) atomicOr(A.err, 1);
+        if (!emit) atomicOr(A.err + (kServe ? vc : 0u), 1);
       }
-      const size_t vcell = static_cast<size_t>(v) * A.su + static_cast<size_t>(vc) * A.sc;
       if (emit && det_bins != nullptr) mark_det_bin<kG>(A, det_bins, v, vc);
-      bool first = false;
-      if (emit) {
-        if (sparse)
-          first = P::add_ret(acc_next, vcell, delta);
-        else
-          P::add(acc_next, vcell, delta);
-      }
-      if (sparse) stage_push(stage, staged, (static_cast<uint64_t>(v) << 32) | vc, first, A.fout, A.cnt_out);
+      push_atomic<T, kMode>(A, stage, staged, sparse, emit, v, vc, delta, acc_next);
     }
   }
   if (sparse) stage_flush(stage, staged, A.fout, A.cnt_out);
@@ -1353,10 +1360,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
     LevelArgs A, typename Prec<T>::Cell* __restrict__ acc_next) {
   using P = Prec<T>;
   using Delta = typename P::Delta;
+  constexpr bool kServe = kMode == kPerColumn;
   constexpr int kWaves = kThreads / kWave;
   __shared__ BatchLds s_batch[kWaves];
   __shared__ uint64_t s_stage[kWaves][kStage];
-  __shared__ unsigned int s_hist[kBuckets];
+  __shared__ unsigned int s_hist[kServe ? 1 : kBuckets];
+  __shared__ ServeSums s_serve[kServe ? kServeLdsSlots : 1];
   const unsigned long long ctr = *A.samp_ctr;
   unsigned long long nb = ctr >> kBigShift;
   if (nb == 0) return;  // the whole grid
@@ -1368,6 +1377,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
   const bool sparse = mode == kModeSparse;
   if (binned) {
     for (int i = threadIdx.x; i < kBuckets; i += blockDim.x) s_hist[i] = 0;
+    __syncthreads();
+  }
+  if (kServe) {
+    for (int i = threadIdx.x; i < kServeLdsSlots; i += blockDim.x) s_serve[i] = ServeSums{};
     __syncthreads();
   }
   const int lane = lane_id();
@@ -1406,7 +1419,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
     B.cv[lane] = bs.cv;
     B.p0[lane] = bs.p0;
     B.th[lane] = cp.theta;
-    B.ctr3[lane] = (cp.qid << 8) | static_cast<uint32_t>(A.level);
+    B.ctr3[lane] = (cp.qid << 8) | static_cast<uint32_t>(kServe ? cp.level : A.level);
     B.u[lane] = bs.u;
     B.c[lane] = bs.c;
     B.d[lane] = bs.d;
@@ -1428,21 +1441,18 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
     }
     Delta delta{};
     if (emit) delta = P::theta_units(A.cp[c], neg);
-    const size_t vcell = static_cast<size_t>(v) * A.su + static_cast<size_t>(c) * A.sc;
-    bool first = false;
-    if (emit) {
-      if (sparse)
-        first = P::add_ret(acc_next, vcell, delta);
-      else
-        P::add(acc_next, vcell, delta);
-    }
-    if (sparse) stage_push(stage, staged, (static_cast<uint64_t>(v) << 32) | c, first, A.fout, A.cnt_out);
+    push_atomic<T, kMode>(A, stage, staged, sparse, emit, v, c, delta, acc_next);
   };
-  auto served = [](uint32_t, uint32_t, uint32_t, uint32_t) {};
+  auto served = [&](uint32_t c, uint32_t cand, uint32_t acc, uint32_t runs) {
+    if (kServe) serve_item(A, s_serve, c, cand, acc, runs);
+  };
   sample_loop<kMode>(A, B, refill, emit_sampled, served, w_cand, w_acc, w_runs);
   if (sparse) stage_flush(stage, staged, A.fout, A.cnt_out);
   if (binned) finish_records<kG>(A, s_hist, reinterpret_cast<uint32_t*>(stage), staged, acc_next);
-  if (lane == 0) {
+  if (kServe) {  // flush the block's per-column sums
+    __syncthreads();
+    for (int i = threadIdx.x; i < kServeLdsSlots && i < A.slots; i += blockDim.x) serve_flush(serve_row(A, i), s_serve[i]);
+  } else if (lane == 0) {
     unsigned long long* cnt = count_row(A);
     if (w_cand) atomicAdd(cnt + 3, static_cast<unsigned long long>(w_cand));
     if (w_acc) atomicAdd(cnt + 4, static_cast<unsigned long long>(w_acc));

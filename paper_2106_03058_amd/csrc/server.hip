@@ -56,12 +56,12 @@ using srv::AdmitItem;
 __global__ void k_admit(const AdmitItem* __restrict__ items, int k, uint32_t* __restrict__ keys,
                         long long* __restrict__ vals, const uint32_t* __restrict__ tab_off,
                         const uint32_t* __restrict__ tab_mask, uint64_t* __restrict__ F,
-                        unsigned long long* __restrict__ cnt, unsigned long long* __restrict__ counters, int slots,
-                        int* __restrict__ err) {
+                        unsigned long long* __restrict__ cnt, unsigned long long* __restrict__ counters, int shards,
+                        int slots, int* __restrict__ err) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= k) return;
   const AdmitItem it = items[i];
-  for (int sh = 0; sh < kServeShards; ++sh)  // (a mass of +0.0 is all zero bits)
+  for (int sh = 0; sh < shards; ++sh)  // (a mass of +0.0 is all zero bits)
     for (int j = 0; j < kCountStride; ++j)
       counters[(static_cast<size_t>(sh) * slots + it.slot) * kCountStride + j] = 0;
   bool first = false;
@@ -77,7 +77,12 @@ __global__ void k_admit(const AdmitItem* __restrict__ items, int k, uint32_t* __
   F[at] = (static_cast<uint64_t>(pos) << 32) | it.slot;
 }
 
-__global__ void k_zero_count(unsigned long long* c) { *c = 0; }
+// A step's counters at its start: the next frontier's and the deferred lists'.
+__global__ void k_zero_counts(unsigned long long* c, unsigned long long* big_ctr) {
+  if (threadIdx.x == 0) *c = 0;
+  if (threadIdx.x < 2) big_ctr[threadIdx.x] = 0;
+}
+constexpr unsigned long long kServeBigCap = 1ull << 16;  // entries of each deferred list
 
 // The next frontier of the queries with plain direct tables: the non-zero
 // positions of their next tables (row y of the grid scans table t[y]; the
@@ -85,7 +90,7 @@ __global__ void k_zero_count(unsigned long long* c) { *c = 0; }
 // kScanCells positions, 32 loads per lane, and appends its non-zero ones with
 // one atomic: every append is a round trip to one address that serialises at
 // about 10 ns, and with one per wave and 512 entries a scan of 32 tables of
-// 2^18 nodes took 0.25 ms, now XXX (its 67 MB at the rate of a copy: 0.013).
+// 2^18 nodes took 0.25 ms, now 0.016 (its 67 MB at the rate of a copy: 0.013).
 constexpr int kScanLoads = 32;
 constexpr int kScanCells = kThreads * kScanLoads;
 __global__ __launch_bounds__(kThreads) void k_scan_plain(const srv::PlainTable* __restrict__ t, int64_t n,
@@ -129,14 +134,14 @@ __global__ __launch_bounds__(kThreads) void k_scan_plain(const srv::PlainTable* 
 }
 
 // Per slot the sums of its counter rows, and its error flags in word 7.
-__global__ void k_fold_slots(const unsigned long long* __restrict__ rows, const int* __restrict__ err, int slots,
-                             unsigned long long* __restrict__ out) {
+__global__ void k_fold_slots(const unsigned long long* __restrict__ rows, const int* __restrict__ err, int shards,
+                             int slots, unsigned long long* __restrict__ out) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= slots * kCountStride) return;
   const int k = i % kCountStride, c = i / kCountStride;
   if (k == kCountMass) {
     double m = 0.0;
-    for (int sh = 0; sh < kServeShards; ++sh)
+    for (int sh = 0; sh < shards; ++sh)
       m += reinterpret_cast<const double*>(rows)[static_cast<size_t>(sh) * slots * kCountStride + i];
     out[i] = static_cast<unsigned long long>(__double_as_longlong(m));
     return;
@@ -146,7 +151,7 @@ __global__ void k_fold_slots(const unsigned long long* __restrict__ rows, const 
     return;
   }
   unsigned long long v = 0;
-  for (int sh = 0; sh < kServeShards; ++sh) v += rows[static_cast<size_t>(sh) * slots * kCountStride + i];
+  for (int sh = 0; sh < shards; ++sh) v += rows[static_cast<size_t>(sh) * slots * kCountStride + i];
   out[i] = v;
 }
 
@@ -190,11 +195,12 @@ struct agp_server {
   agp_server_config_t cfg{};
   int64_t n = 0;
   int S = 0;
+  int shards = 1;  // sets of counter rows
   hipStream_t stream = nullptr;
   std::chrono::steady_clock::time_point t0;
   // device state: the table pool (keys and values of this step's and the
   // next step's tables, frontier lists of pool positions) and per-slot data
-  agp::DevBuf keys, vals, F[2], counts, counters, sums, err, cp, admit, mode, tabs;
+  agp::DevBuf keys, vals, F[2], counts, counters, sums, err, cp, admit, mode, tabs, big;
   int cur = 0;
   uint64_t pool_entries = 0;
   agp::srv::RangePool pool;  // guarded by mu
@@ -425,10 +431,11 @@ int step(agp_server* s) {
     k_clear_err<<<grid_for(nadmit, 64), 64, 0, st>>>(s->admit.as<srv::AdmitItem>(), nadmit, s->err.as<int>());
     k_admit<<<grid_for(nadmit, 64), 64, 0, st>>>(s->admit.as<srv::AdmitItem>(), nadmit, s->keys.as<uint32_t>(),
                                                   s->vals.as<long long>(), tab_off, tab_mask, F[cur],
-                                                  counts + cur, s->counters.as<unsigned long long>(), s->S,
+                                                  counts + cur, s->counters.as<unsigned long long>(), s->shards, s->S,
                                                   s->err.as<int>());
   }
-  k_zero_count<<<1, 1, 0, st>>>(counts + nxt);
+  unsigned long long* big_ctr = s->big.as<unsigned long long>();
+  k_zero_counts<<<1, kWave, 0, st>>>(counts + nxt, big_ctr);
   LevelArgs A{};
   A.rp = s->g->row_ptr;
   A.col = s->g->col;
@@ -446,6 +453,7 @@ int step(agp_server* s) {
   A.cnt_out = counts + nxt;
   A.counters = s->counters.as<unsigned long long>();
   A.slots = s->S;
+  A.shard_mask = s->shards - 1;
   A.err = s->err.as<int>();
   A.positive = 0;
   A.dense_cut = ~0ull;
@@ -457,8 +465,20 @@ int step(agp_server* s) {
   A.tab_off = tab_next;
   A.tab_mask = tab_mask;
   A.tab_cur = tab_off;
+  // rows with many deterministic pushes and entries with many work items are
+  // deferred to the whole grid, as in a batched level (hubs of 10^4
+  // neighbours had been the tail of most steps: YYY)
+  A.big_row = kBigRow;
+  A.samp_items = kBigItems;
+  A.big_cap = kServeBigCap;
+  A.big_ctr = big_ctr;
+  A.samp_ctr = big_ctr + 1;
+  A.big = reinterpret_cast<BigRow*>(big_ctr + 2);
+  A.samp = reinterpret_cast<BigSamp*>(A.big + kServeBigCap);
   k_level<float, false, kPerColumn><<<kLevelBlocks, kThreads, 0, st>>>(A, nullptr, s->vals.as<long long>(),
                                                                  s->vals.as<long long>());
+  k_det_big<float, kPerColumn><<<1024, kThreads, 0, st>>>(A, s->vals.as<long long>());
+  k_samp_big<float, kPerColumn><<<1024, kThreads, 0, st>>>(A, s->vals.as<long long>());
   if (nplain > 0) {
     AGP_HIP(hipMemcpyAsync(s->plain.ptr, s->h_plain, sizeof(srv::PlainTable) * nplain, hipMemcpyHostToDevice, st));
     k_scan_plain<<<dim3(static_cast<unsigned>((s->n + kScanCells - 1) / kScanCells), static_cast<unsigned>(nplain)),
@@ -466,7 +486,7 @@ int step(agp_server* s) {
         s->plain.as<srv::PlainTable>(), s->n, s->vals.as<long long>(), F[nxt], counts + nxt);
   }
   k_fold_slots<<<grid_for(static_cast<int64_t>(s->S) * kCountStride, 256), 256, 0, st>>>(
-      s->counters.as<unsigned long long>(), s->err.as<int>(), s->S, s->sums.as<unsigned long long>());
+      s->counters.as<unsigned long long>(), s->err.as<int>(), s->shards, s->S, s->sums.as<unsigned long long>());
   AGP_HIP(hipGetLastError());
   AGP_HIP(hipMemcpyAsync(s->h_sums, s->sums.ptr, sizeof(unsigned long long) * kCountStride * s->S,
                          hipMemcpyDeviceToHost, st));
@@ -582,6 +602,7 @@ int agp_server_create(const agp_graph_t* g, const agp_server_config_t* cfg, agp_
   s->cfg = *cfg;
   s->n = g->n;
   s->S = cfg->max_slots;
+  s->shards = s->S < lvl::kServeShardSlots ? lvl::kServeShards : 1;
   s->t0 = std::chrono::steady_clock::now();
   s->slot_ticket.assign(s->S, 0);
   // the pool: per entry a key (4 B) and a value (8 B), and half a frontier
@@ -610,13 +631,15 @@ int agp_server_create(const agp_graph_t* g, const agp_server_config_t* cfg, agp_
         (rc = s->F[0].reserve(P / 2 * sizeof(uint64_t), false, s->stream)) ||
         (rc = s->F[1].reserve(P / 2 * sizeof(uint64_t), false, s->stream)) ||
         (rc = s->counts.reserve(2 * sizeof(unsigned long long), true, s->stream)) ||
-        (rc = s->counters.reserve(sizeof(unsigned long long) * lvl::kCountStride * lvl::kServeShards * s->S, true,
+        (rc = s->counters.reserve(sizeof(unsigned long long) * lvl::kCountStride * s->shards * s->S, true,
                                   s->stream)) ||
         (rc = s->sums.reserve(sizeof(unsigned long long) * lvl::kCountStride * s->S, true, s->stream)) ||
         (rc = s->err.reserve(sizeof(int) * s->S, true, s->stream)) ||
         (rc = s->cp.reserve(sizeof(ColParams) * s->S, false, s->stream)) ||
         (rc = s->admit.reserve(sizeof(srv::AdmitItem) * s->S, false, s->stream)) ||
         (rc = s->mode.reserve(sizeof(int), true, s->stream)) ||
+        (rc = s->big.reserve(2 * sizeof(unsigned long long) + (sizeof(lvl::BigRow) + sizeof(lvl::BigSamp)) * kServeBigCap,
+                             false, s->stream)) ||
         (rc = s->tabs.reserve(sizeof(uint32_t) * 3 * s->S, true, s->stream)) ||
         (rc = s->plain.reserve(sizeof(srv::PlainTable) * s->S, false, s->stream))) {
     }
@@ -733,7 +756,7 @@ int agp_server_destroy(agp_server_t* s) {
   if (s->worker.joinable()) s->worker.join();
   if (s->stream) (void)hipStreamSynchronize(s->stream);
   for (auto* b : {&s->keys, &s->vals, &s->F[0], &s->F[1], &s->counts, &s->counters, &s->sums, &s->err, &s->cp,
-                  &s->admit, &s->mode, &s->tabs, &s->plain})
+                  &s->admit, &s->mode, &s->tabs, &s->big, &s->plain})
     b->release();
   if (s->h_cp) (void)hipHostFree(s->h_cp);
   if (s->h_tabs) (void)hipHostFree(s->h_tabs);
