@@ -22,6 +22,18 @@ constexpr int kSeg = 1 << kSegLog2;
 // probability p_v.
 constexpr double kMergeCandidates = 4.0;
 
+// Lanes of the wave whose p holds, and whether any does: the builtin takes the
+// lane mask itself (__ballot and __any take an int, and each use became a
+// select and a compare on the vector unit).
+__device__ __forceinline__ unsigned long long wave_ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+__device__ __forceinline__ bool wave_any(bool p) { return wave_ballot(p) != 0ull; }
+// A wave-uniform value the compiler cannot see to be one, in scalar registers.
+__device__ __forceinline__ uint32_t uniform(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ unsigned long long uniform(unsigned long long v) {
+  return (static_cast<unsigned long long>(uniform(static_cast<uint32_t>(v >> 32))) << 32) |
+         uniform(static_cast<uint32_t>(v));
+}
+
 // ---------------------------------------------------------------- Philox
 // Philox4x32-10 counter-based generator (Salmon, Moraes, Dror, Shaw, "Parallel
 // random numbers: as easy as 1, 2, 3", SC'11): ten rounds, each multiplying
@@ -31,6 +43,11 @@ struct U4 {
   uint32_t x, y, z, w;
 };
 
+// a ^ b ^ c in one instruction
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
 __device__ __forceinline__ U4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                             uint32_t k0, uint32_t k1) {
 #pragma unroll
@@ -38,8 +55,8 @@ __device__ __forceinline__ U4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c
     // one 32 x 32 -> 64-bit product per multiplier (a single v_mad_u64_u32)
     const uint64_t p0 = static_cast<uint64_t>(0xD2511F53u) * c0;
     const uint64_t p1 = static_cast<uint64_t>(0xCD9E8D57u) * c2;
-    const uint32_t y0 = static_cast<uint32_t>(p1 >> 32) ^ c1 ^ k0;
-    const uint32_t y2 = static_cast<uint32_t>(p0 >> 32) ^ c3 ^ k1;
+    const uint32_t y0 = xor3(static_cast<uint32_t>(p1 >> 32), c1, k0);
+    const uint32_t y2 = xor3(static_cast<uint32_t>(p0 >> 32), c3, k1);
     c0 = y0;
     c1 = static_cast<uint32_t>(p1);
     c2 = y2;
@@ -60,8 +77,8 @@ __device__ __forceinline__ U4 philox4x32_10_skey(uint32_t c0, uint32_t c1, uint3
   for (int round = 0; round < 10; ++round) {
     const uint64_t p0 = static_cast<uint64_t>(0xD2511F53u) * c0;
     const uint64_t p1 = static_cast<uint64_t>(0xCD9E8D57u) * c2;
-    const uint32_t y0 = static_cast<uint32_t>(p1 >> 32) ^ c1 ^ k0;
-    const uint32_t y2 = static_cast<uint32_t>(p0 >> 32) ^ c3 ^ k1;
+    const uint32_t y0 = xor3(static_cast<uint32_t>(p1 >> 32), c1, k0);
+    const uint32_t y2 = xor3(static_cast<uint32_t>(p0 >> 32), c3, k1);
     c0 = y0;
     c1 = static_cast<uint32_t>(p1);
     c2 = y2;
@@ -75,11 +92,11 @@ __device__ __forceinline__ U4 philox4x32_10_skey(uint32_t c0, uint32_t c1, uint3
 
 // 53 random bits (32 from `hi`, the top 21 of `lo`) as a double in [0, 1).
 __device__ __forceinline__ double unit_double(uint32_t hi, uint32_t lo) {
-  // hi * 2^21 + (lo >> 11) is an integer below 2^53: both terms and the sum
-  // are exact in binary64
-  const double h = static_cast<double>(hi) * 2097152.0;
-  const double l = static_cast<double>(lo >> 11);
-  return (h + l) * 0x1p-53;
+  // (hi * 2^21 + (lo >> 11)) * 2^-53: the integer is below 2^53, so both
+  // terms and their sum are exact in binary64 however they are scaled and
+  // added (one fused operation here)
+  const double l = static_cast<double>(lo >> 11) * 0x1p-53;
+  return __builtin_fma(static_cast<double>(hi), 0x1p-32, l);
 }
 
 // --------------------------------------------------------- geometric skip
@@ -113,6 +130,28 @@ __device__ __forceinline__ int geometric_skip(const SkipTable& t, double u) {
     if (next <= u) {
       F = next;
       K |= 1 << h;
+    }
+  }
+  return K;
+}
+
+// The same skip where 64 and more are all alike (a run lies inside one window
+// of 64 positions, so such a skip ends it): the largest K < 64, or any K >= 64
+// when s_6 <= u.  The two leading steps are taken on F = 0, where F + s_h -
+// F s_h is s_h exactly.
+__device__ __forceinline__ uint32_t geometric_skip64(const SkipTable& t, double u) {
+  uint32_t K = t.sk[6] <= u ? 64u : 0u;
+  const bool b5 = t.sk[5] <= u;
+  double F = b5 ? t.sk[5] : 0.0;
+  K |= b5 ? 32u : 0u;
+#pragma unroll
+  for (int h = 4; h >= 0; --h) {
+    const double plus = F + t.sk[h];
+    const double times = F * t.sk[h];
+    const double next = plus - times;
+    if (next <= u) {
+      F = next;
+      K |= 1u << h;
     }
   }
   return K;
@@ -278,7 +317,7 @@ __device__ __forceinline__ int lane_id() { return __lane_id(); }
 __device__ __forceinline__ void wave_append(uint64_t* __restrict__ list,
                                             unsigned long long* __restrict__ count,
                                             uint64_t item, bool pred) {
-  const unsigned long long mask = __ballot(pred);
+  const unsigned long long mask = wave_ballot(pred);
   if (mask == 0ull) return;
   const int leader = __ffsll(static_cast<long long>(mask)) - 1;
   unsigned long long base = 0;
@@ -311,7 +350,7 @@ template <int kCap = kStage>
 __device__ __forceinline__ void stage_push(uint64_t* stage, int& staged, uint64_t item, bool pred,
                                            uint64_t* __restrict__ list,
                                            unsigned long long* __restrict__ count) {
-  const unsigned long long mask = __ballot(pred);
+  const unsigned long long mask = wave_ballot(pred);
   if (pred) stage[staged + __popcll(mask & ((1ull << lane_id()) - 1ull))] = item;
   staged += __popcll(mask);
   if (staged > kCap - kWave) stage_flush(stage, staged, list, count);

@@ -478,14 +478,14 @@ __device__ __forceinline__ void emit_record(const LevelArgs& A, unsigned int* s_
   const unsigned long long lt = (1ull << lane_id()) - 1ull;
   if constexpr (kG > 1) {
     const int n0 = staged & 0xFFFF, n1 = staged >> 16;
-    const unsigned long long m1 = __ballot(emit && g != 0);
-    const unsigned long long m0 = __ballot(emit) & ~m1;
+    const unsigned long long m1 = wave_ballot(emit && g != 0);
+    const unsigned long long m0 = wave_ballot(emit) & ~m1;
     if (emit) stage[g ? kRecStage - 1 - (n1 + __popcll(m1 & lt)) : n0 + __popcll(m0 & lt)] = rec;
     const int k0 = n0 + __popcll(m0), k1 = n1 + __popcll(m1);
     staged = k0 | (k1 << 16);
     if (k0 + k1 > kRecStage - kWave) stage_flush_records<kG>(stage, staged, acc);
   } else {
-    const unsigned long long m0 = __ballot(emit);
+    const unsigned long long m0 = wave_ballot(emit);
     if (emit) stage[staged + __popcll(m0 & lt)] = rec;
     staged += __popcll(m0);
     if (staged > kRecStage - kWave) stage_flush_records<kG>(stage, staged, acc);
@@ -714,7 +714,17 @@ __device__ __forceinline__ uint32_t queue_items(BatchLds& B, uint32_t iwork) {
   for (int j = static_cast<int>(iinc - iwork < kItemMap ? iinc - iwork : kItemMap); j < j1; ++j)
     B.item_entry[j] = static_cast<uint8_t>(lane);
   if (lane == kWave - 1) B.ioff[kBatch] = iinc;
-  return __shfl(iinc, kWave - 1);
+  return __builtin_amdgcn_readlane(iinc, kWave - 1);
+}
+
+// v < fl(p / q) for v in [0, 1) and factors p, q > 0: fl(p / q) is p / q and
+// fl(v q) is v q to 2^-53 each, so a product off p by more than 2^-50 decides;
+// the division is left for the others (one in about 2^48).
+__device__ __forceinline__ bool below_ratio(double v, double p, double q) {
+  const double vq = v * q;
+  if (vq < p * (1.0 - 0x1p-50)) return true;
+  if (vq > p * (1.0 + 0x1p-50)) return false;
+  return v < p / q;
 }
 
 // Draws the queued work items of the batches that refill sets up:
@@ -751,10 +761,10 @@ __device__ __forceinline__ void sample_loop(const LevelArgs& A, BatchLds& B, Ref
       if (kServe) served(c, it_cand, it_acc, it_runs);
     }
     // (b) the queue is empty and a lane is idle: set up the next batch
-    if (more && it_next >= it_total && __any(!active)) more = refill(it_next, it_total);
+    if (more && it_next >= it_total && wave_any(!active)) more = refill(it_next, it_total);
     // (c) idle lanes take sampled work items from the queue
     {
-      const unsigned long long idle = __ballot(!active);
+      const unsigned long long idle = wave_ballot(!active);
       if (!active) {
         const uint32_t it = it_next + static_cast<uint32_t>(__popcll(idle & lt_mask));
         if (it < it_total) {
@@ -799,13 +809,13 @@ __device__ __forceinline__ void sample_loop(const LevelArgs& A, BatchLds& B, Ref
       it_next += static_cast<uint32_t>(__popcll(idle));
       if (it_next > it_total) it_next = it_total;
     }
-    if (!__any(active)) {
+    if (!wave_any(active)) {
       if (!more) break;  // queue empty (no idle lane took an item), no batch left
       continue;
     }
     // (d) a run: the rest of the current window, or (a > 0) of its degree
     // group unless few candidates are expected over the rest of the window
-    if (!kServe) w_runs += static_cast<uint32_t>(__popcll(__ballot(active && need_run)));
+    if (!kServe) w_runs += static_cast<uint32_t>(__popcll(wave_ballot(active && need_run)));
     if (active && need_run) {
       if (kServe) ++it_runs;
       const uint32_t wnext = ((s >> kSegLog2) + 1u) << kSegLog2;
@@ -836,7 +846,7 @@ __device__ __forceinline__ void sample_loop(const LevelArgs& A, BatchLds& B, Ref
     if (active && !need_run) {
       const U4 o = kServe ? philox4x32_10(t, s, u, ctr3, key0, key1) : philox4x32_10_skey(t, s, u, ctr3, key0, key1);
       const double V = unit_double(o.x, o.y);
-      const uint32_t cand = pos + static_cast<uint32_t>(geometric_skip(tab, V));
+      const uint32_t cand = pos + geometric_skip64(tab, V);
       if (cand >= run_end) {
         s = run_end;
         need_run = true;
@@ -848,10 +858,8 @@ __device__ __forceinline__ void sample_loop(const LevelArgs& A, BatchLds& B, Ref
         // acceptance test needs it (one round trip instead of two)
         const uint32_t va = A.col[arc];
         bool accept = true;  // a = 0: the ratio is 1 and every uniform is below it
-        if (!azero) {
-          const double ratio = (A.arcfac != nullptr ? A.arcfac[arc] : da[A.nd[arc]]) / dstart;
-          accept = unit_double(o.z, o.w) < ratio;
-        }
+        if (!azero)
+          accept = below_ratio(unit_double(o.z, o.w), A.arcfac != nullptr ? A.arcfac[arc] : da[A.nd[arc]], dstart);
         if (accept) {
           if (kServe) ++it_acc;
           v = va;
@@ -862,8 +870,8 @@ __device__ __forceinline__ void sample_loop(const LevelArgs& A, BatchLds& B, Ref
       }
     }
     if (!kServe) {
-      w_cand += static_cast<uint32_t>(__popcll(__ballot(cand_hit)));
-      w_acc += static_cast<uint32_t>(__popcll(__ballot(emit)));
+      w_cand += static_cast<uint32_t>(__popcll(wave_ballot(cand_hit)));
+      w_acc += static_cast<uint32_t>(__popcll(wave_ballot(emit)));
     }
     emit_sampled(emit, v, c, neg);
   }
@@ -876,7 +884,7 @@ __device__ __forceinline__ void sample_loop(const LevelArgs& A, BatchLds& B, Ref
 __device__ __forceinline__ bool defer_slots(unsigned long long* ctr, unsigned long long cap, bool want,
                                             unsigned long long work, unsigned long long* slot,
                                             unsigned long long* off) {
-  const unsigned long long mask = __ballot(want);
+  const unsigned long long mask = wave_ballot(want);
   if (mask == 0ull) return false;
   if ((__hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> kBigShift) >= cap) return false;
   const int lane = lane_id();
@@ -886,10 +894,10 @@ __device__ __forceinline__ bool defer_slots(unsigned long long* ctr, unsigned lo
     const unsigned long long t = __shfl_up(inc, o);
     if (lane >= o) inc += t;
   }
-  const unsigned long long total = __shfl(inc, kWave - 1);
+  const unsigned long long total = uniform(__shfl(inc, kWave - 1));
   unsigned long long old = 0;
   if (lane == 0) old = atomic_add_ret(ctr, (static_cast<unsigned long long>(__popcll(mask)) << kBigShift) | total);
-  old = __shfl(old, 0);
+  old = uniform(old);
   *slot = (old >> kBigShift) + static_cast<unsigned long long>(__popcll(mask & ((1ull << lane) - 1ull)));
   *off = (old & ((1ull << kBigShift) - 1ull)) + inc - work;
   return want && *slot < cap;
@@ -943,7 +951,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
     __syncthreads();
   }
   const int lane = lane_id();
-  const int wave = threadIdx.x / kWave;
+  const int wave = static_cast<int>(uniform(threadIdx.x / kWave));
   BatchLds& B = s_batch[wave];
   uint64_t* stage = s_stage[wave];
   int staged = 0;  // wave-uniform
@@ -1142,11 +1150,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
         }
       }
     }
-    if (!kServe) w_front += static_cast<uint32_t>(__popcll(__ballot(front_live)));
+    if (!kServe) w_front += static_cast<uint32_t>(__popcll(wave_ballot(front_live)));
     if (kServe && serve_live) serve_entry(A, s_serve, ec, eJ, emass);
     // long deterministic prefixes and entries with many work items leave for
     // the deferred lists
-    if (A.big_ctr != nullptr && __any(eJ >= kBatchDetRow || eJ >= A.big_row)) {
+    if (A.big_ctr != nullptr && wave_any(eJ >= kBatchDetRow || eJ >= A.big_row)) {
       const bool full = wave_sum_all(eJ < (1u << 20) ? eJ : (1u << 20)) > kBatchDet;
       unsigned long long slot = 0, off = 0;
       if (defer_slots(A.big_ctr, A.big_cap, eJ >= A.big_row || (full && eJ >= kBatchDetRow), eJ, &slot, &off)) {
@@ -1161,7 +1169,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
       }
     }
     const uint32_t big_items = static_cast<uint32_t>(A.samp_items);
-    if (A.samp_ctr != nullptr && __any(iwork >= kBatchItemRow || iwork >= big_items)) {
+    if (A.samp_ctr != nullptr && wave_any(iwork >= kBatchItemRow || iwork >= big_items)) {
       const bool full = wave_sum_all(iwork < (1u << 20) ? iwork : (1u << 20)) > kBatchItems;
       unsigned long long slot = 0, off = 0;
       if (defer_slots(A.samp_ctr, A.big_cap, iwork >= big_items || (full && iwork >= kBatchItemRow), iwork, &slot,
@@ -1182,7 +1190,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
       }
     }
     long long dtot = 0;  // deterministic pushes of the batch
-    if (__any(dwork != 0)) {
+    if (wave_any(dwork != 0)) {
       long long dinc = dwork;
 #pragma unroll
       for (int off = 1; off < kWave; off <<= 1) {
@@ -1190,7 +1198,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
         if (lane >= off) dinc += td;
       }
       B.doff[lane] = dinc - dwork;
-      dtot = __shfl(dinc, kWave - 1);
+      dtot = static_cast<long long>(uniform(static_cast<unsigned long long>(__shfl(dinc, kWave - 1))));
     }
     B.rp[lane] = erp;
     B.cv[lane] = ecv;
@@ -1296,7 +1304,7 @@ __global__ __launch_bounds__(kThreads) void k_det_big(LevelArgs A, typename Prec
   const bool sparse = *A.mode_out == kModeSparse;
   uint8_t* const det_bins = *A.mode_out == kModeBinned ? A.det_bins : nullptr;
   const int lane = lane_id();
-  const int wave = threadIdx.x / kWave;
+  const int wave = static_cast<int>(uniform(threadIdx.x / kWave));
   uint64_t* stage = s_stage[wave];
   int staged = 0;  // wave-uniform
   // a chunk of pushes per wave: as many as give every wave one, in whole
@@ -1384,7 +1392,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
     __syncthreads();
   }
   const int lane = lane_id();
-  const int wave = threadIdx.x / kWave;
+  const int wave = static_cast<int>(uniform(threadIdx.x / kWave));
   BatchLds& B = s_batch[wave];
   uint64_t* stage = s_stage[wave];
   int staged = 0;  // wave-uniform
@@ -1590,7 +1598,7 @@ __global__ __launch_bounds__(kThreads) void k_compact(Pred pred, int64_t n, int 
       }
 #pragma unroll
       for (int k = 0; k < kCompactUnroll; ++k) {
-        const unsigned long long m = __ballot(p[k]);
+        const unsigned long long m = wave_ballot(p[k]);
         if (p[k]) stage[staged + __popcll(m & lt_mask)] = static_cast<uint16_t>(j + k * kWave + lane);
         staged += __popcll(m);
         if (staged > kCompactCap - kWave) compact_flush(stage, staged, u0, r0, C, rc, small, F, cnt);
