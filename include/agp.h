@@ -307,7 +307,8 @@ int agp_set_tuning(const agp_graph_t* g, int32_t C, double a, double b, const ag
  *   AGP_AGGREGATION=atomic|binned|auto   the aggregation of agp_tuning_t;
  *   AGP_DENSE=0|1|auto   the dense field of agp_tuning_t;
  *   AGP_CAPTURE=0|1      the capture field of agp_tuning_t;
- *   AGP_RECORD_CAP=n     at most n push records per binned level (per record
+ *   AGP_RECORD_CAP=n     at most n push records per binned level, rounded up to
+ *                        32 (their buffer is kept in 16 segments; per record
  *                        group on dense levels, split between the two groups
  *                        of frontier-list levels; records beyond it are added
  *                        with atomics);

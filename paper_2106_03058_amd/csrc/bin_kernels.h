@@ -25,13 +25,15 @@ constexpr int kReduceThreads = 512;
 
 // One block per column group of records: the group's nbk bucket counts at
 // g * nbk (cleared), its offsets and cursors at g * (kBuckets + 1) and
-// g * kBuckets; a group whose records outgrew its buffer switches the level
-// to the atomic fallback.
+// g * kBuckets, and its record total; a group with a segment whose records
+// outgrew it switches the level to the atomic fallback.
 __global__ __launch_bounds__(1024) void k_bins_scan(unsigned int* __restrict__ bucket_count, int nbk,
                                                     unsigned long long* __restrict__ bucket_off,
                                                     unsigned long long* __restrict__ cursor,
                                                     const unsigned long long* __restrict__ rec_count,
-                                                    unsigned long long cap, int* __restrict__ mode) {
+                                                    unsigned long long seg_cap,
+                                                    unsigned long long* __restrict__ rec_total,
+                                                    int* __restrict__ mode) {
   __shared__ unsigned long long s[kBuckets];
   const int g = blockIdx.x;
   const int t = threadIdx.x;
@@ -39,10 +41,18 @@ __global__ __launch_bounds__(1024) void k_bins_scan(unsigned int* __restrict__ b
   const unsigned long long v = t < nbk ? bc[t] : 0ull;
   if (t < nbk) bc[t] = 0;  // ready for the next level (zero unless this one was binned)
   if (*mode != kModeBinned) return;  // (or another group overflowed)
-  if (rec_count[g] > cap) {
+  unsigned long long all = 0;
+  bool over = false;
+  for (int k = 0; k < kRecSegs; ++k) {
+    const unsigned long long c = rec_count[(g * kRecSegs + k) * kRecStride];
+    all += c;
+    over |= c > seg_cap;
+  }
+  if (over) {
     if (t == 0) atomicExch(mode, kModeOverflow);
     return;
   }
+  if (t == 0) rec_total[g] = all;
   bucket_off += static_cast<size_t>(g) * (kBuckets + 1);
   cursor += static_cast<size_t>(g) * kBuckets;
   s[t] = v;
@@ -63,9 +73,11 @@ __global__ __launch_bounds__(kThreads) void k_apply_overflow(LevelArgs A, long l
                                                              const int* __restrict__ mode) {
   if (*mode != kModeOverflow) return;
   const int ng = A.rec_groups > 1 ? A.rec_groups : 1;
-  for (int g = 0; g < ng; ++g) {
-    const unsigned long long n = A.rec_count[g] < A.rec_cap ? A.rec_count[g] : A.rec_cap;
-    const uint32_t* rec = A.rec + static_cast<size_t>(g) * A.rec_cap;
+  for (int gk = 0; gk < ng * kRecSegs; ++gk) {
+    const int g = gk / kRecSegs;
+    const unsigned long long c = A.rec_count[gk * kRecStride];
+    const unsigned long long n = c < A.rec_cap ? c : A.rec_cap;
+    const uint32_t* rec = A.rec + static_cast<size_t>(gk) * A.rec_cap;
     for (unsigned long long i = blockIdx.x * (unsigned long long)blockDim.x + threadIdx.x; i < n;
          i += (unsigned long long)gridDim.x * blockDim.x)
       apply_record<0>(A, acc, rec[i], static_cast<uint32_t>(g));
@@ -109,25 +121,42 @@ __device__ __forceinline__ unsigned int block_scan_1024(const unsigned int* v, u
 }
 
 // Partition of the records into buckets: a tile of 32768 records is sorted
-// by bucket in LDS, then every bucket's run is written out contiguously.
+// by bucket in LDS, then every bucket's run is written out contiguously.  The
+// records come in nseg segments (at most kRecSegs, seg_cap apart, their
+// counts kRecStride apart), whose tiles are numbered through.
 constexpr int kPartPerThread = 64;
 constexpr int kPartTile = kReduceThreads * kPartPerThread;
 
 __global__ __launch_bounds__(kReduceThreads) void k_partition(const uint32_t* __restrict__ rec,
                                                               const unsigned long long* __restrict__ rec_count,
+                                                              int nseg, unsigned long long seg_cap,
                                                               unsigned long long* __restrict__ cursor,
                                                               uint32_t* __restrict__ out,
                                                               const int* __restrict__ mode, int shift) {
   if (*mode != kModeBinned) return;
+  __shared__ unsigned long long s_tile0[kRecSegs + 1];  // tiles before each segment
   __shared__ uint32_t s_rec[kPartTile];
   __shared__ unsigned int s_hist[kBuckets];
   __shared__ unsigned int s_loc[kBuckets];
   __shared__ unsigned long long s_base[kBuckets];
   __shared__ unsigned int s_wsum[kReduceThreads / kWave];
-  const unsigned long long total = *rec_count;
-  for (unsigned long long lo = (unsigned long long)blockIdx.x * kPartTile; lo < total;
-       lo += (unsigned long long)gridDim.x * kPartTile) {
-    const int nt = static_cast<int>(total - lo < (unsigned long long)kPartTile ? total - lo : kPartTile);
+  if (threadIdx.x == 0) {
+    unsigned long long at = 0;
+    for (int k = 0; k < nseg; ++k) {
+      s_tile0[k] = at;
+      at += (rec_count[k * kRecStride] + kPartTile - 1) / kPartTile;
+    }
+    s_tile0[nseg] = at;
+  }
+  __syncthreads();
+  const unsigned long long tiles = s_tile0[nseg];
+  for (unsigned long long tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    int k0 = 0;
+    while (s_tile0[k0 + 1] <= tile) ++k0;
+    const unsigned long long total = rec_count[k0 * kRecStride];
+    const unsigned long long seg_lo = (tile - s_tile0[k0]) * kPartTile;
+    const unsigned long long lo = static_cast<unsigned long long>(k0) * seg_cap + seg_lo;
+    const int nt = static_cast<int>(total - seg_lo < (unsigned long long)kPartTile ? total - seg_lo : kPartTile);
     for (int b = threadIdx.x; b < kBuckets; b += blockDim.x) s_hist[b] = 0;
     __syncthreads();
     uint32_t r[kPartPerThread];

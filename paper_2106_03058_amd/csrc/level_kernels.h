@@ -186,10 +186,11 @@ struct LevelArgs {
   int* mode_out;                 // how the next frontier is formed (kMode*)
   // binned aggregation (binary32 batched calls; rec == nullptr: disabled);
   // records are kept per column group (rec_groups groups of rec_gw columns,
-  // 1 group: the whole row), group g's at rec + g * rec_cap
+  // 1 group: the whole row) and there in kRecSegs segments, segment k of
+  // group g at rec + (g * kRecSegs + k) * rec_cap
   uint32_t* rec;
-  unsigned long long* rec_count;  // this level's record count of each group
-  unsigned long long rec_cap;     // records per group
+  unsigned long long* rec_count;  // this level's record count of each segment, kRecStride apart
+  unsigned long long rec_cap;     // records per segment
   int rec_groups;
   uint32_t rec_gw;
   unsigned int* bucket_count;    // records per bucket of this level (kBuckets, kBuckets / 2 per group with two)
@@ -373,6 +374,12 @@ __device__ __forceinline__ double to_w(double v, double) { return v; }
 // g rec_gw on and the local cell is u * rec_gw + (c - g rec_gw).
 constexpr int kRecStage = 2 * kStage;  // 4-byte records per wave stage (both groups)
 constexpr uint32_t kRecCellMask = 0x7FFFFFFFu;
+// A group's records go to kRecSegs segments in turn, each with a counter on a
+// line of its own: returning atomics on one address serialise at 12 ns, and
+// the 622 thousand flushes of a dense transition level (637M records, 64
+// columns of 2^22 nodes) took 7.5 of its 9.5 ms on one counter.
+constexpr int kRecSegs = 16;
+constexpr int kRecStride = 16;  // words between counters (128 bytes)
 constexpr int kMaxRecGroups = 2;
 
 // kG: the groups of the launch (A.rec_groups of a binned level), a template
@@ -417,22 +424,24 @@ __device__ __forceinline__ void apply_record(const LevelArgs&, unsigned long lon
 // from its back (one atomic on each group's count; records beyond a group's
 // buffer are added with atomics).  Wave-uniform.
 template <int kG, typename Cell>
-__device__ __forceinline__ void stage_flush_records(uint32_t* stage, int& staged, Cell* acc) {
+__device__ __forceinline__ void stage_flush_records(uint32_t* stage, int& staged, int& seg, Cell* acc) {
   const LevelArgs& A = args_again();
   if constexpr (kG == 1) {
     if (staged == 0) return;
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     unsigned long long base = 0;
-    if (lane_id() == 0) base = atomicAdd(A.rec_count, static_cast<unsigned long long>(staged));
-    base = __shfl(base, 0);
+    if (lane_id() == 0) base = atomicAdd(A.rec_count + seg * kRecStride, static_cast<unsigned long long>(staged));
+    base = uniform(base);
+    uint32_t* const rec = A.rec + static_cast<size_t>(seg) * A.rec_cap;
     for (int i = lane_id(); i < staged; i += kWave) {
       if (base + i < A.rec_cap)
-        A.rec[base + i] = stage[i];
+        rec[base + i] = stage[i];
       else
         apply_record<kG>(A, acc, stage[i], 0u);
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     staged = 0;
+    seg = (seg + 1) & (kRecSegs - 1);
     return;
   }
   const int n0 = staged & 0xFFFF, n1 = staged >> 16;
@@ -443,7 +452,7 @@ __device__ __forceinline__ void stage_flush_records(uint32_t* stage, int& staged
   unsigned long long base = 0;
   if (lane < 2) {
     const int k = lane == 0 ? n0 : n1;
-    if (k > 0) base = atomicAdd(A.rec_count + lane, static_cast<unsigned long long>(k));
+    if (k > 0) base = atomicAdd(A.rec_count + (lane * kRecSegs + seg) * kRecStride, static_cast<unsigned long long>(k));
   }
   const unsigned long long base0 = __shfl(base, 0), base1 = __shfl(base, 1);
   for (int i = lane; i < total; i += kWave) {
@@ -452,12 +461,13 @@ __device__ __forceinline__ void stage_flush_records(uint32_t* stage, int& staged
     const uint32_t r = g ? stage[kRecStage - 1 - j] : stage[j];
     const unsigned long long at = (g ? base1 : base0) + static_cast<unsigned long long>(j);
     if (at < A.rec_cap)
-      A.rec[static_cast<size_t>(g) * A.rec_cap + at] = r;
+      A.rec[static_cast<size_t>(g * kRecSegs + seg) * A.rec_cap + at] = r;
     else
       apply_record<kG>(A, acc, r, g);
   }
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   staged = 0;
+  seg = (seg + 1) & (kRecSegs - 1);
 }
 
 // One sampled push of every lane that emits (a wave-uniform call) as a
@@ -467,7 +477,7 @@ __device__ __forceinline__ void stage_flush_records(uint32_t* stage, int& staged
 // is nearly full.
 template <int kG, typename Cell>
 __device__ __forceinline__ void emit_record(const LevelArgs& A, unsigned int* s_hist, uint32_t* stage, int& staged,
-                                            bool emit, uint32_t v, uint32_t c, bool neg, Cell* acc) {
+                                            int& seg, bool emit, uint32_t v, uint32_t c, bool neg, Cell* acc) {
   uint32_t rec = 0, g = 0;
   if (emit) {
     const RecCell rc = rec_cell<kG>(A, v, c);
@@ -483,12 +493,12 @@ __device__ __forceinline__ void emit_record(const LevelArgs& A, unsigned int* s_
     if (emit) stage[g ? kRecStage - 1 - (n1 + __popcll(m1 & lt)) : n0 + __popcll(m0 & lt)] = rec;
     const int k0 = n0 + __popcll(m0), k1 = n1 + __popcll(m1);
     staged = k0 | (k1 << 16);
-    if (k0 + k1 > kRecStage - kWave) stage_flush_records<kG>(stage, staged, acc);
+    if (k0 + k1 > kRecStage - kWave) stage_flush_records<kG>(stage, staged, seg, acc);
   } else {
     const unsigned long long m0 = wave_ballot(emit);
     if (emit) stage[staged + __popcll(m0 & lt)] = rec;
     staged += __popcll(m0);
-    if (staged > kRecStage - kWave) stage_flush_records<kG>(stage, staged, acc);
+    if (staged > kRecStage - kWave) stage_flush_records<kG>(stage, staged, seg, acc);
   }
 }
 
@@ -496,8 +506,8 @@ __device__ __forceinline__ void emit_record(const LevelArgs& A, unsigned int* s_
 // barrier) the block's bucket counts added to the level's.
 template <int kG, typename Cell>
 __device__ __forceinline__ void finish_records(const LevelArgs& A, unsigned int* s_hist, uint32_t* stage, int& staged,
-                                               Cell* acc) {
-  stage_flush_records<kG>(stage, staged, acc);
+                                               int& seg, Cell* acc) {
+  stage_flush_records<kG>(stage, staged, seg, acc);
   __syncthreads();
   for (int i = threadIdx.x; i < kBuckets; i += blockDim.x)
     if (s_hist[i]) atomicAdd(A.bucket_count + i, s_hist[i]);
@@ -955,6 +965,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
   BatchLds& B = s_batch[wave];
   uint64_t* stage = s_stage[wave];
   int staged = 0;  // wave-uniform
+  int seg = (blockIdx.x * kWaves + wave) & (kRecSegs - 1);  // wave-uniform: the next flush's record segment
 
   // per-lane and per-wave counts stay far below 2^32 in one launch (at least
   // 1024 waves share at most one candidate per arc and column of the level);
@@ -973,7 +984,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
   };
   auto emit_sampled = [&](bool emit, uint32_t v, uint32_t ec, bool eneg) {
     if (binned) {
-      emit_record<kG>(A, s_hist, reinterpret_cast<uint32_t*>(stage), staged, emit, v, ec, eneg, acc_next);
+      emit_record<kG>(A, s_hist, reinterpret_cast<uint32_t*>(stage), staged, seg, emit, v, ec, eneg, acc_next);
     } else {
       Delta delta{};
       if (emit) delta = P::theta_units(A.cp[ec], eneg);
@@ -1241,7 +1252,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
   };
   sample_loop<kMode>(A, B, refill, emit_sampled, served, w_cand, w_acc, w_runs);
   if (sparse) stage_flush(stage, staged, A.fout, A.cnt_out);
-  if (binned) finish_records<kG>(A, s_hist, reinterpret_cast<uint32_t*>(stage), staged, acc_next);
+  if (binned) finish_records<kG>(A, s_hist, reinterpret_cast<uint32_t*>(stage), staged, seg, acc_next);
   if (kServe) {  // flush the block's per-column sums
     __syncthreads();
     for (int i = threadIdx.x; i < kServeLdsSlots && i < A.slots; i += blockDim.x) serve_flush(serve_row(A, i), s_serve[i]);
@@ -1396,6 +1407,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
   BatchLds& B = s_batch[wave];
   uint64_t* stage = s_stage[wave];
   int staged = 0;  // wave-uniform
+  int seg = (blockIdx.x * kWaves + wave) & (kRecSegs - 1);  // wave-uniform: the next flush's record segment
   uint32_t w_cand = 0, w_acc = 0, w_runs = 0;
 
   // items [i0, i1) of this wave, from entry e on
@@ -1444,7 +1456,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
   };
   auto emit_sampled = [&](bool emit, uint32_t v, uint32_t c, bool neg) {
     if (binned) {
-      emit_record<kG>(A, s_hist, reinterpret_cast<uint32_t*>(stage), staged, emit, v, c, neg, acc_next);
+      emit_record<kG>(A, s_hist, reinterpret_cast<uint32_t*>(stage), staged, seg, emit, v, c, neg, acc_next);
       return;
     }
     Delta delta{};
@@ -1456,7 +1468,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
   };
   sample_loop<kMode>(A, B, refill, emit_sampled, served, w_cand, w_acc, w_runs);
   if (sparse) stage_flush(stage, staged, A.fout, A.cnt_out);
-  if (binned) finish_records<kG>(A, s_hist, reinterpret_cast<uint32_t*>(stage), staged, acc_next);
+  if (binned) finish_records<kG>(A, s_hist, reinterpret_cast<uint32_t*>(stage), staged, seg, acc_next);
   if (kServe) {  // flush the block's per-column sums
     __syncthreads();
     for (int i = threadIdx.x; i < kServeLdsSlots && i < A.slots; i += blockDim.x) serve_flush(serve_row(A, i), s_serve[i]);

@@ -604,7 +604,7 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
   int shift = kBinLog2;
   while (shift < 32 && (gcells > 0 ? gcells - 1ull : 0ull) >> shift >= nbk) ++shift;
   const long long nbins = static_cast<long long>(((gcells > 0 ? gcells : 1) - 1) >> kBinLog2) + 1;  // per group
-  unsigned long long rec_cap = 0;  // per group
+  unsigned long long rec_cap = 0, seg_cap = 0;  // per group, and per segment of a group
   // auto: no level can reach the record passes' cut when the call's pushes per
   // level stay below it, at most one per arc and column, and for the
   // column-stochastic a = 0, b = 1 about 1 / eps per column (||r||_1 <=
@@ -625,11 +625,12 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
       const unsigned long long v = std::strtoull(e, nullptr, 10);
       if (v > 0 && v < cap) cap = v;
     }
-    rec_cap = (cap + ng - 1) / ng;
+    seg_cap = (cap + ng * kRecSegs - 1) / (ng * kRecSegs);
+    rec_cap = seg_cap * kRecSegs;
     if (sc.rec[0].reserve(rec_cap * ng * sizeof(uint32_t), false, s) ||
         sc.rec[1].reserve(rec_cap * ng * sizeof(uint32_t), false, s) ||
         sc.bins.reserve(ng * (sizeof(unsigned int) * kBuckets + sizeof(unsigned long long) * (2 * kBuckets + 1) +
-                              sizeof(unsigned long long) * (AGP_MAX_LEVELS + 1) + static_cast<size_t>(nbins)) +
+                              sizeof(unsigned long long) * (kRecSegs * kRecStride * (L + 1) + 1) + static_cast<size_t>(nbins)) +
                             sizeof(unsigned long long) * (3 * nbins + 1),
                         true, s)) {
       sc.rec[0].release();  // not enough memory for the record buffers: atomics instead
@@ -640,18 +641,20 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
   }
   // bucket counts (group g's kBuckets / ng at g * kBuckets / ng); per group:
   // bucket offsets, partition cursors (kBuckets + 1 and kBuckets), per-level
-  // record counts (level i, group g at i * ng + g), deterministic-push flags
+  // record counts (level i, group g, segment k at ((i * ng + g) * kRecSegs + k)
+  // * kRecStride), the level's totals, deterministic-push flags
   // per bin; shared by the groups in turn: bin counts, offsets, cursors
   unsigned int* bucket_count = binned ? sc.bins.as<unsigned int>() : nullptr;
   unsigned long long* bucket_off = binned ? reinterpret_cast<unsigned long long*>(bucket_count + kBuckets * ng) : nullptr;
   unsigned long long* cursor = binned ? bucket_off + (kBuckets + 1) * ng : nullptr;
   unsigned long long* rec_counts = binned ? cursor + kBuckets * ng : nullptr;
-  unsigned long long* bin_count = binned ? rec_counts + (AGP_MAX_LEVELS + 1) * ng : nullptr;
+  unsigned long long* rec_total = binned ? rec_counts + static_cast<size_t>(L + 1) * ng * kRecSegs * kRecStride : nullptr;
+  unsigned long long* bin_count = binned ? rec_total + ng : nullptr;
   unsigned long long* bin_off = binned ? bin_count + nbins : nullptr;
   unsigned long long* bin_cur = binned ? bin_off + nbins + 1 : nullptr;
   uint8_t* det_bins = binned ? reinterpret_cast<uint8_t*>(bin_cur + nbins) : nullptr;  // any stale value is safe
   if (binned) {
-    AGP_HIP(hipMemsetAsync(rec_counts, 0, sizeof(unsigned long long) * (AGP_MAX_LEVELS + 1) * ng, s));
+    AGP_HIP(hipMemsetAsync(rec_counts, 0, sizeof(unsigned long long) * kRecSegs * kRecStride * (L + 1) * ng, s));
     AGP_HIP(hipMemsetAsync(bin_count, 0, sizeof(unsigned long long) * nbins, s));
     AGP_HIP(hipMemsetAsync(bucket_count, 0, sizeof(unsigned int) * kBuckets * ng, s));  // the dense path shares the buffer
   }
@@ -719,7 +722,7 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
   A.big_row = static_cast<uint32_t>(tune.big_row);
   A.rec = nullptr;
   A.rec_count = nullptr;
-  A.rec_cap = rec_cap;
+  A.rec_cap = seg_cap;
   A.rec_groups = ng;
   A.rec_gw = static_cast<uint32_t>(gw);
   A.det_bins_g = static_cast<unsigned long long>(nbins);
@@ -814,7 +817,7 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
       A.samp = samp_rows;
       A.samp_items = samp_items;
       A.big_cap = big_cap;
-      A.rec_count = bin_level ? rec_counts + static_cast<size_t>(i) * ng : nullptr;
+      A.rec_count = bin_level ? rec_counts + static_cast<size_t>(i) * ng * kRecSegs * kRecStride : nullptr;
       Cell* cur = acc[i & 1];
       Cell* nxt = acc[(i + 1) & 1];
       A.bin_est = nullptr;
@@ -836,19 +839,20 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
       if (bin_level) {
         uint32_t* r0 = sc.rec[0].as<uint32_t>();
         uint32_t* r1 = sc.rec[1].as<uint32_t>();
-        unsigned long long* rc = rec_counts + static_cast<size_t>(i) * ng;
-        k_bins_scan<<<ng, kBuckets, 0, s>>>(bucket_count, static_cast<int>(nbk), bucket_off, cursor, rc, rec_cap,
-                                            mode + i + 1);
+        unsigned long long* rc = A.rec_count;
+        k_bins_scan<<<ng, kBuckets, 0, s>>>(bucket_count, static_cast<int>(nbk), bucket_off, cursor, rc, seg_cap,
+                                            rec_total, mode + i + 1);
         k_apply_overflow<<<2048, kThreads, 0, s>>>(A, reinterpret_cast<long long*>(nxt), mode + i + 1);
         for (int gi = 0; gi < ng; ++gi) {  // each group's records in turn
           uint32_t* g0 = r0 + static_cast<size_t>(gi) * rec_cap;
           uint32_t* g1 = r1 + static_cast<size_t>(gi) * rec_cap;
-          k_partition<<<1024, kReduceThreads, 0, s>>>(g0, rc + gi, cursor + static_cast<size_t>(gi) * kBuckets, g1,
+          k_partition<<<1024, kReduceThreads, 0, s>>>(g0, rc + static_cast<size_t>(gi) * kRecSegs * kRecStride, kRecSegs,
+                                                      seg_cap, cursor + static_cast<size_t>(gi) * kBuckets, g1,
                                                       mode + i + 1, shift);
-          k_bin_count<<<2048, kReduceThreads, 0, s>>>(g1, rc + gi, bin_count, mode + i + 1, shift);
+          k_bin_count<<<2048, kReduceThreads, 0, s>>>(g1, rec_total + gi, bin_count, mode + i + 1, shift);
           k_bin_scan<<<static_cast<unsigned>(nbins / kScanChunk + 1), 1024, 0, s>>>(bin_count, nbins, bin_off,
                                                                                  bin_cur, mode + i + 1);
-          k_bin_scatter<<<2048, kReduceThreads, 0, s>>>(g1, rc + gi, bin_cur, g0, mode + i + 1, shift, bin_count,
+          k_bin_scatter<<<2048, kReduceThreads, 0, s>>>(g1, rec_total + gi, bin_cur, g0, mode + i + 1, shift, bin_count,
                                                         nbins);
           if (ng == 1)
             k_bin_sum<<<static_cast<unsigned>(nbins), kSumThreads, 0, s>>>(
@@ -1231,8 +1235,8 @@ int propagate_dense_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune,
           uint32_t* r0 = sc.rec[0].as<uint32_t>() + static_cast<size_t>(gi) * plan.rec_cap;
           uint32_t* r1 = sc.rec[1].as<uint32_t>() + static_cast<size_t>(gi) * plan.rec_cap;
           const unsigned long long* rc_g = D.rec_count + gi;
-          k_partition<<<1024, kReduceThreads, 0, s>>>(r0, rc_g, cursor + static_cast<size_t>(gi) * kBuckets, r1, md,
-                                                      shift);
+          k_partition<<<1024, kReduceThreads, 0, s>>>(r0, rc_g, 1, plan.rec_cap,
+                                                      cursor + static_cast<size_t>(gi) * kBuckets, r1, md, shift);
           k_bin_count<<<2048, kReduceThreads, 0, s>>>(r1, rc_g, bin_count, md, shift);
           k_bin_scan<<<static_cast<unsigned>(nbins / kScanChunk + 1), 1024, 0, s>>>(bin_count, nbins, bin_off,
                                                                                  bin_cur, md);
