@@ -234,6 +234,23 @@ __device__ __forceinline__ const LevelArgs& args_again() {
   return *(const LevelArgs*)p;
 }
 
+// An argument that the draw loop reads in every step, kept in scalar registers
+// (read again from the argument segment, each use is a scalar load that the
+// wave waits for).
+template <typename V>
+__device__ __forceinline__ V pinned(V v) {
+  __asm__ volatile("" : "+s"(v));
+  return v;
+}
+
+template <typename V>
+__device__ __forceinline__ const V* pinned(const V* p) {  // (device memory, so that its loads stay global ones)
+  using Global = const V __attribute__((address_space(1)));
+  Global* g = (Global*)p;
+  __asm__ volatile("" : "+s"(g));
+  return (const V*)g;
+}
+
 // Position of node v in a query's table, claiming it if v is not there yet
 // (*first: v was not there); ~0u when the table is too full.  mask == ~0u:
 // a direct table of n entries (position base + v); else 2^k = mask + 1
@@ -387,13 +404,24 @@ constexpr int kMaxRecGroups = 2;
 struct RecCell {
   uint32_t g, cell;
 };
+// What the cell of a record is made from: the row stride (one group; records
+// are kept on row-major cells only) or the columns of a group, and the
+// buckets' size.
+struct RecShape {
+  uint32_t width;
+  int shift;
+};
 template <int kG>
-__device__ __forceinline__ RecCell rec_cell(const LevelArgs& A, uint32_t u, uint32_t c) {
+__device__ __forceinline__ RecShape rec_shape(const LevelArgs& A) {
+  return RecShape{kG > 1 ? A.rec_gw : static_cast<uint32_t>(A.su), A.bucket_shift};
+}
+template <int kG>
+__device__ __forceinline__ RecCell rec_cell(const RecShape& R, uint32_t u, uint32_t c) {
   if constexpr (kG > 1) {
-    const uint32_t g = c >= A.rec_gw ? 1u : 0u;
-    return RecCell{g, u * A.rec_gw + (c - g * A.rec_gw)};
+    const uint32_t g = c >= R.width ? 1u : 0u;
+    return RecCell{g, u * R.width + (c - g * R.width)};
   } else {
-    return RecCell{0u, u * static_cast<uint32_t>(A.su) + c * static_cast<uint32_t>(A.sc)};
+    return RecCell{0u, u * R.width + c};
   }
 }
 
@@ -454,7 +482,7 @@ __device__ __forceinline__ void stage_flush_records(uint32_t* stage, int& staged
     const int k = lane == 0 ? n0 : n1;
     if (k > 0) base = atomicAdd(A.rec_count + (lane * kRecSegs + seg) * kRecStride, static_cast<unsigned long long>(k));
   }
-  const unsigned long long base0 = __shfl(base, 0), base1 = __shfl(base, 1);
+  const unsigned long long base0 = uniform(base), base1 = uniform(__shfl(base, 1));
   for (int i = lane; i < total; i += kWave) {
     const uint32_t g = i < n0 ? 0u : 1u;
     const int j = i - (g ? n0 : 0);
@@ -476,14 +504,14 @@ __device__ __forceinline__ void stage_flush_records(uint32_t* stage, int& staged
 // the front of the stage, group 1 from its back); the stage goes out when it
 // is nearly full.
 template <int kG, typename Cell>
-__device__ __forceinline__ void emit_record(const LevelArgs& A, unsigned int* s_hist, uint32_t* stage, int& staged,
+__device__ __forceinline__ void emit_record(const RecShape& R, unsigned int* s_hist, uint32_t* stage, int& staged,
                                             int& seg, bool emit, uint32_t v, uint32_t c, bool neg, Cell* acc) {
   uint32_t rec = 0, g = 0;
   if (emit) {
-    const RecCell rc = rec_cell<kG>(A, v, c);
+    const RecCell rc = rec_cell<kG>(R, v, c);
     g = rc.g;
     rec = rc.cell | (neg ? 0x80000000u : 0u);
-    atomicAdd(&s_hist[g * (kBuckets / kMaxRecGroups) + (rc.cell >> A.bucket_shift)], 1u);
+    atomicAdd(&s_hist[g * (kBuckets / kMaxRecGroups) + (rc.cell >> R.shift)], 1u);
   }
   const unsigned long long lt = (1ull << lane_id()) - 1ull;
   if constexpr (kG > 1) {
@@ -516,7 +544,7 @@ __device__ __forceinline__ void finish_records(const LevelArgs& A, unsigned int*
 // a deterministic push's mark on its destination bin (binned levels)
 template <int kG>
 __device__ __forceinline__ void mark_det_bin(const LevelArgs& A, uint8_t* det_bins, uint32_t v, uint32_t c) {
-  const RecCell rc = rec_cell<kG>(A, v, c);
+  const RecCell rc = rec_cell<kG>(rec_shape<kG>(A), v, c);
   det_bins[rc.g * A.det_bins_g + (rc.cell >> kBinLog2)] = 1;
 }
 
@@ -713,18 +741,13 @@ __device__ __forceinline__ void push_atomic(const LevelArgs& A, uint64_t* stage,
 // of the first kItemMap items; returns the items of the whole batch.
 __device__ __forceinline__ uint32_t queue_items(BatchLds& B, uint32_t iwork) {
   const int lane = lane_id();
-  uint32_t iinc = iwork;
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    const uint32_t t = __shfl_up(iinc, off);
-    if (lane >= off) iinc += t;
-  }
+  const uint32_t iinc = wave_scan(iwork);
   B.ioff[lane] = iinc - iwork;
   const int j1 = static_cast<int>(iinc < kItemMap ? iinc : kItemMap);
   for (int j = static_cast<int>(iinc - iwork < kItemMap ? iinc - iwork : kItemMap); j < j1; ++j)
     B.item_entry[j] = static_cast<uint8_t>(lane);
   if (lane == kWave - 1) B.ioff[kBatch] = iinc;
-  return __builtin_amdgcn_readlane(iinc, kWave - 1);
+  return last_lane(iinc);
 }
 
 // v < fl(p / q) for v in [0, 1) and factors p, q > 0: fl(p / q) is p / q and
@@ -761,6 +784,8 @@ __device__ __forceinline__ void sample_loop(const LevelArgs& A, BatchLds& B, Ref
   uint32_t it_cand = 0, it_acc = 0, it_runs = 0;
   int64_t rpu = 0;
   double cv = 0.0, dstart = 1.0, th = 0.0;
+  const uint32_t* const col = pinned(A.col);
+  const double* const arcfac = kMode == kBatchAP ? pinned(A.arcfac) : nullptr;
   const double* da = A.da;
   SkipTable tab;
 
@@ -837,7 +862,7 @@ __device__ __forceinline__ void sample_loop(const LevelArgs& A, BatchLds& B, Ref
         // row start, from the entry's setup); the group end only when the
         // run stops there
         if (!(first && dstart > 0.0))
-          dstart = A.arcfac != nullptr ? A.arcfac[rpu + s] : da[A.nd[rpu + s]];
+          dstart = arcfac != nullptr ? arcfac[rpu + s] : da[A.nd[rpu + s]];
         const double num = cv * dstart;
         const double pr = num / th;
         if (!(pr * static_cast<double>(wend - s) <= kMergeCandidates)) {
@@ -866,10 +891,10 @@ __device__ __forceinline__ void sample_loop(const LevelArgs& A, BatchLds& B, Ref
         const int64_t arc = rpu + cand;
         // the neighbour is loaded beside its factor degree, before the
         // acceptance test needs it (one round trip instead of two)
-        const uint32_t va = A.col[arc];
+        const uint32_t va = col[arc];
         bool accept = true;  // a = 0: the ratio is 1 and every uniform is below it
         if (!azero)
-          accept = below_ratio(unit_double(o.z, o.w), A.arcfac != nullptr ? A.arcfac[arc] : da[A.nd[arc]], dstart);
+          accept = below_ratio(unit_double(o.z, o.w), arcfac != nullptr ? arcfac[arc] : da[A.nd[arc]], dstart);
         if (accept) {
           if (kServe) ++it_acc;
           v = va;
@@ -898,13 +923,8 @@ __device__ __forceinline__ bool defer_slots(unsigned long long* ctr, unsigned lo
   if (mask == 0ull) return false;
   if ((__hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> kBigShift) >= cap) return false;
   const int lane = lane_id();
-  unsigned long long inc = want ? work : 0ull;
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const unsigned long long t = __shfl_up(inc, o);
-    if (lane >= o) inc += t;
-  }
-  const unsigned long long total = uniform(__shfl(inc, kWave - 1));
+  const unsigned long long inc = wave_scan(want ? work : 0ull);
+  const unsigned long long total = last_lane(inc);
   unsigned long long old = 0;
   if (lane == 0) old = atomic_add_ret(ctr, (static_cast<unsigned long long>(__popcll(mask)) << kBigShift) | total);
   old = uniform(old);
@@ -982,9 +1002,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
   auto emit_atomic = [&](bool emit, uint32_t v, uint32_t ec, const Delta& delta) {
     push_atomic<T, kMode>(A, stage, staged, sparse, emit, v, ec, delta, acc_next);
   };
+  const RecShape shape{pinned(rec_shape<kG>(A).width), pinned(A.bucket_shift)};
   auto emit_sampled = [&](bool emit, uint32_t v, uint32_t ec, bool eneg) {
     if (binned) {
-      emit_record<kG>(A, s_hist, reinterpret_cast<uint32_t*>(stage), staged, seg, emit, v, ec, eneg, acc_next);
+      emit_record<kG>(shape, s_hist, reinterpret_cast<uint32_t*>(stage), staged, seg, emit, v, ec, eneg, acc_next);
     } else {
       Delta delta{};
       if (emit) delta = P::theta_units(A.cp[ec], eneg);
@@ -1202,14 +1223,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
     }
     long long dtot = 0;  // deterministic pushes of the batch
     if (wave_any(dwork != 0)) {
-      long long dinc = dwork;
-#pragma unroll
-      for (int off = 1; off < kWave; off <<= 1) {
-        const long long td = __shfl_up(dinc, off);
-        if (lane >= off) dinc += td;
-      }
-      B.doff[lane] = dinc - dwork;
-      dtot = static_cast<long long>(uniform(static_cast<unsigned long long>(__shfl(dinc, kWave - 1))));
+      const unsigned long long dinc = wave_scan(static_cast<unsigned long long>(dwork));
+      B.doff[lane] = static_cast<long long>(dinc) - dwork;
+      dtot = static_cast<long long>(last_lane(dinc));
     }
     B.rp[lane] = erp;
     B.cv[lane] = ecv;
@@ -1454,9 +1470,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
     e += static_cast<unsigned long long>(k);
     return true;
   };
+  const RecShape shape{pinned(rec_shape<kG>(A).width), pinned(A.bucket_shift)};
   auto emit_sampled = [&](bool emit, uint32_t v, uint32_t c, bool neg) {
     if (binned) {
-      emit_record<kG>(A, s_hist, reinterpret_cast<uint32_t*>(stage), staged, seg, emit, v, c, neg, acc_next);
+      emit_record<kG>(shape, s_hist, reinterpret_cast<uint32_t*>(stage), staged, seg, emit, v, c, neg, acc_next);
       return;
     }
     Delta delta{};
@@ -1563,7 +1580,7 @@ __device__ __forceinline__ void compact_flush(const uint16_t* stage, int& staged
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   unsigned long long base = 0;
   if (lane_id() == 0) base = atomicAdd(cnt, static_cast<unsigned long long>(staged));
-  base = __shfl(base, 0);
+  base = uniform(base);
   for (int i = lane_id(); i < staged; i += kWave) {
     const uint32_t a = r0 + stage[i];  // < C + kCompactSeg
     uint32_t c = 0, q = 0;
