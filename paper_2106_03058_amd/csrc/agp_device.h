@@ -27,6 +27,11 @@ constexpr double kMergeCandidates = 4.0;
 // select and a compare on the vector unit).
 __device__ __forceinline__ unsigned long long wave_ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 __device__ __forceinline__ bool wave_any(bool p) { return wave_ballot(p) != 0ull; }
+// n plus the lanes of mask below this one.
+__device__ __forceinline__ uint32_t lanes_below(unsigned long long mask, uint32_t n = 0) {
+  return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
+                                   __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), n));
+}
 // A wave-uniform value the compiler cannot see to be one, in scalar registers.
 __device__ __forceinline__ uint32_t uniform(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ unsigned long long uniform(unsigned long long v) {
@@ -354,8 +359,8 @@ __device__ __forceinline__ void stage_push(uint64_t* stage, int& staged, uint64_
                                            uint64_t* __restrict__ list,
                                            unsigned long long* __restrict__ count) {
   const unsigned long long mask = wave_ballot(pred);
-  if (pred) stage[staged + __popcll(mask & ((1ull << lane_id()) - 1ull))] = item;
-  staged += __popcll(mask);
+  if (pred) stage[lanes_below(mask, staged)] = item;
+  staged = static_cast<int>(uniform(static_cast<uint32_t>(staged + __popcll(mask))));
   if (staged > kCap - kWave) stage_flush(stage, staged, list, count);
 }
 

@@ -445,6 +445,12 @@ __device__ __forceinline__ void apply_record(const LevelArgs& A, long long* acc,
 template <int kG>
 __device__ __forceinline__ void apply_record(const LevelArgs&, unsigned long long*, uint32_t, uint32_t) {}
 
+// The column word of a batch's entry: the column, the residue's sign, and (a
+// batch's own) whether a = 0 and the log2 of the windows per work item.
+constexpr uint32_t kBatchNeg = 1u << 31, kBatchAZero = 1u << 30;
+constexpr int kBatchShiftBit = 27;  // three bits
+constexpr uint32_t kBatchCol = (1u << kBatchShiftBit) - 1u;
+
 // Staged record counts of a wave: the count (one group), or group 0's in the
 // low 16 bits and group 1's in the high 16 bits of one wave-uniform int.
 //
@@ -505,27 +511,26 @@ __device__ __forceinline__ void stage_flush_records(uint32_t* stage, int& staged
 // is nearly full.
 template <int kG, typename Cell>
 __device__ __forceinline__ void emit_record(const RecShape& R, unsigned int* s_hist, uint32_t* stage, int& staged,
-                                            int& seg, bool emit, uint32_t v, uint32_t c, bool neg, Cell* acc) {
+                                            int& seg, bool emit, uint32_t v, uint32_t cw, Cell* acc) {
   uint32_t rec = 0, g = 0;
   if (emit) {
-    const RecCell rc = rec_cell<kG>(R, v, c);
+    const RecCell rc = rec_cell<kG>(R, v, cw & kBatchCol);
     g = rc.g;
-    rec = rc.cell | (neg ? 0x80000000u : 0u);
+    rec = rc.cell | (cw & kBatchNeg);
     atomicAdd(&s_hist[g * (kBuckets / kMaxRecGroups) + (rc.cell >> R.shift)], 1u);
   }
-  const unsigned long long lt = (1ull << lane_id()) - 1ull;
   if constexpr (kG > 1) {
     const int n0 = staged & 0xFFFF, n1 = staged >> 16;
     const unsigned long long m1 = wave_ballot(emit && g != 0);
     const unsigned long long m0 = wave_ballot(emit) & ~m1;
-    if (emit) stage[g ? kRecStage - 1 - (n1 + __popcll(m1 & lt)) : n0 + __popcll(m0 & lt)] = rec;
+    if (emit) stage[g ? kRecStage - 1 - static_cast<int>(lanes_below(m1, n1)) : static_cast<int>(lanes_below(m0, n0))] = rec;
     const int k0 = n0 + __popcll(m0), k1 = n1 + __popcll(m1);
-    staged = k0 | (k1 << 16);
+    staged = static_cast<int>(uniform(static_cast<uint32_t>(k0 | (k1 << 16))));
     if (k0 + k1 > kRecStage - kWave) stage_flush_records<kG>(stage, staged, seg, acc);
   } else {
     const unsigned long long m0 = wave_ballot(emit);
-    if (emit) stage[staged + __popcll(m0 & lt)] = rec;
-    staged += __popcll(m0);
+    if (emit) stage[lanes_below(m0, staged)] = rec;
+    staged = static_cast<int>(uniform(static_cast<uint32_t>(staged + __popcll(m0))));
     if (staged > kRecStage - kWave) stage_flush_records<kG>(stage, staged, seg, acc);
   }
 }
@@ -652,10 +657,6 @@ struct BatchLds {
   uint32_t u[kBatch], c[kBatch], d[kBatch], J[kBatch];
   uint8_t item_entry[kItemMap];  // the entry of each of the batch's first kItemMap work items
 };
-// (the columns of a batched call share one key, held in scalar registers)
-constexpr uint32_t kBatchNeg = 1u << 31, kBatchAZero = 1u << 30;
-constexpr int kBatchShiftBit = 27;  // three bits
-constexpr uint32_t kBatchCol = (1u << kBatchShiftBit) - 1u;
 static_assert(kMaxItemShift < 8, "three bits hold the shift");
 // columns of one level launch at most (the column index leaves those bits free)
 constexpr int32_t kMaxTileColumns = static_cast<int32_t>(kBatchCol);
@@ -762,106 +763,102 @@ __device__ __forceinline__ bool below_ratio(double v, double p, double q) {
 
 // Draws the queued work items of the batches that refill sets up:
 // refill(it_next, it_total) puts the next batch in B and its queue of items
-// [it_next, it_total), or returns false when none is left; emit(pushed, v, c,
-// neg) makes a sampled push of every lane that has one (all lanes
-// together); served(c, candidates, accepted, runs) gets a finished item's
-// counts (server).  w_*: wave-uniform counts (batched calls).
+// [it_next, it_total), or returns false when none is left; emit(pushed, v, cw)
+// makes a sampled push of every lane that has one to node v in the column of
+// word cw (all lanes together); served(c, candidates, accepted, runs) gets a
+// finished item's counts (server).  w_*: wave-uniform counts (batched calls).
+//
+// A lane's state is a few integers, compared where a step needs to know it
+// (kept as flags, every one of them was a handful of lane-mask operations per
+// step): the item's windows [s, rend), the run in progress from s up to run_end
+// with its next position pos.  A lane is idle when s >= rend and between runs
+// when run_end == s; the lanes all draw in every step, an idle one with pos =
+// run_end, past which no skip is a candidate.
+constexpr int kRefillIdle = 8;  // idle lanes from which items are taken: fewer steps read the queue
 template <int kMode, typename Refill, typename Emit, typename Served>
 __device__ __forceinline__ void sample_loop(const LevelArgs& A, BatchLds& B, Refill&& refill, Emit&& emit_sampled,
                                             Served&& served, uint32_t& w_cand, uint32_t& w_acc, uint32_t& w_runs) {
   constexpr bool kServe = kMode == kPerColumn;
-  const int lane = lane_id();
-  const unsigned long long lt_mask = (1ull << lane) - 1ull;
+  constexpr uint32_t kFirstRun = ~0u;  // in t: the item has no run yet
   uint32_t it_next = 0, it_total = 0;  // wave-uniform: queue of the loaded batch
   bool more = true;                    // wave-uniform: refill may have another batch
 
-  // lane state: the sampled work item in progress
-  bool active = false, need_run = false, neg = false;
-  bool azero = kMode == kBatchAZ;  // (a constant but for the server)
-  uint32_t u = 0, c = 0, s = 0, rend = 0, run_end = 0, pos = 0, t = 0, ctr3 = 0;
-  uint32_t key0 = kServe ? 0u : __builtin_amdgcn_readfirstlane(A.lp->key0);
-  uint32_t key1 = kServe ? 0u : __builtin_amdgcn_readfirstlane(A.lp->key1);
+  uint32_t u = 0, cw = 0, s = 0, rend = 0, run_end = 0, pos = 0, t = 0, ctr3 = 0;
+  uint32_t key0 = kServe ? 0u : uniform(A.lp->key0);
+  uint32_t key1 = kServe ? 0u : uniform(A.lp->key1);
   uint32_t it_cand = 0, it_acc = 0, it_runs = 0;
   int64_t rpu = 0;
   double cv = 0.0, dstart = 1.0, th = 0.0;
   const uint32_t* const col = pinned(A.col);
   const double* const arcfac = kMode == kBatchAP ? pinned(A.arcfac) : nullptr;
   const double* da = A.da;
-  SkipTable tab;
+  SkipTable tab{};
+  // a = 0 (a constant but for the server)
+  auto azero = [&]() { return kServe ? (cw & kBatchAZero) != 0 : kMode == kBatchAZ; };
 
   for (;;) {
-    // (a) a lane whose item has no window left becomes idle
-    if (active && need_run && s >= rend) {
-      active = false;
-      if (kServe) served(c, it_cand, it_acc, it_runs);
-    }
-    // (b) the queue is empty and a lane is idle: set up the next batch
-    if (more && it_next >= it_total && wave_any(!active)) more = refill(it_next, it_total);
-    // (c) idle lanes take sampled work items from the queue
-    {
-      const unsigned long long idle = wave_ballot(!active);
-      if (!active) {
-        const uint32_t it = it_next + static_cast<uint32_t>(__popcll(idle & lt_mask));
-        if (it < it_total) {
+    unsigned long long idle = wave_ballot(s >= rend);
+    if (__popcll(idle) >= kRefillIdle) {
+      // the queue is empty: set up the next batch
+      if (more && it_next >= it_total) more = refill(it_next, it_total);
+      if (it_next < it_total) {  // idle lanes take work items
+        const uint32_t it = lanes_below(idle, it_next);
+        if (s >= rend && it < it_total) {
           const int e = it < kItemMap ? B.item_entry[it] : batch_find<uint32_t>(B.ioff, it);
           const uint32_t il = it - B.ioff[e];
           u = B.u[e];
-          const uint32_t cw = B.c[e];
-          c = cw & kBatchCol;
+          cw = B.c[e];
           rpu = B.rp[e];
-          neg = (cw & kBatchNeg) != 0;
           const uint32_t J = B.J[e], d = B.d[e];
           ctr3 = B.ctr3[e];
           if (kServe) {
-            const ColParams& cp = A.cp[c];
-            azero = (cw & kBatchAZero) != 0;
+            const ColParams& cp = A.cp[cw & kBatchCol];
             key0 = cp.key0;
             key1 = cp.key1;
             da = cp.da;
           }
-          if (!azero) {
-            cv = B.cv[e];
-            th = B.th[e];
-          }
           const uint32_t shift = (cw >> kBatchShiftBit) & 7u;
-          const uint32_t nwin = ((d - 1) >> kSegLog2) - (J >> kSegLog2) + 1;
-          const uint32_t w0 = il << shift;
-          const uint32_t w1 = (w0 + (1u << shift)) < nwin ? w0 + (1u << shift) : nwin;
-          const uint32_t ws = ((J >> kSegLog2) + w0) << kSegLog2;
-          const uint32_t we = ((J >> kSegLog2) + w1) << kSegLog2;
+          const uint32_t w0 = (J >> kSegLog2) + (il << shift);
+          const uint32_t ws = w0 << kSegLog2, we = (w0 + (1u << shift)) << kSegLog2;
           s = ws > J ? ws : J;
           rend = we < d ? we : d;
-          if (azero)
+          run_end = pos = s;
+          t = kFirstRun;
+          if (azero()) {
             tab = make_skip_table(B.p0[e]);
-          else  // the first run's factor when the entry's setup has it (else 0)
-            dstart = il == 0 ? B.p0[e] : 0.0;
-          run_end = 0;  // (the item has no run yet)
-          active = true;
-          need_run = true;
-          it_cand = it_acc = it_runs = 0;
+          } else {
+            cv = B.cv[e];
+            th = B.th[e];
+            dstart = il == 0 ? B.p0[e] : 0.0;  // the first run's factor when the entry's setup has it (else 0)
+          }
+          if (kServe) it_cand = it_acc = it_runs = 0;
         }
+        it_next = uniform(it_next + static_cast<uint32_t>(__popcll(idle)));
+        if (it_next > it_total) it_next = it_total;
+        idle = wave_ballot(s >= rend);
       }
-      it_next += static_cast<uint32_t>(__popcll(idle));
-      if (it_next > it_total) it_next = it_total;
+      if (idle == ~0ull) {
+        if (!more && it_next >= it_total) break;  // nothing queued, no batch left
+        continue;
+      }
     }
-    if (!wave_any(active)) {
-      if (!more) break;  // queue empty (no idle lane took an item), no batch left
-      continue;
-    }
-    // (d) a run: the rest of the current window, or (a > 0) of its degree
-    // group unless few candidates are expected over the rest of the window
-    if (!kServe) w_runs += static_cast<uint32_t>(__popcll(wave_ballot(active && need_run)));
-    if (active && need_run) {
-      if (kServe) ++it_runs;
-      const uint32_t wnext = ((s >> kSegLog2) + 1u) << kSegLog2;
-      const uint32_t wend = wnext < rend ? wnext : rend;
-      const bool first = run_end == 0;
+    // a run: the rest of the current window, or (a > 0) of its degree group
+    // unless few candidates are expected over the rest of the window
+    const bool fresh = run_end == s;  // (an idle lane's run stays empty)
+    const uint32_t wnext = (s | (kSeg - 1u)) + 1u;
+    const uint32_t wend = wnext < rend ? wnext : rend;
+    if constexpr (kMode == kBatchAZ) {
+      const uint32_t end = wend > s ? wend : s;
+      run_end = fresh ? end : run_end;
+      t = fresh ? 0u : t;
+    } else if (fresh && s < rend) {
       run_end = wend;
-      if (!azero) {
+      if (kServe) ++it_runs;
+      if (!azero()) {
         // the factor of the run's first arc (for an item's first run at the
         // row start, from the entry's setup); the group end only when the
         // run stops there
-        if (!(first && dstart > 0.0))
+        if (!(t == kFirstRun && dstart > 0.0))
           dstart = arcfac != nullptr ? arcfac[rpu + s] : da[A.nd[rpu + s]];
         const double num = cv * dstart;
         const double pr = num / th;
@@ -871,44 +868,37 @@ __device__ __forceinline__ void sample_loop(const LevelArgs& A, BatchLds& B, Ref
         }
         tab = make_skip_table(pr);
       }
-      pos = s;
       t = 0;
-      need_run = false;
     }
-    // (e) one draw of the run's chain
-    bool emit = false, cand_hit = false;
+    // one draw of the run's chain
+    const U4 o = kServe ? philox4x32_10(t, s, u, ctr3, key0, key1) : philox4x32_10_skey(t, s, u, ctr3, key0, key1);
+    const uint32_t cand = pos + geometric_skip64(tab, unit_double(o.x, o.y));
+    const bool hit = cand < run_end;
+    bool emit = hit;
     uint32_t v = 0;
-    if (active && !need_run) {
-      const U4 o = kServe ? philox4x32_10(t, s, u, ctr3, key0, key1) : philox4x32_10_skey(t, s, u, ctr3, key0, key1);
-      const double V = unit_double(o.x, o.y);
-      const uint32_t cand = pos + geometric_skip64(tab, V);
-      if (cand >= run_end) {
-        s = run_end;
-        need_run = true;
-      } else {
-        cand_hit = true;
-        if (kServe) ++it_cand;
-        const int64_t arc = rpu + cand;
-        // the neighbour is loaded beside its factor degree, before the
-        // acceptance test needs it (one round trip instead of two)
-        const uint32_t va = col[arc];
-        bool accept = true;  // a = 0: the ratio is 1 and every uniform is below it
-        if (!azero)
-          accept = below_ratio(unit_double(o.z, o.w), arcfac != nullptr ? arcfac[arc] : da[A.nd[arc]], dstart);
-        if (accept) {
-          if (kServe) ++it_acc;
-          v = va;
-          emit = true;
-        }
-        pos = cand + 1;
-        ++t;
-      }
+    if (hit) {
+      const int64_t arc = rpu + cand;
+      // the neighbour is loaded beside its factor degree, before the
+      // acceptance test needs it (one round trip instead of two)
+      v = col[arc];
+      if (!azero())  // (a = 0: the ratio is 1 and every uniform is below it)
+        emit = below_ratio(unit_double(o.z, o.w), arcfac != nullptr ? arcfac[arc] : da[A.nd[arc]], dstart);
     }
     if (!kServe) {
-      w_cand += static_cast<uint32_t>(__popcll(wave_ballot(cand_hit)));
-      w_acc += static_cast<uint32_t>(__popcll(wave_ballot(emit)));
+      const uint32_t hits = static_cast<uint32_t>(__popcll(wave_ballot(hit)));
+      w_cand += hits;
+      // every active lane without a candidate ends its run
+      w_runs += static_cast<uint32_t>(kWave - __popcll(idle)) - hits;
+      w_acc += kMode == kBatchAZ ? hits : static_cast<uint32_t>(__popcll(wave_ballot(emit)));
+    } else {
+      it_cand += hit ? 1u : 0u;
+      it_acc += emit ? 1u : 0u;
+      if (!hit && s < rend && run_end >= rend) served(cw & kBatchCol, it_cand, it_acc, it_runs);  // the item's end
     }
-    emit_sampled(emit, v, c, neg);
+    s = hit ? s : run_end;
+    pos = hit ? cand + 1u : run_end;
+    t = hit ? t + 1u : t;
+    emit_sampled(emit, v, cw);
   }
 }
 
@@ -1003,12 +993,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
     push_atomic<T, kMode>(A, stage, staged, sparse, emit, v, ec, delta, acc_next);
   };
   const RecShape shape{pinned(rec_shape<kG>(A).width), pinned(A.bucket_shift)};
-  auto emit_sampled = [&](bool emit, uint32_t v, uint32_t ec, bool eneg) {
+  auto emit_sampled = [&](bool emit, uint32_t v, uint32_t cw) {
     if (binned) {
-      emit_record<kG>(shape, s_hist, reinterpret_cast<uint32_t*>(stage), staged, seg, emit, v, ec, eneg, acc_next);
+      emit_record<kG>(shape, s_hist, reinterpret_cast<uint32_t*>(stage), staged, seg, emit, v, cw, acc_next);
     } else {
+      const uint32_t ec = cw & kBatchCol;
       Delta delta{};
-      if (emit) delta = P::theta_units(A.cp[ec], eneg);
+      if (emit) delta = P::theta_units(A.cp[ec], (cw & kBatchNeg) != 0);
       emit_atomic(emit, v, ec, delta);
     }
   };
@@ -1471,13 +1462,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
     return true;
   };
   const RecShape shape{pinned(rec_shape<kG>(A).width), pinned(A.bucket_shift)};
-  auto emit_sampled = [&](bool emit, uint32_t v, uint32_t c, bool neg) {
+  auto emit_sampled = [&](bool emit, uint32_t v, uint32_t cw) {
     if (binned) {
-      emit_record<kG>(shape, s_hist, reinterpret_cast<uint32_t*>(stage), staged, seg, emit, v, c, neg, acc_next);
+      emit_record<kG>(shape, s_hist, reinterpret_cast<uint32_t*>(stage), staged, seg, emit, v, cw, acc_next);
       return;
     }
+    const uint32_t c = cw & kBatchCol;
     Delta delta{};
-    if (emit) delta = P::theta_units(A.cp[c], neg);
+    if (emit) delta = P::theta_units(A.cp[c], (cw & kBatchNeg) != 0);
     push_atomic<T, kMode>(A, stage, staged, sparse, emit, v, c, delta, acc_next);
   };
   auto served = [&](uint32_t c, uint32_t cand, uint32_t acc, uint32_t runs) {
