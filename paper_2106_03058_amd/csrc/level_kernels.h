@@ -761,6 +761,21 @@ __device__ __forceinline__ bool below_ratio(double v, double p, double q) {
   return v < p / q;
 }
 
+// Sum of v over the lanes before this one in its group of eight.
+__device__ __forceinline__ uint32_t group_scan_before(uint32_t v) {
+  const uint32_t sub = lane_id() & 7;
+  // (moves outside the selections: under one, its lanes alone would take part)
+  uint32_t m = lane_move<0x111, 0xf>(v);
+  uint32_t x = sub >= 1 ? m : 0u;  // v of the lane before
+  m = lane_move<0x111, 0xf>(x);
+  x += sub >= 1 ? m : 0u;
+  m = lane_move<0x112, 0xf>(x);
+  x += sub >= 2 ? m : 0u;
+  m = lane_move<0x114, 0xf>(x);
+  x += sub >= 4 ? m : 0u;
+  return x;
+}
+
 // Draws the queued work items of the batches that refill sets up:
 // refill(it_next, it_total) puts the next batch in B and its queue of items
 // [it_next, it_total), or returns false when none is left; emit(pushed, v, cw)
@@ -774,10 +789,24 @@ __device__ __forceinline__ bool below_ratio(double v, double p, double q) {
 // with its next position pos.  A lane is idle when s >= rend and between runs
 // when run_end == s; the lanes all draw in every step, an idle one with pos =
 // run_end, past which no skip is a candidate.
-constexpr int kRefillIdle = 8;  // idle lanes from which items are taken: fewer steps read the queue
+//
+// group (levels with few entries): the eight lanes of a group take one item
+// together and make eight draws of its run in a step.  Draw t of a run is a
+// function of the run and t alone, so only the positions chain: a scan of the
+// skips over the group.  A lane's chain of up to 64 draws, a memory round trip
+// each, had been the length of a small level.  (refill may set it with a wave's
+// first batch, when every lane is idle.)
+constexpr int kGroup = 8;
+constexpr unsigned long long kGroupItems = 16;  // k_samp_big: items per wave up to which groups draw
+// Idle lanes from which items are taken on large levels with a = 0: fewer steps
+// read the queue (8 against 1: transition block 96.8 and 98.0 ms, Katz block
+// 44.0 and 44.7; for a > 0 and on small levels every idle lane is worth the
+// read: 128 feature columns on 2.4M nodes 83.8 and 82.1).
+constexpr int kRefillIdle = 8;
 template <int kMode, typename Refill, typename Emit, typename Served>
 __device__ __forceinline__ void sample_loop(const LevelArgs& A, BatchLds& B, Refill&& refill, Emit&& emit_sampled,
-                                            Served&& served, uint32_t& w_cand, uint32_t& w_acc, uint32_t& w_runs) {
+                                            Served&& served, int refill_idle, bool& group, uint32_t& w_cand, uint32_t& w_acc,
+                                            uint32_t& w_runs) {
   constexpr bool kServe = kMode == kPerColumn;
   constexpr uint32_t kFirstRun = ~0u;  // in t: the item has no run yet
   uint32_t it_next = 0, it_total = 0;  // wave-uniform: queue of the loaded batch
@@ -793,16 +822,21 @@ __device__ __forceinline__ void sample_loop(const LevelArgs& A, BatchLds& B, Ref
   const double* const arcfac = kMode == kBatchAP ? pinned(A.arcfac) : nullptr;
   const double* da = A.da;
   SkipTable tab{};
+  constexpr unsigned long long kGroupFirst = 0x0101010101010101ull;  // the groups' first lanes
   // a = 0 (a constant but for the server)
   auto azero = [&]() { return kServe ? (cw & kBatchAZero) != 0 : kMode == kBatchAZ; };
 
   for (;;) {
     unsigned long long idle = wave_ballot(s >= rend);
-    if (__popcll(idle) >= kRefillIdle) {
+    if (__popcll(idle) >= refill_idle) {
       // the queue is empty: set up the next batch
       if (more && it_next >= it_total) more = refill(it_next, it_total);
+      const uint32_t sub = group ? lane_id() & (kGroup - 1) : 0u;
       if (it_next < it_total) {  // idle lanes take work items
-        const uint32_t it = lanes_below(idle, it_next);
+        // (a group's lanes share the item of its first lane)
+        const unsigned long long takers = group ? idle & kGroupFirst : idle;
+        const uint32_t it = group ? lanes_below(takers, it_next) - (sub != 0u && s >= rend ? 1u : 0u)
+                                  : lanes_below(takers, it_next);
         if (s >= rend && it < it_total) {
           const int e = it < kItemMap ? B.item_entry[it] : batch_find<uint32_t>(B.ioff, it);
           const uint32_t il = it - B.ioff[e];
@@ -833,7 +867,7 @@ __device__ __forceinline__ void sample_loop(const LevelArgs& A, BatchLds& B, Ref
           }
           if (kServe) it_cand = it_acc = it_runs = 0;
         }
-        it_next = uniform(it_next + static_cast<uint32_t>(__popcll(idle)));
+        it_next = uniform(it_next + static_cast<uint32_t>(__popcll(takers)));
         if (it_next > it_total) it_next = it_total;
         idle = wave_ballot(s >= rend);
       }
@@ -853,7 +887,7 @@ __device__ __forceinline__ void sample_loop(const LevelArgs& A, BatchLds& B, Ref
       t = fresh ? 0u : t;
     } else if (fresh && s < rend) {
       run_end = wend;
-      if (kServe) ++it_runs;
+      if (kServe) it_runs += !group || (lane_id() & (kGroup - 1)) == 0 ? 1u : 0u;
       if (!azero()) {
         // the factor of the run's first arc (for an item's first run at the
         // row start, from the entry's setup); the group end only when the
@@ -870,10 +904,15 @@ __device__ __forceinline__ void sample_loop(const LevelArgs& A, BatchLds& B, Ref
       }
       t = 0;
     }
-    // one draw of the run's chain
-    const U4 o = kServe ? philox4x32_10(t, s, u, ctr3, key0, key1) : philox4x32_10_skey(t, s, u, ctr3, key0, key1);
-    const uint32_t cand = pos + geometric_skip64(tab, unit_double(o.x, o.y));
-    const bool hit = cand < run_end;
+    // one draw of the run's chain (a group: draws t to t + 7)
+    const uint32_t sub = group ? lane_id() & (kGroup - 1) : 0u;
+    const uint32_t draw = t + sub;
+    const U4 o = kServe ? philox4x32_10(draw, s, u, ctr3, key0, key1)
+                        : philox4x32_10_skey(draw, s, u, ctr3, key0, key1);
+    uint32_t cand = geometric_skip64(tab, unit_double(o.x, o.y));
+    if (group) cand += group_scan_before(cand + 1u);
+    cand += pos;
+    const bool hit = cand < run_end;  // (the draws of a group after its first miss miss too)
     bool emit = hit;
     uint32_t v = 0;
     if (hit) {
@@ -884,20 +923,28 @@ __device__ __forceinline__ void sample_loop(const LevelArgs& A, BatchLds& B, Ref
       if (!azero())  // (a = 0: the ratio is 1 and every uniform is below it)
         emit = below_ratio(unit_double(o.z, o.w), arcfac != nullptr ? arcfac[arc] : da[A.nd[arc]], dstart);
     }
+    const unsigned long long hit_mask = wave_ballot(hit);
+    // whether the run goes on (a group: all eight draws hit), and its next position
+    bool on = hit;
+    uint32_t next = cand + 1u;
+    unsigned long long ended = ~idle & ~hit_mask;  // active lanes whose run ended
+    if (group) {
+      next = __shfl(next, lane_id() | (kGroup - 1));
+      on = ((hit_mask >> (lane_id() & ~(kGroup - 1))) & 0xffull) == 0xffull;
+      ended = ~idle & ~wave_ballot(on) & kGroupFirst;
+    }
     if (!kServe) {
-      const uint32_t hits = static_cast<uint32_t>(__popcll(wave_ballot(hit)));
-      w_cand += hits;
-      // every active lane without a candidate ends its run
-      w_runs += static_cast<uint32_t>(kWave - __popcll(idle)) - hits;
-      w_acc += kMode == kBatchAZ ? hits : static_cast<uint32_t>(__popcll(wave_ballot(emit)));
+      w_cand += static_cast<uint32_t>(__popcll(hit_mask));
+      w_runs += static_cast<uint32_t>(__popcll(ended));
+      w_acc += static_cast<uint32_t>(__popcll(kMode == kBatchAZ ? hit_mask : wave_ballot(emit)));
     } else {
       it_cand += hit ? 1u : 0u;
       it_acc += emit ? 1u : 0u;
-      if (!hit && s < rend && run_end >= rend) served(cw & kBatchCol, it_cand, it_acc, it_runs);  // the item's end
+      if (!on && s < rend && run_end >= rend) served(cw & kBatchCol, it_cand, it_acc, it_runs);  // the item's end
     }
-    s = hit ? s : run_end;
-    pos = hit ? cand + 1u : run_end;
-    t = hit ? t + 1u : t;
+    s = on ? s : run_end;
+    pos = on ? next : run_end;
+    t = on ? t + (group ? kGroup : 1u) : t;
     emit_sampled(emit, v, cw);
   }
 }
@@ -1024,6 +1071,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
   };
   uint64_t next_items = load_items(bnext);
 
+  bool group = false, first_batch = true;
   auto refill = [&](uint32_t& it_next, uint32_t& it_total) -> bool {
     if (bnext >= nbatch) return false;
     const LevelArgs& A = args_again();
@@ -1227,6 +1275,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
     B.J[lane] = eJ;
     it_next = 0;
     it_total = queue_items(B, iwork);
+    // groups where the items' chains are long (single windows of 8 expected
+    // draws or more) and at most one per lane, or where there is one per group
+    // at most; rows of small probabilities are better off with a lane each (a
+    // cluster's estimate on 4e5 nodes 1.82 ms, 3.1 with groups throughout)
+    if (few && first_batch) {
+      const uint32_t chains = wave_sum_all(((ecw >> kBatchShiftBit) & 7u) == 0u ? iwork : 0u);
+      group = it_total <= static_cast<uint32_t>(kWave / kGroup) ||
+              (it_total <= static_cast<uint32_t>(kWave) && 2u * chains > it_total);
+    }
+    first_batch = false;
     wave_sync();
     // deterministic pushes of the batch: the increment reaches theta
     for (long long kb = 0; kb < dtot; kb += kWave) {
@@ -1257,7 +1315,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
   auto served = [&](uint32_t c, uint32_t cand, uint32_t acc, uint32_t runs) {
     if (kServe) serve_item(A, s_serve, c, cand, acc, runs);
   };
-  sample_loop<kMode>(A, B, refill, emit_sampled, served, w_cand, w_acc, w_runs);
+  sample_loop<kMode>(A, B, refill, emit_sampled, served, kMode == kBatchAZ && !few ? kRefillIdle : 1, group, w_cand, w_acc,
+                     w_runs);
   if (sparse) stage_flush(stage, staged, A.fout, A.cnt_out);
   if (binned) finish_records<kG>(A, s_hist, reinterpret_cast<uint32_t*>(stage), staged, seg, acc_next);
   if (kServe) {  // flush the block's per-column sums
@@ -1475,7 +1534,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
   auto served = [&](uint32_t c, uint32_t cand, uint32_t acc, uint32_t runs) {
     if (kServe) serve_item(A, s_serve, c, cand, acc, runs);
   };
-  sample_loop<kMode>(A, B, refill, emit_sampled, served, w_cand, w_acc, w_runs);
+  bool group = per <= kGroupItems;
+  sample_loop<kMode>(A, B, refill, emit_sampled, served, kMode == kBatchAZ ? kRefillIdle : 1, group, w_cand, w_acc,
+                     w_runs);
   if (sparse) stage_flush(stage, staged, A.fout, A.cnt_out);
   if (binned) finish_records<kG>(A, s_hist, reinterpret_cast<uint32_t*>(stage), staged, seg, acc_next);
   if (kServe) {  // flush the block's per-column sums
