@@ -181,6 +181,10 @@ struct LevelArgs {
   int slots;                     // server: rows per shard
   int shard_mask;                // server: shards - 1 (a power of two of them)
   int* err;                      // batched: one flag; server: one per column
+  // batched calls: the next residues are kept rep_mask + 1 times, rep_stride
+  // words apart; block b adds to copy b mod (rep_mask + 1), k_merge adds them up
+  uint32_t rep_mask;
+  long long rep_stride;
   int positive;                  // non-negative signals: sparse levels allowed
   unsigned long long dense_cut;  // frontier size from which a level is dense
   int* mode_out;                 // how the next frontier is formed (kMode*)
@@ -330,6 +334,11 @@ struct Prec<float> {
     atomic_add_relaxed(reinterpret_cast<unsigned long long*>(acc + cell), static_cast<unsigned long long>(d));
   }
   static __device__ __forceinline__ bool nonzero(const Cell* acc, size_t cell) { return acc[cell] != 0; }
+  // whole cells (k_merge)
+  static __device__ __forceinline__ Delta load(const Cell* acc, size_t cell) { return acc[cell]; }
+  static __device__ __forceinline__ void store(Cell* acc, size_t cell, Delta v) { acc[cell] = v; }
+  static __device__ __forceinline__ bool is_zero(Delta v) { return v == 0; }
+  static __device__ __forceinline__ Delta sum(Delta a, Delta b) { return a + b; }
   static __device__ __forceinline__ void set_units(Cell* acc, size_t cell, long long v) { acc[cell] = v; }
 };
 
@@ -364,6 +373,19 @@ struct Prec<double> {
   static __device__ __forceinline__ bool add_ret(Cell* acc, size_t cell, Delta d) {
     add(acc, cell, d);
     return false;  // binary64 calls always compact the next frontier
+  }
+  static __device__ __forceinline__ Delta load(const Cell* acc, size_t cell) {
+    return U128{acc[2 * cell], static_cast<long long>(acc[2 * cell + 1])};
+  }
+  static __device__ __forceinline__ void store(Cell* acc, size_t cell, Delta v) {
+    acc[2 * cell] = v.lo;
+    acc[2 * cell + 1] = static_cast<unsigned long long>(v.hi);
+  }
+  static __device__ __forceinline__ bool is_zero(Delta v) { return (v.lo | static_cast<unsigned long long>(v.hi)) == 0ull; }
+  static __device__ __forceinline__ Delta sum(Delta a, Delta b) {
+    const unsigned long long lo = a.lo + b.lo;
+    return U128{lo, static_cast<long long>(static_cast<unsigned long long>(a.hi) + static_cast<unsigned long long>(b.hi) +
+                                           (lo < a.lo ? 1ull : 0ull))};
   }
   static __device__ __forceinline__ bool nonzero(const Cell* acc, size_t cell) {
     return (acc[2 * cell] | acc[2 * cell + 1]) != 0ull;
@@ -989,6 +1011,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
   __shared__ ServeSums s_serve[kServe ? kServeLdsSlots : 1];
 
   const unsigned long long count = *A.cnt_in;
+  if (!kServe) acc_next += (blockIdx.x & A.rep_mask) * A.rep_stride;
   // Binned levels write (cell, value) records that later kernels group by
   // destination and sum in LDS.  Without binning, sparse levels detect the
   // first contribution to a cell from the atomic's old value and append the
@@ -1378,6 +1401,7 @@ __global__ __launch_bounds__(kThreads) void k_det_big(LevelArgs A, typename Prec
   if (nb > A.big_cap) nb = A.big_cap;  // rows beyond the list were pushed by their waves
   const BigRow* R = A.big;
   const unsigned long long total = R[nb - 1].off + R[nb - 1].J;
+  if (!kServe) acc_next += (blockIdx.x & A.rep_mask) * A.rep_stride;
   const bool sparse = *A.mode_out == kModeSparse;
   uint8_t* const det_bins = *A.mode_out == kModeBinned ? A.det_bins : nullptr;
   const int lane = lane_id();
@@ -1457,6 +1481,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
   if (nb > A.big_cap) nb = A.big_cap;  // entries beyond the list kept their items
   const BigSamp* R = A.samp;
   const unsigned long long total = R[nb - 1].off + R[nb - 1].items;
+  if (!kServe) acc_next += (blockIdx.x & A.rep_mask) * A.rep_stride;
   const int mode = *A.mode_out;
   const bool binned = mode == kModeBinned;
   const bool sparse = mode == kModeSparse;
