@@ -269,14 +269,18 @@ __global__ __launch_bounds__(kWave) void k_theta_scan(const T* __restrict__ x, l
 }
 
 // nnz_out (if not null) receives *nnz_in, so that one copy to the host
-// brings the signal flags and the count of non-zero cells together.
+// brings the signal flags and the count of non-zero cells together; entries0
+// (if not 0) then replaces it as the number of level-0 entries.
 template <typename T>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_theta_final(const double* __restrict__ partial, int64_t nblocks, int C, double eps,
                               const uint32_t* __restrict__ qids, uint32_t qid_base, ColParams* __restrict__ cp,
-                              const unsigned long long* __restrict__ nnz_in = nullptr,
-                              unsigned long long* __restrict__ nnz_out = nullptr) {
+                              unsigned long long* __restrict__ nnz_in = nullptr,
+                              unsigned long long* __restrict__ nnz_out = nullptr, unsigned long long entries0 = 0) {
   const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c == 0 && nnz_out != nullptr) *nnz_out = *nnz_in;
+  if (c == 0 && nnz_out != nullptr) {
+    *nnz_out = *nnz_in;
+    if (entries0) *nnz_in = entries0;
+  }
   double total = 0.0;
   if (C == 1) {  // one wave: lane l loads block b0 + 64 k + l
     constexpr int kInFlight = 16;
@@ -447,10 +451,32 @@ __global__ __launch_bounds__(kThreads) void k_merge(typename Prec<T>::Cell* __re
   }
 }
 
-// The counter rows of level blockIdx.x added up: its counters and mass.
+// What a call's control arrays hold at its start: zeros, and the levels'
+// parameters (as kernel arguments, so that calls of up to 64 levels copy
+// nothing).  With one result copy less and no listing pass at level 0, one PPR
+// query on 10^4 nodes takes 0.58 ms instead of 0.65 with seven launches for
+// the same.
+constexpr int kBeginLevels = 64;
+constexpr int kBeginRanges = 5;
+struct BeginArgs {
+  uint32_t* ptr[kBeginRanges];
+  uint32_t words[kBeginRanges];
+  LevelParams* lp;
+  int levels;
+  LevelParams level[kBeginLevels];
+};
+__global__ void k_begin(BeginArgs B) {
+  const uint32_t i0 = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
+  for (int k = 0; k < kBeginRanges; ++k)
+    for (uint32_t i = i0; i < B.words[k]; i += step) B.ptr[k][i] = 0u;
+  if (i0 < static_cast<uint32_t>(B.levels)) B.lp[i0] = B.level[i0];
+}
+
+// The counter rows of level blockIdx.x added up: its counters and mass; the
+// error flag after the last level's mass, so that one copy brings both.
 __global__ __launch_bounds__(kWave) void k_fold_counts(const unsigned long long* __restrict__ rows,
                                                        unsigned long long* __restrict__ counters,
-                                                       double* __restrict__ mass) {
+                                                       double* __restrict__ mass, const int* __restrict__ err) {
   static_assert(kCountShards == kWave, "one row per lane");
   const int lane = lane_id();
   const unsigned long long* row =
@@ -467,6 +493,7 @@ __global__ __launch_bounds__(kWave) void k_fold_counts(const unsigned long long*
 #pragma unroll
     for (int k = 0; k < kNumCounters; ++k) counters[static_cast<size_t>(blockIdx.x) * kNumCounters + k] = v[k];
     mass[blockIdx.x] = m;
+    if (blockIdx.x == 0) mass[gridDim.x] = static_cast<double>(*err);
   }
 }
 
@@ -629,10 +656,61 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
   int* mode = reinterpret_cast<int*>(est + AGP_MAX_LEVELS + 2);
   LevelParams* lpd = reinterpret_cast<LevelParams*>(
       (reinterpret_cast<uintptr_t>(mode + AGP_MAX_LEVELS + 2) + 255) & ~static_cast<uintptr_t>(255));
-  AGP_HIP(hipMemsetAsync(sc.levelinfo.ptr, 0, sc.levelinfo.bytes, s));
-  AGP_HIP(hipMemsetAsync(counts, 0, sc.counts.bytes, s));
-  AGP_HIP(hipMemsetAsync(sc.count_rows.ptr, 0, kCountLevelBytes * (L + 1), s));
-  AGP_HIP(hipMemsetAsync(flags, 0, sc.flags.bytes, s));
+  // rows with long deterministic prefixes, deferred per level to k_det_big
+  constexpr unsigned long long kBigCap = 1ull << 18;
+  unsigned long long big_cap = kBigCap;
+  if (const char* e = std::getenv("AGP_BIG_ROWS")) {  // shorter lists (tests); 0: no deferral
+    const unsigned long long v = std::strtoull(e, nullptr, 10);
+    if (v < big_cap) big_cap = v;
+  }
+  const long long samp_items = tune.big_items;
+  // (and entries with many sampled work items, deferred to k_samp_big):
+  // per-level counters of both lists, then the two lists
+  unsigned long long* big_ctr = nullptr;
+  unsigned long long* samp_ctr = nullptr;
+  BigRow* big_rows = nullptr;
+  BigSamp* samp_rows = nullptr;
+  if (big_cap > 0 && (may_alloc || sc.big.bytes > 0) &&
+      sc.big.reserve(sizeof(unsigned long long) * 2 * (AGP_MAX_LEVELS + 1) + sizeof(BigRow) * kBigCap +
+                         sizeof(BigSamp) * kBigCap,
+                     false, s) == AGP_OK) {
+    big_ctr = sc.big.as<unsigned long long>();
+    samp_ctr = big_ctr + AGP_MAX_LEVELS + 1;
+    big_rows = reinterpret_cast<BigRow*>(samp_ctr + AGP_MAX_LEVELS + 1);
+    samp_rows = reinterpret_cast<BigSamp*>(big_rows + kBigCap);
+  } else {
+    (void)hipGetLastError();  // no room for the list: every row stays with its wave
+  }
+  // per-level values of this call (read by the level kernels from device memory)
+  LevelParams lph[AGP_MAX_LEVELS + 1];
+  const uint32_t key0 = static_cast<uint32_t>(seed), key1 = static_cast<uint32_t>(seed >> 32);
+  for (int32_t i = 0; i <= L; ++i) {
+    lph[i].rho = rho[i];
+    lph[i].kappa = kappa[i];
+    lph[i].flags = i == L ? kLastLevel : 0;
+    lph[i].key0 = key0;
+    lph[i].key1 = key1;
+    lph[i].pad = 0;
+  }
+
+  {  // control arrays cleared, level parameters set
+    BeginArgs B{};
+    B.ptr[0] = static_cast<uint32_t*>(sc.levelinfo.ptr);
+    B.words[0] = static_cast<uint32_t>((reinterpret_cast<char*>(lpd) - sc.levelinfo.as<char>()) / sizeof(uint32_t));
+    B.ptr[1] = reinterpret_cast<uint32_t*>(counts);
+    B.words[1] = static_cast<uint32_t>(sizeof(unsigned long long) * (AGP_MAX_LEVELS + 2) / sizeof(uint32_t));
+    B.ptr[2] = sc.count_rows.as<uint32_t>();
+    B.words[2] = static_cast<uint32_t>(kCountLevelBytes * (L + 1) / sizeof(uint32_t));
+    B.ptr[3] = reinterpret_cast<uint32_t*>(flags);
+    B.words[3] = 4;
+    B.ptr[4] = reinterpret_cast<uint32_t*>(big_ctr);
+    B.words[4] = big_ctr ? static_cast<uint32_t>(sizeof(unsigned long long) * 2 * (AGP_MAX_LEVELS + 1) / sizeof(uint32_t)) : 0u;
+    B.lp = lpd;
+    B.levels = L + 1 <= kBeginLevels ? L + 1 : 0;
+    std::copy(lph, lph + B.levels, B.level);
+    k_begin<<<64, 256, 0, s>>>(B);
+    if (B.levels == 0) AGP_HIP(hipMemcpyAsync(lpd, lph, sizeof(LevelParams) * (L + 1), hipMemcpyHostToDevice, s));
+  }
   if (qids) AGP_HIP(hipMemcpyAsync(dq, qids, sizeof(uint32_t) * C, hipMemcpyHostToDevice, s));
 
   // thresholds theta_c = eps ||x_c||_1 and signal checks, counting the
@@ -645,10 +723,14 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
     k_theta_partial<T><<<dim3((unsigned)tblocks, (unsigned)((C + kWave - 1) / kWave)), kThetaWaves * kWave, 0, s>>>(
         x, ldc, n, C, lw, sc.partial.as<double>(), flags + 1, counts);
   }
+  // calls of few cells visit every cell at level 0 whatever the signal holds: a
+  // listing pass and its clear cost them more than the empty entries
+  const bool all_cells = cells <= kFewEntries && static_cast<long long>(C) <= kVirtualMaxC;
   // flags[2..3]: the count of non-zero cells of x
   k_theta_final<T><<<grid_for(C, 64), 64, 0, s>>>(sc.partial.as<double>(), tblocks, C, eps,
                                                   qids ? dq : nullptr, qid_base, cp, counts,
-                                                  reinterpret_cast<unsigned long long*>(flags + 2));
+                                                  reinterpret_cast<unsigned long long*>(flags + 2),
+                                                  all_cells ? static_cast<unsigned long long>(cells) : 0ull);
   AGP_HIP(hipGetLastError());
   int hflags[4] = {0, 0, 0, 0};
   AGP_HIP(hipMemcpyAsync(hflags, flags, sizeof(hflags), hipMemcpyDeviceToHost, s));
@@ -661,9 +743,10 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
   long long cseg = kCompactUnroll * kWave;
   while (cseg < kCompactSeg && cseg * 4096 < static_cast<long long>(cells)) cseg <<= 1;
   const unsigned cgrid = grid_for(static_cast<int64_t>((cells + cseg - 1) / cseg), kThreads / kWave, 1280);
-  const bool virtual0 = nnz_x > 0 && 2 * nnz_x >= static_cast<unsigned long long>(cells) &&
-                        static_cast<long long>(C) <= kVirtualMaxC;
-  if (virtual0) {
+  const bool virtual0 = all_cells || (nnz_x > 0 && 2 * nnz_x >= static_cast<unsigned long long>(cells) &&
+                                      static_cast<long long>(C) <= kVirtualMaxC);
+  if (all_cells) {  // k_theta_final has set the level-0 count
+  } else if (virtual0) {
     k_set_u64<<<1, 1, 0, s>>>(counts, static_cast<unsigned long long>(cells));  // the level-0 entries
   } else if (tblocks > 0) {
     k_set_u64<<<1, 1, 0, s>>>(counts, 0ull);
@@ -741,32 +824,6 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
   uint64_t* F[2] = {sc.frontier[0].as<uint64_t>(), sc.frontier[1].as<uint64_t>()};
   Cell* acc[2] = {sc.acc[0].as<Cell>(), sc.acc[1].as<Cell>()};
 
-  // rows with long deterministic prefixes, deferred per level to k_det_big
-  constexpr unsigned long long kBigCap = 1ull << 18;
-  unsigned long long big_cap = kBigCap;
-  if (const char* e = std::getenv("AGP_BIG_ROWS")) {  // shorter lists (tests); 0: no deferral
-    const unsigned long long v = std::strtoull(e, nullptr, 10);
-    if (v < big_cap) big_cap = v;
-  }
-  const long long samp_items = tune.big_items;
-  // (and entries with many sampled work items, deferred to k_samp_big):
-  // per-level counters of both lists, then the two lists
-  unsigned long long* big_ctr = nullptr;
-  unsigned long long* samp_ctr = nullptr;
-  BigRow* big_rows = nullptr;
-  BigSamp* samp_rows = nullptr;
-  if (big_cap > 0 && (may_alloc || sc.big.bytes > 0) &&
-      sc.big.reserve(sizeof(unsigned long long) * 2 * (AGP_MAX_LEVELS + 1) + sizeof(BigRow) * kBigCap +
-                         sizeof(BigSamp) * kBigCap,
-                     false, s) == AGP_OK) {
-    big_ctr = sc.big.as<unsigned long long>();
-    samp_ctr = big_ctr + AGP_MAX_LEVELS + 1;
-    big_rows = reinterpret_cast<BigRow*>(samp_ctr + AGP_MAX_LEVELS + 1);
-    samp_rows = reinterpret_cast<BigSamp*>(big_rows + kBigCap);
-    AGP_HIP(hipMemsetAsync(big_ctr, 0, sizeof(unsigned long long) * 2 * (AGP_MAX_LEVELS + 1), s));
-  } else {
-    (void)hipGetLastError();  // no room for the list: every row stays with its wave
-  }
   // no list (and no launch for it) where no entry of this call can reach it:
   // a batch holds at most cells / kResidentWaves entries
   const unsigned long long max_eb = std::min<unsigned long long>(kBatch, (cells + kResidentWaves - 1) / kResidentWaves);
@@ -855,19 +912,6 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
       sc.arcfac_a = -1.0;
     }
   }
-  // per-level values of this call (read by the level kernels from device memory)
-  LevelParams lph[AGP_MAX_LEVELS + 1];
-  const uint32_t key0 = static_cast<uint32_t>(seed), key1 = static_cast<uint32_t>(seed >> 32);
-  for (int32_t i = 0; i <= L; ++i) {
-    lph[i].rho = rho[i];
-    lph[i].kappa = kappa[i];
-    lph[i].flags = i == L ? kLastLevel : 0;
-    lph[i].key0 = key0;
-    lph[i].key1 = key1;
-    lph[i].pad = 0;
-  }
-  AGP_HIP(hipMemcpyAsync(lpd, lph, sizeof(LevelParams) * (L + 1), hipMemcpyHostToDevice, s));
-
   // workgroups of the level kernel: as many as its batches at the most
   // (batches of 64 entries, on calls of at most kFewEntries cells
   // kResidentWaves of them)
@@ -953,7 +997,7 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
                                              mode + i + 1);
       if (timed) (void)hipEventRecord(ev[4 * i + 3], s);
     }
-    k_fold_counts<<<L + 1, kWave, 0, s>>>(sc.count_rows.as<unsigned long long>(), counters, mass);
+    k_fold_counts<<<L + 1, kWave, 0, s>>>(sc.count_rows.as<unsigned long long>(), counters, mass, flags);
   };
   if (tune.capture == 1) {
     // key: everything the captured kernels take by value
@@ -1006,10 +1050,10 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
     levels(s, stats != nullptr);
   }
   AGP_HIP(hipGetLastError());
-  double hmass[AGP_MAX_LEVELS + 1];
-  AGP_HIP(hipMemcpyAsync(hflags, flags, sizeof(int), hipMemcpyDeviceToHost, s));
-  AGP_HIP(hipMemcpyAsync(hmass, mass, sizeof(double) * (L + 1), hipMemcpyDeviceToHost, s));
+  double hmass[AGP_MAX_LEVELS + 2];
+  AGP_HIP(hipMemcpyAsync(hmass, mass, sizeof(double) * (L + 2), hipMemcpyDeviceToHost, s));
   AGP_HIP(hipStreamSynchronize(s));
+  hflags[0] = static_cast<int>(hmass[L + 1]);
   // no partial sum can wrap while a level's total magnitude stays below the cell range
   const double mass_cap = sizeof(T) == 4 ? 0x1p61 : 0x1p125;
   for (int32_t i = 0; i <= L; ++i)
