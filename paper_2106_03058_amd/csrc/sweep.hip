@@ -400,10 +400,11 @@ extern "C" int agp_sweep(const agp_graph_t* g, const float* pi, int64_t ld, void
 
 // ------------------------------------------------------------ batched sweep
 // The sweeps of many columns at once.  Per group of up to 64 columns: the
-// keys of all columns, a radix sort per column, the ranks, and one pass over
+// keys of all columns, their order, the ranks, and one pass over
 // the arcs in which a wave's lanes are the columns:
 // an arc's neighbour costs one coalesced gather of its 64 byte ranks instead
-// of 64 single-byte gathers.  The per-(node, column) cut terms are node-major;
+// of 64 single-byte gathers.  Ranks and cut terms are node-major (cell v G + g
+// of node v, column g), and the orders hold cells;
 // one scan over the group (read through the order of each column) gives every
 // column's prefix sums, from which each column's first minimum of Phi is
 // taken.
@@ -413,30 +414,34 @@ namespace {
 constexpr int kBatchCols = 64;    // columns per group (one per lane)
 constexpr int kBatchUnroll = 8;   // arcs per lane with their gathers in flight
 constexpr int kBatchPhiBlocks = 256;
-
-__global__ void k_sweepb_keys(const float* __restrict__ pi, int64_t ld, int64_t c0, int G,
+// keys of the cells and the cells, node-major: coalesced both ways
+__global__ void k_sweepb_keys(const float* __restrict__ pi, int64_t ld, int64_t c0, uint32_t G,
                               const int32_t* __restrict__ deg, int64_t n, uint64_t* __restrict__ keys,
-                              int32_t* __restrict__ ids) {
+                              uint32_t* __restrict__ ids) {
   const int64_t total = n * G;
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t v = t / G;
-    const int64_t g = t - v * G;
-    keys[g * n + v] = sweep_key(pi[v * ld + c0 + g], deg[v]);  // reads of a node's columns coalesce
-    ids[g * n + v] = static_cast<int32_t>(v);
+    const uint32_t v = static_cast<uint32_t>(t) / G;
+    const uint32_t g = static_cast<uint32_t>(t) - v * G;
+    keys[t] = sweep_key(pi[v * ld + c0 + g], deg[v]);
+    ids[t] = static_cast<uint32_t>(t);
   }
 }
 
-// rank (column-major) and byte rank (node-major: a node's 64 columns are 64
-// consecutive bytes) of every column
-__global__ void k_sweepb_rank(const int32_t* __restrict__ ids, int64_t n, int G, int shift,
+// the cells' columns: the keys of the stable pass
+__global__ void k_sweepb_cols(const uint32_t* __restrict__ ids, int64_t total, uint32_t G, uint8_t* __restrict__ cols) {
+  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x)
+    cols[t] = static_cast<uint8_t>(ids[t] % G);
+}
+
+// rank and byte rank of every cell (a node's 64 columns are 64 consecutive
+// entries); position g n + i of the orders is column g's i-th cell
+__global__ void k_sweepb_rank(const uint32_t* __restrict__ ids, int64_t n, int G, int shift,
                               int32_t* __restrict__ rank, uint8_t* __restrict__ coarse) {
   const int64_t total = n * G;
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t g = t / n;
-    const int64_t i = t - g * n;
-    const int32_t v = ids[t];
-    rank[g * n + v] = static_cast<int32_t>(i);
-    coarse[static_cast<int64_t>(v) * G + g] = static_cast<uint8_t>(i >> shift);
+    const uint32_t i = static_cast<uint32_t>(t) % static_cast<uint32_t>(n);
+    rank[ids[t]] = static_cast<int32_t>(i);
+    coarse[ids[t]] = static_cast<uint8_t>(i >> shift);
   }
 }
 
@@ -444,7 +449,7 @@ __global__ void k_sweepb_rank(const int32_t* __restrict__ ids, int64_t n, int G,
 __global__ void k_sweepb_init(const int32_t* __restrict__ deg, int64_t n, int G, long long* __restrict__ dcut) {
   const int64_t total = n * G;
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x)
-    dcut[t] = deg[t / G];
+    dcut[t] = deg[static_cast<uint32_t>(t) / static_cast<uint32_t>(G)];
 }
 
 // One wave per work item (a piece of the arc run of 64 consecutive node ids),
@@ -513,8 +518,8 @@ __global__ __launch_bounds__(kSweepThreads) void k_sweepb_delta(
             if (cu[jj] < cv) {
               ++earlier;
             } else if (cu[jj] == cv) {
-              if (rv < 0) rv = rank[static_cast<int64_t>(lane) * n + v];
-              if (rank[static_cast<int64_t>(lane) * n + u[jj]] < rv) ++earlier;
+              if (rv < 0) rv = rank[v * G + lane];
+              if (rank[static_cast<int64_t>(u[jj]) * G + lane] < rv) ++earlier;
             }
           }
         }
@@ -535,17 +540,15 @@ struct VolCutPlus {
   }
 };
 
-// position t = g n + i of the group: (d_v, cut term of (v, g)), v = order_g[i]
+// position g n + i of the group: (d_v, cut term) of column g's i-th cell
 struct VolCutAt {
-  const int32_t* ids;
+  const uint32_t* ids;
   const int32_t* deg;
   const long long* dcut;
-  int64_t n;
-  int G;
+  uint32_t G;
   __device__ VolCut operator()(size_t t) const {
-    const int64_t g = static_cast<int64_t>(t) / n;
-    const int32_t v = ids[t];
-    return VolCut{deg[v], dcut[static_cast<int64_t>(v) * G + g]};
+    const uint32_t cell = ids[t];
+    return VolCut{deg[cell / G], dcut[cell]};
   }
 };
 
@@ -613,11 +616,25 @@ extern "C" int agp_sweep_batch(const agp_graph_t* g, const float* pi, int64_t ld
   if (static_cast<double>(n) * G >= 4294967295.0) G = static_cast<int>(4294967294.0 / static_cast<double>(n));
   if (G < 1) return fail(AGP_EINVAL, "agp_sweep_batch: graph too large");
   const size_t GN = static_cast<size_t>(n) * G;
+  // One sort of all the group's cells by key and one stable pass by column:
+  // 20 launches a group, where a sort per column took 1300 (HKPR estimates of
+  // 64 seeds on 600,000 nodes and the sweeps: 28.5 ms with those, 20.7 so; the
+  // sweep alone at 30,000 nodes 4.3 and 1.8, at 1,000,000 19.5 and 11.8, at
+  // 3,000,000, where a column's sort fills the chip, 45.5 and 38.8).
+  int col_bits = 0;
+  while ((1 << col_bits) < G) ++col_bits;
   size_t sort_bytes = 0, scan_bytes = 0;
-  AGP_HIP(rocprim::radix_sort_pairs(nullptr, sort_bytes, static_cast<uint64_t*>(nullptr),
-                                    static_cast<uint64_t*>(nullptr), static_cast<int32_t*>(nullptr),
-                                    static_cast<int32_t*>(nullptr), static_cast<size_t>(n), 0, 64, s));
-  const VolCutAt at0{nullptr, nullptr, nullptr, n, G};
+  // (the space is not monotone in the size: also for the last group's)
+  for (const size_t cells : {GN, static_cast<size_t>(n) * (C % G)}) {
+    rocprim::double_buffer<uint64_t> k(nullptr, nullptr);
+    rocprim::double_buffer<uint32_t> v(nullptr, nullptr);
+    rocprim::double_buffer<uint8_t> c(nullptr, nullptr);
+    size_t key_bytes = 0, col_bytes = 0;
+    AGP_HIP(rocprim::radix_sort_pairs(nullptr, key_bytes, k, v, cells, 0, 64, s));
+    if (col_bits) AGP_HIP(rocprim::radix_sort_pairs(nullptr, col_bytes, c, v, cells, 0, col_bits, s));
+    sort_bytes = std::max({sort_bytes, key_bytes, col_bytes});
+  }
+  const VolCutAt at0{nullptr, nullptr, nullptr, static_cast<uint32_t>(G)};
   AGP_HIP(rocprim::inclusive_scan(nullptr, scan_bytes,
                                   rocprim::make_transform_iterator(rocprim::make_counting_iterator<size_t>(0), at0),
                                   static_cast<VolCut*>(nullptr), GN, VolCutPlus(), s));
@@ -634,8 +651,8 @@ extern "C" int agp_sweep_batch(const agp_graph_t* g, const float* pi, int64_t ld
   uint64_t* keys_out = reinterpret_cast<uint64_t*>(p + b8);
   VolCut* P = reinterpret_cast<VolCut*>(p);  // over both key arrays once the sort is done
   long long* dcut = reinterpret_cast<long long*>(p + 2 * b8);
-  int32_t* ids_in = reinterpret_cast<int32_t*>(p + 3 * b8);
-  int32_t* ids_out = reinterpret_cast<int32_t*>(p + 3 * b8 + b4);
+  uint32_t* ids_in = reinterpret_cast<uint32_t*>(p + 3 * b8);
+  uint32_t* ids_out = reinterpret_cast<uint32_t*>(p + 3 * b8 + b4);
   int32_t* rank = reinterpret_cast<int32_t*>(p + 3 * b8 + 2 * b4);
   uint8_t* coarse = reinterpret_cast<uint8_t*>(p + 3 * b8 + 3 * b4);
   PhiIdx* parts = reinterpret_cast<PhiIdx*>(p + 3 * b8 + 3 * b4 + b1);
@@ -653,22 +670,26 @@ extern "C" int agp_sweep_batch(const agp_graph_t* g, const float* pi, int64_t ld
     const int Gc = std::min<int32_t>(G, C - c0);
     const size_t gn = static_cast<size_t>(n) * Gc;
     const unsigned grid = static_cast<unsigned>(std::min<int64_t>((static_cast<int64_t>(gn) + 255) / 256, 65536));
-    k_sweepb_keys<<<grid, 256, 0, s>>>(pi, ld, c0, Gc, g->degree, n, keys_in, ids_in);
+    k_sweepb_keys<<<grid, 256, 0, s>>>(pi, ld, c0, static_cast<uint32_t>(Gc), g->degree, n, keys_in, ids_in);
     size_t tb = temp_bytes;
-    for (int gi = 0; gi < Gc; ++gi) {  // one device-wide sort per column (a segmented sort takes a
-      tb = temp_bytes;                 // block per segment, far slower on segments of millions)
-      const size_t o = static_cast<size_t>(gi) * static_cast<size_t>(n);
-      AGP_HIP(rocprim::radix_sort_pairs(temp, tb, keys_in + o, keys_out + o, ids_in + o, ids_out + o,
-                                        static_cast<size_t>(n), 0, 64, s));
+    rocprim::double_buffer<uint64_t> k(keys_in, keys_out);
+    rocprim::double_buffer<uint32_t> v(ids_in, ids_out);
+    AGP_HIP(rocprim::radix_sort_pairs(temp, tb, k, v, gn, 0, 64, s));
+    if (col_bits) {
+      rocprim::double_buffer<uint8_t> c(reinterpret_cast<uint8_t*>(keys_in), reinterpret_cast<uint8_t*>(keys_out));
+      k_sweepb_cols<<<grid, 256, 0, s>>>(v.current(), static_cast<int64_t>(gn), static_cast<uint32_t>(Gc), c.current());
+      tb = temp_bytes;
+      AGP_HIP(rocprim::radix_sort_pairs(temp, tb, c, v, gn, 0, col_bits, s));
     }
-    k_sweepb_rank<<<grid, 256, 0, s>>>(ids_out, n, Gc, shift, rank, coarse);
+    const uint32_t* ids = v.current();
+    k_sweepb_rank<<<grid, 256, 0, s>>>(ids, n, Gc, shift, rank, coarse);
     k_sweepb_init<<<grid, 256, 0, s>>>(g->degree, n, Gc, dcut);
     const unsigned dgrid = static_cast<unsigned>(
         std::max<int64_t>(1, std::min<int64_t>((nitems + kSweepThreads / 64 - 1) / (kSweepThreads / 64), 65536)));
     k_sweepb_delta<<<dgrid, kSweepThreads, 0, s>>>(g->row_ptr, g->col, rank, coarse, shift, n, Gc, items, first,
                                                   nitems, dcut);
     tb = temp_bytes;
-    const VolCutAt at{ids_out, g->degree, dcut, n, Gc};
+    const VolCutAt at{ids, g->degree, dcut, static_cast<uint32_t>(Gc)};
     AGP_HIP(rocprim::inclusive_scan(temp, tb,
                                     rocprim::make_transform_iterator(rocprim::make_counting_iterator<size_t>(0), at),
                                     P, gn, VolCutPlus(), s));
