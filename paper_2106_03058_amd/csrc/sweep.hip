@@ -433,23 +433,23 @@ __global__ void k_sweepb_cols(const uint32_t* __restrict__ ids, int64_t total, u
     cols[t] = static_cast<uint8_t>(ids[t] % G);
 }
 
-// rank and byte rank of every cell (a node's 64 columns are 64 consecutive
-// entries); position g n + i of the orders is column g's i-th cell
-__global__ void k_sweepb_rank(const uint32_t* __restrict__ ids, int64_t n, int G, int shift,
-                              int32_t* __restrict__ rank, uint8_t* __restrict__ coarse) {
-  const int64_t total = n * G;
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
-    const uint32_t i = static_cast<uint32_t>(t) % static_cast<uint32_t>(n);
-    rank[ids[t]] = static_cast<int32_t>(i);
-    coarse[ids[t]] = static_cast<uint8_t>(i >> shift);
-  }
-}
-
-// cut terms (node-major) start at d_v
-__global__ void k_sweepb_init(const int32_t* __restrict__ deg, int64_t n, int G, long long* __restrict__ dcut) {
+// rank of every cell; position g n + i of the orders is column g's i-th cell
+__global__ void k_sweepb_rank(const uint32_t* __restrict__ ids, int64_t n, int G, int32_t* __restrict__ rank) {
   const int64_t total = n * G;
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x)
+    rank[ids[t]] = static_cast<int32_t>(static_cast<uint32_t>(t) % static_cast<uint32_t>(n));
+}
+
+// byte ranks (a node's 64 columns are 64 consecutive bytes), and the cut terms
+// start at d_v
+__global__ void k_sweepb_init(const int32_t* __restrict__ deg, int64_t n, int G, int shift,
+                              const int32_t* __restrict__ rank, uint8_t* __restrict__ coarse,
+                              long long* __restrict__ dcut) {
+  const int64_t total = n * G;
+  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
+    coarse[t] = static_cast<uint8_t>(rank[t] >> shift);
     dcut[t] = deg[static_cast<uint32_t>(t) / static_cast<uint32_t>(G)];
+  }
 }
 
 // One wave per work item (a piece of the arc run of 64 consecutive node ids),
@@ -682,8 +682,8 @@ extern "C" int agp_sweep_batch(const agp_graph_t* g, const float* pi, int64_t ld
       AGP_HIP(rocprim::radix_sort_pairs(temp, tb, c, v, gn, 0, col_bits, s));
     }
     const uint32_t* ids = v.current();
-    k_sweepb_rank<<<grid, 256, 0, s>>>(ids, n, Gc, shift, rank, coarse);
-    k_sweepb_init<<<grid, 256, 0, s>>>(g->degree, n, Gc, dcut);
+    k_sweepb_rank<<<grid, 256, 0, s>>>(ids, n, Gc, rank);
+    k_sweepb_init<<<grid, 256, 0, s>>>(g->degree, n, Gc, shift, rank, coarse, dcut);
     const unsigned dgrid = static_cast<unsigned>(
         std::max<int64_t>(1, std::min<int64_t>((nitems + kSweepThreads / 64 - 1) / (kSweepThreads / 64), 65536)));
     k_sweepb_delta<<<dgrid, kSweepThreads, 0, s>>>(g->row_ptr, g->col, rank, coarse, shift, n, Gc, items, first,
