@@ -786,6 +786,7 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
       if (v > 0 && v < cap) cap = v;
     }
     seg_cap = (cap + ng * kRecSegs - 1) / (ng * kRecSegs);
+    seg_cap = (seg_cap + kQuad - 1) / kQuad * kQuad;
     rec_cap = seg_cap * kRecSegs;
     if (sc.rec[0].reserve(rec_cap * ng * sizeof(uint32_t), false, s) ||
         sc.rec[1].reserve(rec_cap * ng * sizeof(uint32_t), false, s) ||
@@ -1226,6 +1227,7 @@ DensePlan dense_plan(agp_graph* g, int32_t C, const agp_tuning_t& tune, bool bin
     // allocating tens of GB
     const unsigned long long have = std::min(sc.rec[0].bytes, sc.rec[1].bytes) / (sizeof(uint32_t) * p.ng);
     if (p.rec_cap > 0 && have >= p.rec_cap / 10 * 9) p.rec_cap = std::min<unsigned long long>(have, 2 * p.rec_cap);
+    p.rec_cap = p.rec_cap / kQuad * kQuad;
   }
   return p;
 }
