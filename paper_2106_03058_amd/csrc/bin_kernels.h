@@ -225,9 +225,10 @@ __device__ __forceinline__ unsigned long long bin_of(uint32_t rec) {
   return static_cast<unsigned long long>(rec & kRecCellMask) >> kBinLog2;
 }
 
-// Counts use tiles of kCountTile records (read kBinPerThread per thread at a
-// time): a tile's window of bins is flushed with one global atomic per bin,
-// so larger tiles mean fewer atomics on the same counters.
+// Counts use tiles of up to kCountTile records (read kBinPerThread per thread
+// at a time): a tile's window of bins is flushed with one global atomic per
+// bin, so larger tiles mean fewer atomics on the same counters; but levels of
+// few records take smaller ones, to have a tile for every block.
 constexpr int kCountTile = 8 * kBinTile;
 
 __global__ __launch_bounds__(kReduceThreads) void k_bin_count(const uint32_t* __restrict__ part,
@@ -238,10 +239,11 @@ __global__ __launch_bounds__(kReduceThreads) void k_bin_count(const uint32_t* __
   __shared__ unsigned int s_h[kBinWindow];
   const unsigned long long total = *rec_count;
   const unsigned long long bpb = 1ull << (shift - kBinLog2);  // bins per bucket
-  for (unsigned long long t0 = (unsigned long long)blockIdx.x * kCountTile; t0 < total;
-       t0 += (unsigned long long)gridDim.x * kCountTile) {
+  unsigned long long tile = kCountTile;
+  while (tile > kBinTile && tile * gridDim.x > total) tile >>= 1;
+  for (unsigned long long t0 = blockIdx.x * tile; t0 < total; t0 += gridDim.x * tile) {
     const unsigned long long w0 = (bin_of(part[t0]) / bpb) * bpb;  // first bin of the tile's first bucket
-    const unsigned long long t1 = t0 + kCountTile < total ? t0 + kCountTile : total;
+    const unsigned long long t1 = t0 + tile < total ? t0 + tile : total;
     for (int i = threadIdx.x; i < kBinWindow; i += blockDim.x) s_h[i] = 0;
     __syncthreads();
     for (unsigned long long lo = t0; lo < t1; lo += kBinTile) {
