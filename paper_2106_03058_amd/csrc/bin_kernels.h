@@ -24,7 +24,7 @@ constexpr int kMaxBinnedC = 1024;
 constexpr int kReduceThreads = 512;
 
 // One block per column group of records: the group's nbk bucket counts at
-// g * nbk (cleared), its offsets and cursors at g * (kBuckets + 1) and
+// g * kBuckets / groups (cleared), its offsets and cursors at g * (kBuckets + 1) and
 // g * kBuckets, and its record total; a group with a segment whose records
 // outgrew it switches the level to the atomic fallback.
 __global__ __launch_bounds__(1024) void k_bins_scan(unsigned int* __restrict__ bucket_count, int nbk,
@@ -37,7 +37,7 @@ __global__ __launch_bounds__(1024) void k_bins_scan(unsigned int* __restrict__ b
   __shared__ unsigned long long s[kBuckets];
   const int g = blockIdx.x;
   const int t = threadIdx.x;
-  unsigned int* bc = bucket_count + static_cast<size_t>(g) * nbk;
+  unsigned int* bc = bucket_count + g * (kBuckets / gridDim.x);
   const unsigned long long v = t < nbk ? bc[t] : 0ull;
   if (t < nbk) bc[t] = 0;  // ready for the next level (zero unless this one was binned)
   if (*mode != kModeBinned) return;  // (or another group overflowed)

@@ -765,11 +765,20 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
   const long long gw = ng == 1 ? C : (C + 1) / 2;
   const unsigned long long gcells = static_cast<unsigned long long>(n) * static_cast<unsigned long long>(gw);
   bool binned = may_bin && gcells < (1ull << 31) && C <= kMaxBinnedC && cells > 0;
-  // buckets of 2^shift group cells: at most 1024 buckets (512 per group with
-  // two groups, which share the level kernel's histogram), bins of 8192 cells
-  const unsigned long long nbk = static_cast<unsigned long long>(kBuckets / ng);
+  // buckets of 2^shift group cells, bins of 8192 cells.  Up to 8192 cells for
+  // each of 1024 buckets (512 per group with two groups, which share the level
+  // kernel's histogram) a bucket is a bin, and its records are summed as the
+  // partition leaves them, without the count, scan and scatter of bins (split
+  // features of 11 columns on 200,003 nodes 5.4 ms, 6.4 with them; 33
+  // single-target queries on 2^17 nodes 5.2 and 5.7).  More cells take 512
+  // buckets a group: the partition writes runs of 64 records of a tile rather
+  // than 32 (11.2 ms instead of 12.6 for 4.5e9 records, the scatter 10.7 both
+  // times; with 256 buckets 10.2 and 11.0).
+  const unsigned long long nbk = gcells <= (static_cast<unsigned long long>(kBuckets / ng) << kBinLog2)
+                                     ? static_cast<unsigned long long>(kBuckets / ng) : kBuckets / 2;
   int shift = kBinLog2;
   while (shift < 32 && (gcells > 0 ? gcells - 1ull : 0ull) >> shift >= nbk) ++shift;
+  const bool bucket_bins = shift == kBinLog2;
   const long long nbins = static_cast<long long>(((gcells > 0 ? gcells : 1) - 1) >> kBinLog2) + 1;  // per group
   unsigned long long rec_cap = 0, seg_cap = 0;  // per group, and per segment of a group
   if (binned) {
@@ -974,18 +983,23 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
           k_partition<<<1024, kReduceThreads, 0, s>>>(g0, rc + static_cast<size_t>(gi) * kRecSegs * kRecStride, kRecSegs,
                                                       seg_cap, cursor + static_cast<size_t>(gi) * kBuckets, g1,
                                                       mode + i + 1, shift);
-          k_bin_count<<<2048, kReduceThreads, 0, s>>>(g1, rec_total + gi, bin_count, mode + i + 1, shift);
-          k_bin_scan<<<static_cast<unsigned>(nbins / kScanChunk + 1), 1024, 0, s>>>(bin_count, nbins, bin_off,
-                                                                                 bin_cur, mode + i + 1);
-          k_bin_scatter<<<2048, kReduceThreads, 0, s>>>(g1, rec_total + gi, bin_cur, g0, mode + i + 1, shift, bin_count,
-                                                        nbins);
+          if (!bucket_bins) {
+            k_bin_count<<<2048, kReduceThreads, 0, s>>>(g1, rec_total + gi, bin_count, mode + i + 1, shift);
+            k_bin_scan<<<static_cast<unsigned>(nbins / kScanChunk + 1), 1024, 0, s>>>(bin_count, nbins, bin_off,
+                                                                                   bin_cur, mode + i + 1);
+            k_bin_scatter<<<2048, kReduceThreads, 0, s>>>(g1, rec_total + gi, bin_cur, g0, mode + i + 1, shift,
+                                                          bin_count, nbins);
+          }
+          const uint32_t* sorted = bucket_bins ? g1 : g0;
+          const unsigned long long* offs =
+              bucket_bins ? bucket_off + static_cast<size_t>(gi) * (kBuckets + 1) : bin_off;
           if (ng == 1)
             k_bin_sum<<<static_cast<unsigned>(nbins), kSumThreads, 0, s>>>(
-                g0, bin_off, cp, (long long)C, 1ll, static_cast<unsigned long long>(cells),
+                sorted, offs, cp, (long long)C, 1ll, static_cast<unsigned long long>(cells),
                 reinterpret_cast<long long*>(nxt), F[(i + 1) & 1], counts + i + 1, mode + i + 1, det_bins);
           else
             k_bin_sum<<<static_cast<unsigned>(nbins), kSumThreads, 0, s>>>(
-                g0, bin_off, cp, gw, 1ll, gcells, reinterpret_cast<long long*>(nxt), F[(i + 1) & 1], counts + i + 1,
+                sorted, offs, cp, gw, 1ll, gcells, reinterpret_cast<long long*>(nxt), F[(i + 1) & 1], counts + i + 1,
                 mode + i + 1, det_bins + static_cast<size_t>(gi) * nbins, (long long)C, static_cast<int>(gi * gw),
                 static_cast<int>(std::min<long long>(gw, C - gi * gw)));
         }
