@@ -1580,11 +1580,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
 // sampled rows their expected d_u c / theta with c = rho |r| d_u^-b), summed
 // over the frontier (over a sample of it when it is large): decides whether
 // the level is worth binning.
+// One atomic a block on one address, about 10 ns each: few, large blocks.
+constexpr int kEstimateThreads = 1024;
+constexpr int kEstimateBlocks = 256;
+
 template <typename T, bool kFirst>
-__global__ __launch_bounds__(kThreads) void k_estimate(LevelArgs A, const T* __restrict__ x,
+__global__ __launch_bounds__(kEstimateThreads) void k_estimate(LevelArgs A, const T* __restrict__ x,
                                                        const typename Prec<T>::Cell* __restrict__ acc_cur,
                                                        double* __restrict__ est) {
-  __shared__ double s_part[kThreads / kWave];
+  __shared__ double s_part[kEstimateThreads / kWave];
   const unsigned long long count = *A.cnt_in;
   // large frontiers: an evenly spaced sample of 2^20 to 2^21 entries, scaled
   // up (the estimate only chooses between interchangeable aggregation modes)
@@ -1626,7 +1630,7 @@ __global__ __launch_bounds__(kThreads) void k_estimate(LevelArgs A, const T* __r
   __syncthreads();
   if (threadIdx.x == 0) {  // one atomic per block
     double b = 0.0;
-    for (int w = 0; w < kThreads / kWave; ++w) b += s_part[w];
+    for (int w = 0; w < kEstimateThreads / kWave; ++w) b += s_part[w];
     if (b != 0.0) atomicAdd(est, b * static_cast<double>(stride));
   }
 }

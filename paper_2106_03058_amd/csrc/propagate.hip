@@ -959,9 +959,9 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
       if (bin_level && tune.aggregation == 2) {
         A.bin_est = est + i;
         if (i == 0)
-          k_estimate<T, true><<<1024, kThreads, 0, s>>>(A, x, cur, est + i);
+          k_estimate<T, true><<<kEstimateBlocks, kEstimateThreads, 0, s>>>(A, x, cur, est + i);
         else
-          k_estimate<T, false><<<1024, kThreads, 0, s>>>(A, x, cur, est + i);
+          k_estimate<T, false><<<kEstimateBlocks, kEstimateThreads, 0, s>>>(A, x, cur, est + i);
       }
       if (timed) (void)hipEventRecord(ev[4 * i + 1], s);
       const bool grouped = sizeof(T) == 4 && bin_level && ng > 1;  // records in two column groups
