@@ -268,7 +268,9 @@ typedef struct agp_tuning {
                            expected draws each) from which an entry's sampled
                            suffix is deferred; 0: 64                            */
   int32_t sparse_shift; /* a level whose frontier holds fewer than n C / 2^k
-                           entries appends first contributions directly; 0: 5 */
+                           entries appends first contributions directly; 0: 5
+                           (at 5 not on calls of at most 2^18 cells without
+                           records, which keep copies of the residues)        */
   int32_t bin_shift;    /* (aggregation 2) a level whose estimated pushes reach
                            n C / 2^k is binned; 0: 3                            */
   int32_t capture;      /* 1: the level loop of each column tile (frontier
@@ -308,10 +310,10 @@ int agp_set_tuning(const agp_graph_t* g, int32_t C, double a, double b, const ag
  *   AGP_DENSE=0|1|auto   the dense field of agp_tuning_t;
  *   AGP_CAPTURE=0|1      the capture field of agp_tuning_t;
  *   AGP_RECORD_CAP=n     at most n push records per binned level, rounded up to
- *                        32 (their buffer is kept in 16 segments; per record
- *                        group on dense levels, split between the two groups
- *                        of frontier-list levels; records beyond it are added
- *                        with atomics);
+ *                        64 (their buffer is kept in 16 segments of four-record
+ *                        loads; per record group on dense levels, split between
+ *                        the two groups of frontier-list levels; records beyond
+ *                        it are added with atomics);
  *   AGP_RECORD_GROUPS=2  frontier-list levels keep their records in two
  *                        column groups even when n C < 2^31 (they always do
  *                        from n C >= 2^31 on: record cells are 31-bit);

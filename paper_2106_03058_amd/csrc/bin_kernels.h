@@ -15,8 +15,8 @@ namespace {
 
 // ------------------------------------------------ binned aggregation
 // After a binned level: bucket offsets (one block), then the records are
-// partitioned into buckets, then into bins of 8192 cells, and one block per
-// bin counts the signed records of every cell in LDS, adds count *
+// partitioned into buckets, then (where a bucket is more than one bin) into
+// bins of 8192 cells, and one block per bin counts the signed records of every cell in LDS, adds count *
 // fl(theta_c) in units to each cell (the deterministic pushes are already
 // there: integer sums, so the order is irrelevant) and appends every
 // non-zero cell to the next frontier.

@@ -634,15 +634,20 @@ __device__ __forceinline__ unsigned long long* count_row(const LevelArgs& A) {
 // across entries and batches.  All loops run in lockstep per wave so that
 // staging can use wave-wide ballots.
 //
-// What bounds it: VALU issue on the first level of a feature matrix (74% of
-// the cycles at 76 Gdraw/s), elsewhere VALU issue and the latency of the
-// dependent loads together (46% busy on dense transition levels), at four
-// waves per SIMD (127 VGPRs, 37 KB of LDS per block).  On levels with hubs
+// What bounds it: the draw loop's own steps (taking items, runs and emits
+// beside the draw) with lanes that wait for their wave: dense transition
+// levels make 129 Gdraw/s (runs and candidates), the first level of a feature
+// matrix 99, of the 382 that draws alone would; copies of such a level
+// without the record writes, the neighbour loads or the Philox rounds take 7,
+// 9 and 7% less.  The a = 0 kernels hold five waves per SIMD (at most 96
+// registers, 29 KB of LDS per block), those of a > 0 four (103 to 110).  On
+// levels with hubs
 // the longest lane used to be the bound: items of 16 windows are up to 1024
 // draws for one lane, and the 64 columns of a hub are one batch.  Items of
 // even draws and batch-wise deferral took a level of 64 Katz columns on a
 // 2^20-node R-MAT graph (47M draws) from 6.3 to 1.2 ms, the call from 148 to
-// 41 ms, and 64 ten-step transition columns on 2^22 nodes from 155 to 129 ms.
+// 41 ms, and 64 ten-step transition columns on 2^22 nodes from 155 to 129 ms
+// (90 with all that followed).
 constexpr int kBatch = kWave;
 constexpr int kMaxItemShift = 4;  // at most 16 windows per item
 constexpr int kItemMap = 128;

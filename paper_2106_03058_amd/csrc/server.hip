@@ -603,7 +603,7 @@ int agp_server_create(const agp_graph_t* g, const agp_server_config_t* cfg, agp_
   s->g = const_cast<agp_graph*>(g);
   s->cfg = *cfg;
   s->n = g->n;
-  s->S = cfg->max_slots;
+  s->S = std::min(cfg->max_slots, lvl::kMaxTileColumns);  // (slot numbers travel in 27 bits; more queries queue)
   s->shards = s->S < lvl::kServeShardSlots ? lvl::kServeShards : 1;
   s->t0 = std::chrono::steady_clock::now();
   s->slot_ticket.assign(s->S, 0);
