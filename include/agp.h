@@ -269,8 +269,9 @@ typedef struct agp_tuning {
                            suffix is deferred; 0: 64                            */
   int32_t sparse_shift; /* a level whose frontier holds fewer than n C / 2^k
                            entries appends first contributions directly; 0: 5
-                           (at 5 not on calls of at most 2^18 cells without
-                           records, which keep copies of the residues)        */
+                           (at 5 not on calls of at most 2^20 cells without
+                           records whose pushes could leave these levels,
+                           which keep copies of the residues)                 */
   int32_t bin_shift;    /* (aggregation 2) a level whose estimated pushes reach
                            n C / 2^k is binned; 0: 3                            */
   int32_t capture;      /* 1: the level loop of each column tile (frontier

@@ -378,16 +378,33 @@ __global__ void k_arc_factors(const uint32_t* __restrict__ nd, const double* __r
     out[j] = da[nd[j]];
 }
 
+constexpr int kSparseShift = 5;  // sparse levels: frontier below n C / 32
+
+// Pushes per level at most: one per arc and column, and for the
+// column-stochastic a = 0, b = 1 about 1 / eps per column (||r||_1 <=
+// ||x||_1 = theta / eps).
+inline double pushes_per_level(const agp_graph* g, double a, double b, double eps, int32_t C) {
+  return static_cast<double>(C) *
+         std::min(static_cast<double>(g->nnz), a == 0.0 && b == 1.0 ? 1.0 / eps : HUGE_VAL);
+}
+
 // Copies of the next residues, on calls of few cells that add with atomics
 // only: a power-law graph's pushes meet on its hubs, and atomics on one cache
 // line serialise at about 10 ns (on a graph of 10^4 nodes, where the sixteen
 // heaviest share a line, 35 of a level's 45 us).  Blocks add to the copies in
 // turn and k_merge adds them up as it lists the next frontier.  One PPR query
-// on 10^4 nodes takes 0.66 ms with 4 copies, 0.65 with 8, 0.89 without; at
-// 270,000 cells 4 copies gain 2%, above nothing, and the sparse levels, which
-// tell first touches by a cell's old value, would go.
+// on 10^4 nodes takes 0.66 ms with 4 copies, 0.65 with 8, 0.89 without (all
+// before its entries were dealt out); a cluster's estimate and sweep on 4e5
+// nodes 1.30 and 1.39, 30 queries on 3e4 nodes at eps = 1e-3 0.68 and 0.78;
+// beyond 2^20 cells gains and losses of 2% and less.
+// Calls whose pushes per level stay below the cut of the sparse levels keep
+// those (they tell first touches by a cell's old value) and one copy: at 3e5
+// cells and eps = 1e-3 0.44 ms, 0.49 with copies.
 constexpr int kCopies = 4;
-inline int residue_copies(size_t cells) { return cells <= kFewEntries ? kCopies : 1; }
+constexpr size_t kCopyCells = 1u << 20;
+inline int residue_copies(size_t cells, double level_pushes) {
+  return cells <= kCopyCells && level_pushes > static_cast<double>(cells >> kSparseShift) ? kCopies : 1;
+}
 
 // Adds the copies of every cell into the first one, clears the others and
 // lists the non-zero sums, one append per block of 4 x 256 cells.
@@ -498,7 +515,6 @@ __global__ __launch_bounds__(kWave) void k_fold_counts(const unsigned long long*
 }
 
 // ------------------------------------------------------------ driver
-constexpr int kSparseShift = 5;  // sparse levels: frontier below n C / 32
 constexpr int kBinShift = 3;     // binned levels: estimated pushes reach n C / 8
 // and at least 2^23: the record passes are eight launches, about 0.1 ms however
 // few the records, while plain atomics add 1.8e10 pushes a second (levels of 60
@@ -620,16 +636,13 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
   const size_t cell_bytes = sizeof(Cell) * (sizeof(T) == 4 ? 1 : 2);
   const int64_t tblocks = (n + kThetaRows - 1) / kThetaRows;
   // auto: no level can reach the record passes' cut when the call's pushes per
-  // level stay below it, at most one per arc and column, and for the
-  // column-stochastic a = 0, b = 1 about 1 / eps per column (||r||_1 <=
-  // ||x||_1 = theta / eps): then neither the estimate nor the passes run
-  const double level_pushes = static_cast<double>(C) *
-      std::min(static_cast<double>(g->nnz), a == 0.0 && b == 1.0 ? 1.0 / eps : HUGE_VAL);
+  // level stay below it: then neither the estimate nor the passes run
+  const double level_pushes = pushes_per_level(g, a, b, eps, C);
   const bool may_bin = sizeof(T) == 4 && (tune.aggregation == 1 ||
                                           (tune.aggregation == 2 && level_pushes >= kMinBinPushes));
   // copies of the next residues, on calls that add with atomics only (and
   // whose tuning leaves the sparse levels, which list first touches, alone)
-  int copies = !may_bin && tune.sparse_shift == kSparseShift ? residue_copies(cells) : 1;
+  int copies = !may_bin && tune.sparse_shift == kSparseShift ? residue_copies(cells, level_pushes) : 1;
   if (!may_alloc && sc.acc[0].bytes < cells * cell_bytes * copies) copies = 1;
   if ((rc = sc.acc[0].reserve(cells * cell_bytes * copies, true, s)) ||
       (rc = sc.acc[1].reserve(cells * cell_bytes * copies, true, s)) ||
@@ -1828,7 +1841,8 @@ int propagate_noalloc(agp_graph* g, double a, double b, const double* w, int32_t
                     cv.take(v.levelinfo, (2 * sizeof(double) + sizeof(int)) * (AGP_MAX_LEVELS + 2) + 256 +
                                               sizeof(LevelParams) * (AGP_MAX_LEVELS + 1));
   };
-  const bool fits = (residue_copies(cells) > 1 && carve(residue_copies(cells))) || carve(1);
+  const int copies = residue_copies(cells, pushes_per_level(g, a, b, eps, C));
+  const bool fits = (copies > 1 && carve(copies)) || carve(1);
   if (!fits)
     return fail(AGP_EINVAL, std::string(fn) + ": n * C = " + std::to_string(cells) + " cells need about " +
                                 std::to_string(cells * 2 * (sizeof(Cell) + sizeof(uint64_t))) +
