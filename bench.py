@@ -66,8 +66,8 @@ ALU_PEAK_GDRAWS = VALU_LANE_OPS / VALU_PER_DRAW / 1e9
 # sources they were taken from (the files that define k_level, k_det_big and
 # k_samp_big, code without comments) and the default tuning.
 TRAFFIC = {
-    "gnn-ppr-large": {"sources": "0fd3ed3950369b42", "columns": 128, "bytes_per_launch": 102346960000.0,
-                      "fetch_bytes": 85478380000.0, "write_bytes": 16868580000.0},
+    "gnn-ppr-large": {"sources": "1d44cb0d4c1254d3", "columns": 128, "bytes_per_launch": 103172180000.0,
+                      "fetch_bytes": 86299490000.0, "write_bytes": 16872680000.0},
 }
 KERNEL_SOURCES = ("paper_2106_03058_amd/csrc/level_kernels.h", "paper_2106_03058_amd/csrc/agp_device.h")
 
@@ -783,7 +783,7 @@ def level_roofline(runs, models, args, C) -> dict:
     if rec and rec["sources"] == kernel_sources_sha() and rec["columns"] == C and not args.tune and not dense:
         traffic = rec["bytes_per_launch"] / avg_s / 1e9
     kernel = ("k_dense_level (levels 0..L-1)" if dense else
-              "k_level<float, false, false, G> + k_det_big<float, G> + k_samp_big<float, G> (levels 1..L; "
+              "k_level<float, false, M, G> + k_det_big<float, M, G> + k_samp_big<float, M, G> (levels 1..L; M = 0 for a = 0, else 1; "
               "G = 2 record column groups on binned levels of tiles with n C >= 2^31, else 1)")
     alu = {"bound": "alu", "achieved": gdraws, "peak": ALU_PEAK_GDRAWS, "unit": "Gdraw/s",
            "frac": gdraws / ALU_PEAK_GDRAWS,
