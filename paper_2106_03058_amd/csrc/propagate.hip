@@ -378,6 +378,11 @@ __global__ void k_arc_factors(const uint32_t* __restrict__ nd, const double* __r
     out[j] = da[nd[j]];
 }
 
+__global__ void k_zero_words(unsigned long long* p, size_t nwords) {
+  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < nwords; i += (size_t)gridDim.x * blockDim.x)
+    p[i] = 0ull;
+}
+
 constexpr int kSparseShift = 5;  // sparse levels: frontier below n C / 32
 
 // Pushes per level at most: one per arc and column, and for the
@@ -663,6 +668,12 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
                                      sizeof(LevelParams) * (AGP_MAX_LEVELS + 1),
                                  false, s)))
     return rc;
+
+  if (!may_alloc) {  // a borrowed region keeps the last call's contents: the residues start at zero
+    const size_t words = cells * cell_bytes * copies / sizeof(unsigned long long);
+    for (DevBuf& acc : sc.acc)
+      k_zero_words<<<grid_for(static_cast<int64_t>(words), 256, 4096), 256, 0, s>>>(acc.as<unsigned long long>(), words);
+  }
 
   ColParams* cp = sc.colparams.as<ColParams>();
   uint32_t* dq = reinterpret_cast<uint32_t*>(cp + C);
@@ -1595,11 +1606,17 @@ int propagate_impl(agp_graph* g, double a, double b, const double* w, int32_t L,
     tune.dense = 0;
     tune.capture = 0;
   }
+  bool enqueued = false;
   auto run = [&]() -> int {
     if (stats) std::memset(stats, 0, sizeof(*stats));
+    // (before anything is enqueued: without may_alloc a missing table refuses the call)
+    const double* table = nullptr;
+    int rc = pow_table(g, a, &table, may_alloc);
+    if (rc != AGP_OK || (rc = pow_table(g, b, &table, may_alloc)) != AGP_OK) return rc;
+    enqueued = true;
     if constexpr (std::is_same<T, float>::value) {
       if (may_alloc && (tune.dense == 1 || (tune.dense == 2 && C >= 16))) {
-        const int rc = propagate_dense(g, fn, tune, a, b, rho, kappa, L, x, C, eps, seed, qids, out, s, stats);
+        rc = propagate_dense(g, fn, tune, a, b, rho, kappa, L, x, C, eps, seed, qids, out, s, stats);
         if (rc != kNotDense) {
           if (rc == AGP_OK && stats) {
             stats->levels = L;
@@ -1614,9 +1631,8 @@ int propagate_impl(agp_graph* g, double a, double b, const double* w, int32_t L,
     AGP_HIP(hipMemsetAsync(out, 0, cells * sizeof(T), s));
     for (int32_t c0 = 0; c0 < C; c0 += tile) {
       const int32_t ct = std::min(tile, C - c0);
-      const int rc = propagate_tile<T>(g, fn, tune, a, b, rho, kappa, L, x + c0, static_cast<long long>(C), ct,
-                                       eps, seed, qids ? qids + c0 : nullptr, static_cast<uint32_t>(c0), out + c0,
-                                       s, stats, sc, may_alloc);
+      rc = propagate_tile<T>(g, fn, tune, a, b, rho, kappa, L, x + c0, static_cast<long long>(C), ct, eps, seed,
+                             qids ? qids + c0 : nullptr, static_cast<uint32_t>(c0), out + c0, s, stats, sc, may_alloc);
       if (rc != AGP_OK) return rc;
     }
     if (stats) {
@@ -1634,6 +1650,8 @@ int propagate_impl(agp_graph* g, double a, double b, const double* w, int32_t L,
     g->scratch.release();
     rc = run();
   }
+  // what a call that fails has enqueued ends before another call may take its scratch
+  if (rc != AGP_OK && enqueued) (void)hipStreamSynchronize(s);
   return rc;
 }
 
@@ -1779,11 +1797,6 @@ constexpr int kNoAllocDevices = 64;
 std::mutex g_noalloc_mu[kNoAllocDevices];   // one call at a time per device (they share the array)
 void* g_noalloc_base[kNoAllocDevices] = {};  // device address of the array, per device
 
-__global__ void k_zero_words(unsigned long long* p, size_t nwords) {
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < nwords; i += (size_t)gridDim.x * blockDim.x)
-    p[i] = 0ull;
-}
-
 // Successive 256-byte aligned regions of [base, base + cap) as borrowed buffers.
 struct Carve {
   char* base;
@@ -1830,10 +1843,9 @@ int propagate_noalloc(agp_graph* g, double a, double b, const double* w, int32_t
   const int64_t tblocks = (n + kThetaRows - 1) / kThetaRows;
   Scratch v;
   // (with as many copies of the residues as the array holds beside the rest)
-  size_t acc_bytes = 0;
   auto carve = [&](int copies) {
     Carve cv{static_cast<char*>(g_noalloc_base[dev]), static_cast<size_t>(AGP_NOALLOC_SCRATCH_BYTES)};
-    acc_bytes = cells * sizeof(Cell) * copies;
+    const size_t acc_bytes = cells * sizeof(Cell) * copies;
     return cells <= (static_cast<size_t>(AGP_NOALLOC_SCRATCH_BYTES) / sizeof(Cell)) &&
                     cv.take(v.acc[0], acc_bytes) && cv.take(v.acc[1], acc_bytes) &&
                     cv.take(v.frontier[0], cells * sizeof(uint64_t)) &&
@@ -1856,12 +1868,7 @@ int propagate_noalloc(agp_graph* g, double a, double b, const double* w, int32_t
   v.count_rows.ptr = static_cast<char*>(g_noalloc_base[dev]) + AGP_NOALLOC_SCRATCH_BYTES;
   v.count_rows.bytes = kNoAllocCountBytes;
   v.count_rows.borrowed = true;
-  // the residue accumulators start at zero (the array keeps the last call's contents)
-  const size_t words = acc_bytes / sizeof(unsigned long long);
-  for (DevBuf& acc : v.acc)
-    k_zero_words<<<grid_for(static_cast<int64_t>(words > 0 ? words : 1), 256, 4096), 256, 0, s>>>(
-        acc.as<unsigned long long>(), words);
-  AGP_HIP(hipGetLastError());
+  // (the tile clears the residues, so a call that is refused enqueues nothing)
   return propagate_impl<float>(g, a, b, w, L, x, C, eps, seed, qids, out, s, nullptr, nullptr, false, &v, fn);
 }
 }  // namespace agp
