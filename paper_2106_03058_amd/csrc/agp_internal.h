@@ -66,6 +66,9 @@ struct Scratch {
   // start and end, and the end of the level's next frontier
   hipEvent_t events[4 * (AGP_MAX_LEVELS + 1)] = {};
   int ensure_events();
+  // acc[] of `copies` times `bytes` each, or, where they do not both fit, of
+  // one (copies is set to 1)
+  int reserve_acc(size_t bytes, int* copies, hipStream_t s);
   void release();
 };
 

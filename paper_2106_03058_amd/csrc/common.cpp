@@ -45,6 +45,20 @@ int Scratch::ensure_events() {
   return AGP_OK;
 }
 
+int Scratch::reserve_acc(size_t bytes, int* copies, hipStream_t s) {
+  int rc = AGP_OK;
+  if (*copies > 1) {
+    if ((rc = acc[0].reserve(bytes * *copies, true, s)) == AGP_OK) rc = acc[1].reserve(bytes * *copies, true, s);
+    if (rc != AGP_ENOMEM) return rc;
+    // one copy needs the room that a buffer of several would keep
+    acc[0].release();
+    acc[1].release();
+    *copies = 1;
+  }
+  if ((rc = acc[0].reserve(bytes, true, s)) == AGP_OK) rc = acc[1].reserve(bytes, true, s);
+  return rc;
+}
+
 void Scratch::release() {
   for (auto& e : events)
     if (e) {

@@ -649,13 +649,7 @@ int propagate_tile(agp_graph* g, const char* fn, const agp_tuning_t& tune, doubl
   // whose tuning leaves the sparse levels, which list first touches, alone)
   int copies = !may_bin && tune.sparse_shift == kSparseShift ? residue_copies(cells, level_pushes) : 1;
   if (!may_alloc && sc.acc[0].bytes < cells * cell_bytes * copies) copies = 1;
-  if (copies > 1 && (sc.acc[0].reserve(cells * cell_bytes * copies, true, s) ||
-                     sc.acc[1].reserve(cells * cell_bytes * copies, true, s))) {
-    (void)hipGetLastError();  // no room for them
-    copies = 1;
-  }
-  if ((rc = sc.acc[0].reserve(cells * cell_bytes * copies, true, s)) ||
-      (rc = sc.acc[1].reserve(cells * cell_bytes * copies, true, s)) ||
+  if ((rc = sc.reserve_acc(cells * cell_bytes, &copies, s)) ||
       (rc = sc.frontier[0].reserve(cells * sizeof(uint64_t), false, s)) ||
       (rc = sc.frontier[1].reserve(cells * sizeof(uint64_t), false, s)) ||
       (rc = sc.counts.reserve(sizeof(unsigned long long) * (AGP_MAX_LEVELS + 2), false, s)) ||
