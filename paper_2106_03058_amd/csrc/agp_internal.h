@@ -91,6 +91,7 @@ struct agp_graph {
   int32_t max_fdeg = 0;         // largest factor degree
   int device = 0;
   bool directed = false;        // built with AGP_DIRECTED
+  bool reversed = false;        // and AGP_REVERSE: row lengths differ from the factor degrees
   int64_t* row_ptr = nullptr;   // device int64[n + 1], rows in the push direction
   uint32_t* col = nullptr;      // device uint32[nnz], rows sorted by (factor degree, id)
   uint32_t* ndeg = nullptr;     // device uint32[nnz], factor degree of col[j]
