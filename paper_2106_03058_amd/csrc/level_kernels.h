@@ -985,7 +985,9 @@ __device__ __forceinline__ bool defer_slots(unsigned long long* ctr, unsigned lo
                                             unsigned long long* off) {
   const unsigned long long mask = wave_ballot(want);
   if (mask == 0ull) return false;
-  if ((__hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> kBigShift) >= cap) return false;
+  // (one value for the wave: other waves add to the counter, and the lanes scan together below)
+  const unsigned long long seen = uniform(__hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  if ((seen >> kBigShift) >= cap) return false;
   const int lane = lane_id();
   const unsigned long long inc = wave_scan(want ? work : 0ull);
   const unsigned long long total = last_lane(inc);
