@@ -40,7 +40,12 @@ __global__ __launch_bounds__(1024) void k_bins_scan(unsigned int* __restrict__ b
   unsigned int* bc = bucket_count + g * (kBuckets / gridDim.x);
   const unsigned long long v = t < nbk ? bc[t] : 0ull;
   if (t < nbk) bc[t] = 0;  // ready for the next level (zero unless this one was binned)
-  if (*mode != kModeBinned) return;  // (or another group overflowed)
+  // (one value for the block, which meets at barriers below: another group's
+  // block may be changing it)
+  __shared__ int s_mode;
+  if (t == 0) s_mode = __hip_atomic_load(mode, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  if (s_mode != kModeBinned) return;  // (or another group overflowed)
   unsigned long long all = 0;
   bool over = false;
   for (int k = 0; k < kRecSegs; ++k) {
