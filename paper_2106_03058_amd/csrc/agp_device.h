@@ -317,23 +317,6 @@ __device__ __forceinline__ double units_to_f64(U128 K, int ue) {
 
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
 
-// Append `item` for every active lane with `pred` to list[], reserving the
-// slots with one atomic per wave.  All active lanes must call it together.
-__device__ __forceinline__ void wave_append(uint64_t* __restrict__ list,
-                                            unsigned long long* __restrict__ count,
-                                            uint64_t item, bool pred) {
-  const unsigned long long mask = wave_ballot(pred);
-  if (mask == 0ull) return;
-  const int leader = __ffsll(static_cast<long long>(mask)) - 1;
-  unsigned long long base = 0;
-  if (lane_id() == leader) base = atomicAdd(count, static_cast<unsigned long long>(__popcll(mask)));
-  base = __shfl(base, leader);
-  if (pred) {
-    const unsigned long long below = mask & ((1ull << lane_id()) - 1ull);
-    list[base + static_cast<unsigned long long>(__popcll(below))] = item;
-  }
-}
-
 // Per-wave LDS staging of list entries: entries are gathered with ballots and
 // written out in chunks, one global atomic per chunk.  Every call must be
 // made by all lanes of the wave together (wave-uniform control flow).

@@ -674,7 +674,7 @@ struct BatchLds {
                                // a > 0: the first arc's factor when the entry has no
                                // deterministic push (its first run starts there), else 0
   long long doff[kBatch];      // deterministic pushes before each entry (exclusive scan)
-  uint32_t ioff[kBatch + 2];   // sampled work items before each entry
+  uint32_t ioff[kBatch];       // sampled work items before each entry
   // the entry's column parameters that its work items need (theta, the
   // random stream's counter word), so that taking an item reads LDS
   double th[kBatch];
@@ -774,7 +774,6 @@ __device__ __forceinline__ uint32_t queue_items(BatchLds& B, uint32_t iwork) {
   const int j1 = static_cast<int>(iinc < kItemMap ? iinc : kItemMap);
   for (int j = static_cast<int>(iinc - iwork < kItemMap ? iinc - iwork : kItemMap); j < j1; ++j)
     B.item_entry[j] = static_cast<uint8_t>(lane);
-  if (lane == kWave - 1) B.ioff[kBatch] = iinc;
   return last_lane(iinc);
 }
 
@@ -1191,7 +1190,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
       // lanes without an entry get no work items)
       B.th[lane] = cp.theta;
       B.ctr3[lane] = (cp.qid << 8) | static_cast<uint32_t>(kServe ? cp.level : A.level);
-          if (live) {
+      if (live) {
         if (kServe) {
           serve_live = true;
         } else {
