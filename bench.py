@@ -48,15 +48,19 @@ HBM_PEAK_GBPS = 8000.0
 # Vector ALU issue rate of MI355X: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz
 # = 39.32e12 lane-instructions/s (32-bit integer, binary32 and binary64
 # adds/multiplies/FMAs all issue at this rate on gfx950).  One random draw of
-# the sampling step is at least 103 such instructions: Philox4x32-10 (42,
-# with 32x32->64 multiply-adds), two 53-bit uniforms and the 7-step lifted
-# geometric skip (61), counted in the gfx950 assembly of a draw-only loop;
-# the skip table of each run, the acceptance test of each candidate and every
-# memory access come on top.  A level whose time goes to its draws is bound
-# by ALU_PEAK_DRAWS draws/s.
+# the sampling step is at least as many such instructions as the gfx950
+# assembly of a draw-only loop over agp_device.h holds: at a = 0 Philox4x32-10
+# without the words that no uniform reads (37), one 53-bit uniform (5) and the
+# skip below 64 (42); at a > 0 all of Philox (40), two uniforms (10) and the
+# same skip; dense levels take the 7-step skip, five more.  The loops run at
+# 98% of what these counts give (460 and 421 Gdraw/s measured, of 468 and
+# 427).  The skip table of each run, the acceptance test of each candidate and
+# every memory access come on top: a level whose time goes to its draws is
+# bound by its draws times their instructions over the issue rate.
 VALU_LANE_OPS = 256 * 4 * 16 * 2.4e9
-VALU_PER_DRAW = 103
-ALU_PEAK_GDRAWS = VALU_LANE_OPS / VALU_PER_DRAW / 1e9
+VALU_PER_DRAW_A0 = 84
+VALU_PER_DRAW = 92
+VALU_DENSE_SKIP = 5
 
 # HBM bytes per launch of the level kernel (levels 1..L with the launches
 # that make its deferred rows and suffixes), from two rocprofv3 --pmc runs
@@ -757,19 +761,23 @@ def level_roofline(runs, models, args, C) -> dict:
     launches that make its deferred rows and suffixes), or node-major dense
     levels 0..L-1 (level L only converts residues); one launch per level and
     column tile.  Two floors bound a launch: its random draws (runs +
-    candidates) at ALU_PEAK_GDRAWS, and its algorithmic bytes at the HBM
-    peak.  `bound` is the one with the larger floor (the larger fraction);
+    candidates) at the vector issue rate over the instructions of a draw
+    (weighted by draws where models with a = 0 and a > 0 take turns), and its
+    algorithmic bytes at the HBM peak.  `bound` is the one with the larger floor (the larger fraction);
     the other is reported beside it, with the measured HBM traffic while the
     kernel sources hash to the profiled ones."""
     dense = all(st["dense"] for r in runs for st, _ in r)
-    draws = lvl_ms = alg = 0.0
+    draws = ops = lvl_ms = alg = 0.0
     launches = 0
     for r in runs:
         for (st, _), m in zip(r, models):
             L = st["levels"]
             lv = range(0, L) if dense else range(1, L + 1)
+            per_draw = (VALU_PER_DRAW_A0 if m["a"] == 0.0 else VALU_PER_DRAW) + (VALU_DENSE_SKIP if dense else 0)
             for i in lv:
-                draws += float(st["runs"][i]) + float(st["cand"][i])
+                d = float(st["runs"][i]) + float(st["cand"][i])
+                draws += d
+                ops += d * per_draw
                 lvl_ms += float(st["level_ms"][i])
             alg += alg_bytes(st, lv, m["a"] == 0.0)
             launches += len(lv) * max(int(st["tiles"]), 1)
@@ -785,9 +793,11 @@ def level_roofline(runs, models, args, C) -> dict:
     kernel = ("k_dense_level (levels 0..L-1)" if dense else
               "k_level<float, false, M, G> + k_det_big<float, M, G> + k_samp_big<float, M, G> (levels 1..L; M = 0 for a = 0, else 1; "
               "G = 2 record column groups on binned levels of tiles with n C >= 2^31, else 1)")
-    alu = {"bound": "alu", "achieved": gdraws, "peak": ALU_PEAK_GDRAWS, "unit": "Gdraw/s",
-           "frac": gdraws / ALU_PEAK_GDRAWS,
-           "peak_derivation": f"{VALU_LANE_OPS:.4g} VALU lane-ops/s / {VALU_PER_DRAW} per draw",
+    per_draw = ops / draws if draws > 0 else VALU_PER_DRAW
+    peak = VALU_LANE_OPS / per_draw / 1e9
+    alu = {"bound": "alu", "achieved": gdraws, "peak": peak, "unit": "Gdraw/s",
+           "frac": gdraws / peak,
+           "peak_derivation": f"{VALU_LANE_OPS:.4g} VALU lane-ops/s / {per_draw:.4g} per draw",
            "draws_per_launch": draws / max(launches, 1)}
     hbm = {"bound": "hbm", "achieved": alg_gbps, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
            "frac": alg_gbps / HBM_PEAK_GBPS, "alg_bytes_per_launch": alg / max(launches, 1)}

@@ -636,8 +636,9 @@ __device__ __forceinline__ unsigned long long* count_row(const LevelArgs& A) {
 //
 // What bounds it: the draw loop's own steps (taking items, runs and emits
 // beside the draw) with lanes that wait for their wave: dense transition
-// levels make 129 Gdraw/s (runs and candidates), the first level of a feature
-// matrix 99, of the 382 that draws alone would; copies of such a level
+// levels make 129 Gdraw/s (runs and candidates) of the 460 that draws alone
+// make at a = 0, the first level of a feature matrix 99 of the 421 at a > 0
+// (draw-only loops of 84 and 92 vector instructions); copies of such a level
 // without the record writes, the neighbour loads or the Philox rounds take 7,
 // 9 and 7% less.  The a = 0 kernels hold five waves per SIMD (at most 96
 // registers, 29 KB of LDS per block), those of a > 0 four (103 to 110).  On
