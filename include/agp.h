@@ -183,7 +183,8 @@ int agp_graph_destroy(agp_graph_t* g);
  * fits beside them, 8 bytes per arc (reused while a and b stay the same).
  * Errors: AGP_EINVAL (bad sizes/ranges, non-finite x), AGP_ERANGE (a
  * residue outgrew the exact accumulators: contributions larger than about
- * 2^39 theta), AGP_ENOMEM, AGP_EDEVICE.  On AGP_EINVAL nothing is written; on
+ * 2^39 theta), AGP_ENOMEM, AGP_EDEVICE.  On AGP_EINVAL nothing is written
+ * (but out is cleared where x proves to hold a non-finite value); on
  * AGP_ERANGE the contents of out are unspecified. */
 int agp_propagate(const agp_graph_t* g, double a, double b, const double* w, int32_t L,
                   const float* x, int32_t C, double eps, uint64_t seed,
@@ -198,10 +199,12 @@ int agp_propagate_f64(const agp_graph_t* g, double a, double b, const double* w,
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc):
  * agp_propagate (binary32, same arguments, no stats) that allocates nothing.
- * Its buffers live in one fixed array of AGP_NOALLOC_SCRATCH_BYTES in the
- * library's static device memory, one copy per device, held until the
- * process ends; they take 32 bytes per cell, so n * C is limited to about
- * 2 million cells (AGP_EINVAL beyond, with the sizes in the message).  The
+ * Its buffers live in the library's static device memory, one copy per device,
+ * held until the process ends: AGP_NOALLOC_SCRATCH_BYTES for those that grow
+ * with the call and 1 MiB of counter rows.  The former take 32 bytes per cell,
+ * so n * C is limited to about 2 million cells (AGP_EINVAL beyond, with the
+ * sizes in the message); calls of few cells use and clear up to 80 bytes per
+ * cell (four copies of the residues) where that fits.  The
  * degree-power tables of (a, b) must already exist on g: any earlier
  * agp_propagate (or agp_autotune) on g with the same exponents makes them
  * (AGP_EINVAL otherwise).  It runs frontier lists with atomic aggregation
@@ -209,8 +212,8 @@ int agp_propagate_f64(const agp_graph_t* g, double a, double b, const double* w,
  * call on a device shares that device's array, which keeps the last call's
  * contents (each call clears what must start at zero): calls that overlapped
  * on one GPU would race, so the library runs them one at a time per device
- * (each returns only after its work on `stream` has finished).  Errors as
- * agp_propagate. */
+ * (each returns only after its work on `stream` has finished, also one that
+ * fails; a refused one puts none there).  Errors as agp_propagate. */
 #define AGP_NOALLOC_SCRATCH_BYTES (64u << 20)
 int agp_propagate_noalloc(const agp_graph_t* g, double a, double b, const double* w, int32_t L,
                           const float* x, int32_t C, double eps, uint64_t seed, const uint32_t* qids,
@@ -269,11 +272,13 @@ typedef struct agp_tuning {
                            suffix is deferred; 0: 64                            */
   int32_t sparse_shift; /* a level whose frontier holds fewer than n C / 2^k
                            entries appends first contributions directly; 0: 5
-                           (at 5 not on calls of at most 2^20 cells without
-                           records whose pushes could leave these levels,
-                           which keep copies of the residues)                 */
+                           (at 5, given or default, not on calls of at most
+                           2^20 cells without records whose pushes could leave
+                           these levels: they keep copies of the residues and
+                           list the next frontier as those are added up)      */
   int32_t bin_shift;    /* (aggregation 2) a level whose estimated pushes reach
-                           n C / 2^k is binned; 0: 3                            */
+                           n C / 2^k (2^(k-1) with two record groups), and at
+                           least 2^23, is binned; 0: 3                          */
   int32_t capture;      /* 1: the level loop of each column tile (frontier
                            lists) is captured once into a hipGraph per graph,
                            column count, level count, buffers and modes, and
@@ -285,8 +290,9 @@ typedef struct agp_tuning {
  * with the defaults (untimed), then once per candidate, timing each with HIP
  * events on `stream`: a coordinate descent over dense (0, 1), aggregation
  * (0, 1, 2), level_blocks (1024 .. 8192), tile_columns (all, C/2, C/4) and,
- * unless the dense levels won, big_row, big_items, sparse_shift and
- * bin_shift.  The fastest choice is kept for later agp_propagate calls on g
+ * unless the dense levels won, big_row, big_items, sparse_shift (where calls
+ * keep copies of the residues its 5 stands for those), bin_shift and capture.
+ * The fastest choice is kept for later agp_propagate calls on g
  * with the same column count and exponents (a, b).  `out` holds the result
  * on return (identical for every candidate).  *best (nullable) receives the
  * choice.  Errors as agp_propagate. */

@@ -320,7 +320,7 @@ __device__ __forceinline__ int lane_id() { return __lane_id(); }
 // Per-wave LDS staging of list entries: entries are gathered with ballots and
 // written out in chunks, one global atomic per chunk.  Every call must be
 // made by all lanes of the wave together (wave-uniform control flow).
-// 256: with 29 KB of LDS per block the a = 0 level kernel (91 registers) holds
+// 256: with 29 KB of LDS per block the a = 0 level kernel (90 registers) holds
 // five waves per SIMD (64 transition columns on 2^22 nodes: 102.9 ms, 106.8
 // with 512 entries and four).
 constexpr int kStage = 256;

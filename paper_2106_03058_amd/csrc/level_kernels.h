@@ -627,7 +627,7 @@ __device__ __forceinline__ unsigned long long* count_row(const LevelArgs& A) {
 // deterministic pushes with all lanes, one push per lane and step, and puts
 // the sampled work items in a queue that idle lanes draw from.  A sampled
 // work item is a run of 1 to 16 consecutive 64-position windows of one
-// entry's suffix, as many as are expected to take about kItemDraws draws (so
+// entry's suffix, as many as are expected to take about 64 draws (so
 // that no lane is left with a long chain while the others idle); a lane walks
 // their Philox / geometric-skip chains one draw per step and takes the next
 // item from the queue in the step after its last draw, so lanes stay busy
@@ -640,10 +640,10 @@ __device__ __forceinline__ unsigned long long* count_row(const LevelArgs& A) {
 // make at a = 0, the first level of a feature matrix 99 of the 421 at a > 0
 // (draw-only loops of 84 and 92 vector instructions); copies of such a level
 // without the record writes, the neighbour loads or the Philox rounds take 7,
-// 9 and 7% less.  The a = 0 kernels hold five waves per SIMD (at most 96
-// registers, 29 KB of LDS per block), those of a > 0 four (103 to 110).  On
-// levels with hubs
-// the longest lane used to be the bound: items of 16 windows are up to 1024
+// 9 and 7% less.  The a = 0 kernels of levels 1 on hold five waves per SIMD (90
+// registers, 94 with two record groups or binary64, of the 96 that five allow;
+// 29 KB of LDS per block); level 0 in binary32 (98 and 101), a > 0 (104 to 113)
+// and the server's (114) four.  On levels with hubs the longest lane used to be the bound: items of 16 windows are up to 1024
 // draws for one lane, and the 64 columns of a hub are one batch.  Items of
 // even draws and batch-wise deferral took a level of 64 Katz columns on a
 // 2^20-node R-MAT graph (47M draws) from 6.3 to 1.2 ms, the call from 148 to
@@ -1054,9 +1054,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
   int staged = 0;  // wave-uniform
   int seg = (blockIdx.x * kWaves + wave) & (kRecSegs - 1);  // wave-uniform: the next flush's record segment
 
-  // per-lane and per-wave counts stay far below 2^32 in one launch (at least
-  // 1024 waves share at most one candidate per arc and column of the level);
-  // the hash wraps mod 2^64
+  // 32 bits hold a launch's counts: 2^32 candidates of one wave are minutes of
+  // draws (a wave makes some 3e7 a second), and a lane's deterministic pushes
+  // are the prefixes (below 2^31) of the entries it sets up, one on levels of
+  // at most 2^18 entries and on larger ones one a batch of its wave, so that
+  // rows of 2^32 arcs in all would have to meet in one lane; the hash wraps
+  // mod 2^64
   uint32_t n_det = 0;
   uint32_t w_front = 0, w_cand = 0, w_acc = 0, w_runs = 0;  // wave-uniform (ballot counts)
   unsigned long long n_hash = 0;

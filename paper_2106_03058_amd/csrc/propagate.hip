@@ -184,7 +184,7 @@ __global__ __launch_bounds__(kThetaWaves* kWave) void k_theta_partial(const T* _
   __syncthreads();
   if (s_redo) {  // in row order: the workgroup stages rows in LDS, a lane adds its column
     constexpr int kPer = kThetaStage / (kThetaWaves * kWave);  // values per thread and chunk
-    const int rows = kThetaStage >> lw;                        // rows per chunk (at least 64, at most 4096)
+    const int rows = kThetaStage >> lw;                        // rows per chunk (256 to 16384, in binary64 128 to 8192)
     const int tr = static_cast<int>(threadIdx.x) >> lw, trstep = (kThetaWaves * kWave) >> lw;
     const int tc = static_cast<int>(blockIdx.y) * kWave + (threadIdx.x & (width - 1));
     auto load = [&](int64_t r1, T* v) {
@@ -408,7 +408,12 @@ inline double pushes_per_level(const agp_graph* g, double a, double b, double ep
 // beyond 2^20 cells gains and losses of 2% and less.
 // Calls whose pushes per level stay below the cut of the sparse levels keep
 // those (they tell first touches by a cell's old value) and one copy: at 3e5
-// cells and eps = 1e-3 0.44 ms, 0.49 with copies.
+// cells and eps = 1e-3 0.44 ms, 0.49 with copies.  All of this is at a = 0, b =
+// 1.  Elsewhere the bound on the pushes does not know eps, so every such call
+// takes copies, also one whose levels stay sparse: 3 sources on 3e5 nodes
+// (copies, sparse levels) at a = b = 0 and eps = 0.1, 1e-3, 1e-5 0.56 and 0.52,
+// 1.78 and 1.96, 3.35 and 3.83 ms; at (1, 0) 0.27 and 0.23, 0.38 and 0.31, 0.62
+// and 0.63; at (1/2, 1/2) 0.27 and 0.22, 0.37 and 0.31, 0.70 and 0.69.
 constexpr int kCopies = 4;
 constexpr size_t kCopyCells = 1u << 20;
 inline int residue_copies(size_t cells, double level_pushes) {
