@@ -70,8 +70,8 @@ VALU_DENSE_SKIP = 5
 # sources they were taken from (the files that define k_level, k_det_big and
 # k_samp_big, code without comments) and the default tuning.
 TRAFFIC = {
-    "gnn-ppr-large": {"sources": "1d44cb0d4c1254d3", "columns": 128, "bytes_per_launch": 103172180000.0,
-                      "fetch_bytes": 86299490000.0, "write_bytes": 16872680000.0},
+    "gnn-ppr-large": {"sources": "8aebf193e5ad8245", "columns": 128, "bytes_per_launch": 103202360000.0,
+                      "fetch_bytes": 86329610000.0, "write_bytes": 16872750000.0},
 }
 KERNEL_SOURCES = ("paper_2106_03058_amd/csrc/level_kernels.h", "paper_2106_03058_amd/csrc/agp_device.h")
 
