@@ -183,9 +183,9 @@ int agp_graph_destroy(agp_graph_t* g);
  * fits beside them, 8 bytes per arc (reused while a and b stay the same).
  * Errors: AGP_EINVAL (bad sizes/ranges, non-finite x), AGP_ERANGE (a
  * residue outgrew the exact accumulators: contributions larger than about
- * 2^39 theta), AGP_ENOMEM, AGP_EDEVICE.  On AGP_EINVAL nothing is written
- * (but out is cleared where x proves to hold a non-finite value); on
- * AGP_ERANGE the contents of out are unspecified. */
+ * 2^39 theta), AGP_ENOMEM, AGP_EDEVICE.  On AGP_EINVAL nothing is written,
+ * except that where x proves to hold a non-finite value, and on AGP_ERANGE, the
+ * contents of out are unspecified. */
 int agp_propagate(const agp_graph_t* g, double a, double b, const double* w, int32_t L,
                   const float* x, int32_t C, double eps, uint64_t seed,
                   const uint32_t* qids, float* out, void* stream, agp_stats_t* stats);
