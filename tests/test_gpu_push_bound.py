@@ -5,6 +5,8 @@ degrees count, and the call need not be ready for levels of many pushes.
 Along in-edges it can grow by in-degree over out-degree: such a call keeps its
 record buffers (seen in the device memory that a graph's first call takes) and
 equals the oracle."""
+import gc
+
 import numpy as np
 import pytest
 
@@ -48,10 +50,15 @@ def test_record_buffers_follow_the_push_bound(reverse, monkeypatch):
     for aggregation in ("atomic", "auto"):
         monkeypatch.setenv("AGP_AGGREGATION", aggregation)
         G = agp.Graph.from_inputs(g, directed=True, reverse=reverse)
+        gc.collect()  # (what the collector frees meanwhile would count)
         torch.cuda.synchronize()
-        free = torch.cuda.mem_get_info()[0]
-        _, st = agp.propagate(G, 0.0, 1.0, w, X, eps, 3, out=out, stats=True)
-        taken[aggregation] = free - torch.cuda.mem_get_info()[0]
+        gc.disable()
+        try:
+            free = torch.cuda.mem_get_info()[0]
+            _, st = agp.propagate(G, 0.0, 1.0, w, X, eps, 3, out=out, stats=True)
+            taken[aggregation] = free - torch.cuda.mem_get_info()[0]
+        finally:
+            gc.enable()
         ref, cnt = oracle.propagate(oracle.directed(g, reverse), 0.0, 1.0, w, x, eps, 3, wp=32, threads=8)
         assert np.array_equal(out.cpu().numpy().astype(np.float64), ref)
         for k in ("frontier", "hash", "det", "cand", "acc", "runs"):
